@@ -339,12 +339,11 @@ hipError_t m2l_spectral_tables(M2LSpectral* f, const std::vector<double*>& tab64
 // on = 1: the 16^3 leaf level's stencil (L = 4) sums each zone column in
 // FP32 (FP32 sources and kernel values) and the column sums in FP64.
 void m2l_spectral_set_f32(M2LSpectral* f, int on);
-// Pl (+)= the level-l zone sums of Ml over `offs` (noff per class: 8 classes
-// at levels >= 3, one at level 2); m64 / p64: the buffers hold doubles.
+// Pl (+)= the level-l zone sums of Ml (Sec. 2's zones, or the isolated
+// twin's); m64 / p64: the buffers hold doubles.
 // Parts for a timer: 0 the node transforms, 1 the stencil, 2 the inverse.
 hipError_t m2l_spectral_level(M2LSpectral* f, int l, const void* Ml, int m64, void* Pl, int p64,
-                              int accumulate, const int* offs, int noff, int isolated, hipStream_t st,
-                              KernelTimer* kt = nullptr);
+                              int accumulate, int isolated, hipStream_t st, KernelTimer* kt = nullptr);
 
 // FP64 -> FP32 copy of n elements.
 hipError_t launch_cast_d2f(const double* src, float* dst, int64_t n, hipStream_t st);

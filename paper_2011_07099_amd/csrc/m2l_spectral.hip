@@ -21,9 +21,7 @@
 // Layout: spectra of a level as [frequency / 8][node][frequency % 8]: a
 // node's transform writes (and its inverse reads) 128-byte runs, and the 8
 // frequencies of a chunk, whose stencil workgroups run on one XCD, share
-// every line of it.  In the stencil each wave handles
-// one parity class, so the offset, and with it the kernel value, is the same
-// across the wave.
+// every line of it.
 #include "internal.h"
 
 #include <vector>
@@ -35,8 +33,7 @@ struct M2LSpectral {
   int64_t F = 0;                 // (2p)^2 (p + 1) frequencies per node
   double2* spec = nullptr;       // [F][nodes] of the level being summed
   double2* out = nullptr;        // [F][nodes]
-  std::vector<double2*> khat;    // per level: [343][F], offsets of [-3, 3]^3
-  std::vector<double2*> khatT;   // per level: [F][kKT], the same values frequency by frequency
+  std::vector<double2*> khatT;   // per level: [F][kKT] kernel values, offsets of [-3, 3]^3 innermost
   float2* khatT32 = nullptr;     // the leaf level's khatT in FP32 (the FP32 16^3 stencil)
   int f32 = 0;                   // the 16^3 level's stencil in FP32 with FP64 column totals
   double2* dft[2] = {nullptr, nullptr};  // [343][F] DFT passes of the kernels
@@ -45,6 +42,7 @@ struct M2LSpectral {
 namespace {
 
 constexpr int kThreads = 256;
+constexpr int kFC = 8;    // frequencies per chunk of a spectrum
 constexpr int kKT = 344;  // kernel values per frequency in khatT (343 offsets, padded)
 
 inline unsigned nblk(int64_t n) { return (unsigned)((n + kThreads - 1) / kThreads); }
@@ -148,19 +146,7 @@ __device__ __forceinline__ int64_t xcd_node(int64_t g, int64_t nn) { return (g &
 
 // Spectrum element (frequency f, node) of a level with nn nodes.
 __device__ __forceinline__ int64_t sidx(int f, int64_t node, int64_t nn) {
-  return ((int64_t)(f >> 3) * nn + node) * 8 + (f & 7);
-}
-
-// Stencil block g: the 8 XCDs (blocks dealt round robin) take whole
-// 8-frequency chunks, all of a chunk's frequencies and tiles back to back.
-// The grid covers the chunks rounded up to a multiple of 8; false for the
-// blocks beyond the last chunk.
-__device__ __forceinline__ bool zone_block(int g, int tiles, int nchunk, int& k, int& tile) {
-  const int j = g >> 3;
-  const int chunk = (j / (8 * tiles)) * 8 + (g & 7);
-  k = chunk * 8 + (j / tiles) % 8;
-  tile = j % tiles;
-  return chunk < nchunk;
+  return ((int64_t)(f / kFC) * nn + node) * kFC + f % kFC;
 }
 
 // Forward transform of one node's p^3 gridlet (on the 2p cyclic grid, zero
@@ -304,13 +290,6 @@ __device__ __forceinline__ void cmac(double& re, double& im, double2 k, double2 
   im = fma(k.x, s.y, im);
   im = fma(k.y, s.x, im);
 }
-__device__ __forceinline__ void cmac(float& re, float& im, float2 k, float2 s) {
-  re = fmaf(k.x, s.x, re);
-  re = fmaf(-k.y, s.y, re);
-  im = fmaf(k.x, s.y, im);
-  im = fmaf(k.y, s.x, im);
-}
-
 // A wave-uniform FP32 value copied into a vector register, so that the
 // multiply-adds that use it take the two-operand form with all operands in
 // vector registers, which gfx950 issues at twice the rate of the forms with
@@ -325,183 +304,129 @@ template <class T> struct Vec2;
 template <> struct Vec2<double> { using type = double2; };
 template <> struct Vec2<float> { using type = float2; };
 
-// out_t(k) = sum_{d in zone(class of t)} khat_d(k) spec_{t+d}(k) for one
-// frequency k and one tile of T^3 targets; T = 8, or T = n = 4 on the 4^3
-// level (one class).  Blocks are dealt to the 8 XCDs round robin; block g
-// takes frequency 8 (g / 8 / tiles) + g % 8 and tile (g / 8) % tiles, so each
-// XCD runs all tiles of a frequency back to back and their overlapping halos
-// come from its L2.  The tile's source spectra with a
-// 3-node halo are staged in LDS (wrapped, or zero outside an isolated box).
-// Wave w handles the targets of class w (levels >= 3), so the offset list,
-// and the kernel value at k, is uniform across the wave.
-__global__ void __launch_bounds__(512) k_zone_spec(const double2* __restrict__ spec,
-                                                   const double2* __restrict__ khat,
-                                                   const int* __restrict__ offs, int noff, int n,
-                                                   int classes, int isolated, int64_t F,
-                                                   double2* __restrict__ out) {
-  __shared__ double2 box[14 * 14 * 14];
-  __shared__ double2 kk[343];        // this frequency's kernel values, all offsets of [-3, 3]^3
-  __shared__ int sof[8 * 316];       // the zone's offsets per class, as box steps and kernel index
-  const int T = n < 8 ? n : 8;
-  const int B = T + 6;
-  const int Bh = B / 2, H3 = Bh * Bh * Bh;  // parity-split box
-  const int64_t nn = (int64_t)n * n * n;
-  const int tpa = n / T;  // tiles per axis
-  const int tiles = tpa * tpa * tpa;
-  int k, tile;
-  if (!zone_block(blockIdx.x, tiles, (int)(F >> 3), k, tile)) return;
-  const int ox = (tile / (tpa * tpa)) * T, oy = ((tile / tpa) % tpa) * T, oz = (tile % tpa) * T;
-  const double2* sk = spec + sidx(k, 0, nn);  // node v at sk[8 v]
-  for (int i = threadIdx.x; i < 343; i += blockDim.x) kk[i] = khat[(int64_t)i * F + k];
-  // per (class, offset): the box position of the source of the class's first
-  // target (the others follow it by the lane's lattice step), and the kernel
-  for (int i = threadIdx.x; i < classes * noff; i += blockDim.x) {
-    const int pk = offs[i];
-    const int dx = ((pk >> 16) & 255) - 128, dy = ((pk >> 8) & 255) - 128, dz = (pk & 255) - 128;
-    int pos;
-    if (classes == 8) {
-      const int c = i / noff;
-      const int sx = (c >> 2) + dx + 3, sy = ((c >> 1) & 1) + dy + 3, sz = (c & 1) + dz + 3;
-      pos = (((sx & 1) * 2 + (sy & 1)) * 2 + (sz & 1)) * H3 + ((sx >> 1) * Bh + (sy >> 1)) * Bh + (sz >> 1);
-    } else {
-      pos = ((dx + 3) * B + (dy + 3)) * B + (dz + 3);
-    }
-    sof[i] = pos * 512 + ((dx + 3) * 49 + (dy + 3) * 7 + (dz + 3));
-  }
-  // With 8 classes the box is stored split by parity, [px][py][pz][hx][hy][hz]
-  // (coordinate 2h + p): for one offset, the 64 targets of a class (a 4^3
-  // lattice of step 2) then read 64 consecutive entries.  On the 4^3 level it
-  // is stored plainly.
-  for (int i = threadIdx.x; i < B * B * B; i += blockDim.x) {
-    const int bx = i / (B * B), by = (i / B) % B, bz = i % B;
-    const int x = ox + bx - 3, y = oy + by - 3, z = oz + bz - 3;
-    double2 v = make_double2(0.0, 0.0);
-    if (!isolated || ((unsigned)x < (unsigned)n && (unsigned)y < (unsigned)n && (unsigned)z < (unsigned)n)) {
-      const int xw = x & (n - 1), yw = y & (n - 1), zw = z & (n - 1);
-      v = sk[(((int64_t)xw * n + yw) * n + zw) * 8];
-    }
-    const int dst = classes == 8 ? (((bx & 1) * 2 + (by & 1)) * 2 + (bz & 1)) * H3 +
-                                       ((bx >> 1) * Bh + (by >> 1)) * Bh + (bz >> 1)
-                                 : i;
-    box[dst] = v;
-  }
-  __syncthreads();
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  int tx, ty, tz, cls;
-  if (classes == 8) {  // 4^3 targets of class `wave` in the 8^3 tile
-    cls = wave;
-    tx = 2 * (lane >> 4) + (cls >> 2);
-    ty = 2 * ((lane >> 2) & 3) + ((cls >> 1) & 1);
-    tz = 2 * (lane & 3) + (cls & 1);
-  } else {             // one class, the whole 4^3 level
-    cls = 0;
-    tx = lane >> 4;
-    ty = (lane >> 2) & 3;
-    tz = lane & 3;
-  }
-  const int* o = sof + cls * noff;
-  const int base = classes == 8 ? ((lane >> 4) * Bh + ((lane >> 2) & 3)) * Bh + (lane & 3)
-                                : (tx * B + ty) * B + tz;
-  double re = 0.0, im = 0.0;
-#pragma unroll 4
-  for (int i = 0; i < noff; ++i) {
-    const int w = o[i];
-    const double2 kd = kk[w & 511];
-    const double2 s = box[base + (w >> 9)];
-    re += kd.x * s.x - kd.y * s.y;
-    im += kd.x * s.y + kd.y * s.x;
-  }
-  out[sidx(k, ((int64_t)(ox + tx) * n + (oy + ty)) * n + (oz + tz), nn)] = make_double2(re, im);
+// The 16 x 16 x 4 FP64 matrix-core product d += a b.  Operands: lane l holds
+// a[l % 16][l / 16] and b[l / 16][l % 16].  Results: lane l holds column l % 16
+// of the rows 4 r + l / 16, in register r.
+typedef double v4d __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ v4d mma(double a, double b, v4d d) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, d, 0, 0, 0);
 }
 
-// The same sums on levels with n >= 8 nodes per axis (levels >= 3), tiles
-// of 8 x 8 x TZ targets (TZ = 16, or 8 on the 8^3 level): each lane owns two
-// targets of its class, 2 apart in z, and walks the zone by (dx, dy)
-// columns.  With TZ = 16 a wave is one class; with TZ = 8 a wave holds two
-// classes that differ only in z parity, so the column loops stay uniform.  Stored split by
-// parity, a full column (six consecutive dz) is two runs of three entries
-// per target, and the second target's runs are the first's shifted by one,
-// so four loads per parity plane serve both (8 loads for 12 multiply-adds).
-// Columns next to the target (|dx|, |dy| <= 1) keep the three dz outside the
-// near zone.  The zone of class c is {d : d_i in [-2 - c_i, 3 - c_i],
-// max |d_i| > 1} (Sec. 2), enumerated here directly.
-template <int TZ>
-__global__ void __launch_bounds__(TZ * 32) k_zone_spec2(const double2* __restrict__ spec,
-                                                        const double2* __restrict__ khat, int n,
-                                                        int isolated, int64_t F,
-                                                        double2* __restrict__ out) {
-  constexpr int TX = 8, BX = TX + 6, BZ = TZ + 6;
-  constexpr int KZ = TZ / 4;       // target pairs along z per class and (x, y)
-  constexpr int LPC = 16 * KZ;     // lanes per class
-  constexpr int HX = BX / 2, HZ = BZ / 2, H3 = HX * HX * HZ;
-  __shared__ double2 box[8 * H3];
-  __shared__ double2 kk[343];
+// The zones of a level as matrix products over octets.  The eight targets of
+// one parent see together the 6^3 children of the parent's 27 neighbours
+// (Sec. 2), s_i in [-2, 3] counted from the parent's first child; the pair
+// (source s, target t) is in the zone unless every |s_i - t_i| <= 1, and its
+// kernel is that of d = s - t.  So at one frequency the targets of all parents
+// are one product, complex [8 x 216] by [216 x parents], 189 / 216 of whose
+// kernel entries are in the zone (the others are zero): real
+// [16 x 432] by [432 x parents] with the rows (target, re / im), the columns
+// (source, re / im) and [re, -im; im, re] blocks, on the matrix cores in steps
+// of four columns (two sources neighbouring in z).  Both operands are read
+// from LDS at one address per lane plus a constant: the kernel's entry index
+// is linear in s and in t, the sources are split by child,
+// [px][py][pz][hx][hy][hz], where a step of s moves whole parents.
+//
+// One workgroup per (frequency, tile of HX x HY x HZ parents); a wave sums G
+// groups of 16 parents, which share the kernel operand.  WRAP: the tile is the
+// whole periodic level and parents wrap.  Else the tile has a halo of one
+// parent (wrapped, or zero outside an isolated box).
+//
+// Bound: the matrix cores (108 products of 64 cycles, FP64, per 16 parents and
+// frequency; they are busy 0.57-0.67 of the kernel) plus the staging, whose
+// 16-byte reads at a 128-byte stride do not all hide behind the products.  On
+// the vector ALUs, one lane per target and parity class, LDS reads (one per
+// multiply-add) and waits for scalar kernel loads were the bound.  Measured,
+// p = 8, before / after: 32^3 level 4.23 / 2.72 ms (1.14e11 flops), 8^3 level
+// 59 / 49 us, isolated 16^3 level at p = 4 77 / 55 us; the periodic 16^3 level
+// would take 330 us here against the 325 us of the runs along y below, which
+// keep it.  The same octets on the vector ALUs (kernel values by scalar loads)
+// took 2.6-2.9 ms and 57 us: as fast at 32^3, slower at 8^3, where a wave waits
+// for its scalar loads.
+template <int HX, int HY, int HZ, int G, bool WRAP>
+__global__ void __launch_bounds__(HX * HY * HZ * 4 / G, 4) k_zone_oct(
+    const double2* __restrict__ spec, const double2* __restrict__ khatT, int n, int isolated,
+    int nchunk, double2* __restrict__ out) {
+  constexpr int NP = HX * HY * HZ, NT = NP * 4 / G, HALO = WRAP ? 0 : 1;
+  constexpr int BX = HX + 2 * HALO, BY = HY + 2 * HALO, BZ = HZ + 2 * HALO, B3 = BX * BY * BZ;
+  static_assert(16 % HZ == 0 && (HY * HZ) % (16 * G) == 0, "a wave's groups share h_x, its lanes h_z");
+  __shared__ double2 box[8 * B3];
+  // kernel entry (dx, dy, dz) at (dx + 3) KX + (dy + 3) 7 + dz + 3: with planes
+  // of 51 entries the 8 targets' entries fall on different banks
+  constexpr int KX = 51;
+  __shared__ double2 kk[7 * KX];
+  const int hn = n >> 1;  // parents per axis
+  const int tpx = hn / HX, tpy = hn / HY, tpz = hn / HZ, tiles = tpx * tpy * tpz;
+  // the 8 XCDs (blocks dealt round robin) take whole chunks, a tile's kFC
+  // frequencies, which share their lines, back to back
+  const int blk = blockIdx.x >> 3;
+  const int chunk = (blk / (kFC * tiles)) * 8 + (blockIdx.x & 7);
+  if (chunk >= nchunk) return;
+  const int f = blk % kFC, tile = (blk / kFC) % tiles;
+  const int ox = (tile / (tpy * tpz)) * HX, oy = ((tile / tpz) % tpy) * HY, oz = (tile % tpz) * HZ;
   const int64_t nn = (int64_t)n * n * n;
-  const int tpx = n / TX, tpz = n / TZ;
-  const int tiles = tpx * tpx * tpz;
-  int k, tile;
-  if (!zone_block(blockIdx.x, tiles, (int)(F >> 3), k, tile)) return;
-  const int ox = (tile / (tpx * tpz)) * TX, oy = ((tile / tpz) % tpx) * TX, oz = (tile % tpz) * TZ;
-  const double2* sk = spec + sidx(k, 0, nn);  // node v at sk[8 v]
-  for (int i = threadIdx.x; i < 343; i += blockDim.x) kk[i] = khat[(int64_t)i * F + k];
-  for (int i = threadIdx.x; i < BX * BX * BZ; i += blockDim.x) {
-    const int bx = i / (BX * BZ), by = (i / BZ) % BX, bz = i % BZ;
-    const int x = ox + bx - 3, y = oy + by - 3, z = oz + bz - 3;
+  const double2* sk = spec + (int64_t)chunk * nn * kFC + f;  // node v at sk[kFC v]
+  for (int i = threadIdx.x; i < 8 * B3; i += NT) {
+    const int bz = i % (2 * BZ), by = (i / (2 * BZ)) % (2 * BY), bx = i / (4 * BZ * BY);
+    const int x = 2 * (ox - HALO) + bx, y = 2 * (oy - HALO) + by, z = 2 * (oz - HALO) + bz;
     double2 v = make_double2(0.0, 0.0);
-    if (!isolated || ((unsigned)x < (unsigned)n && (unsigned)y < (unsigned)n && (unsigned)z < (unsigned)n))
-      v = sk[(((int64_t)(x & (n - 1)) * n + (y & (n - 1))) * n + (z & (n - 1))) * 8];
-    box[(((bx & 1) * 2 + (by & 1)) * 2 + (bz & 1)) * H3 + ((bx >> 1) * HX + (by >> 1)) * HZ + (bz >> 1)] = v;
+    if (WRAP || !isolated ||
+        ((unsigned)x < (unsigned)n && (unsigned)y < (unsigned)n && (unsigned)z < (unsigned)n))
+      v = sk[(((int64_t)(x & (n - 1)) * n + (y & (n - 1))) * n + (z & (n - 1))) * kFC];
+    box[(((bx & 1) * 2 + (by & 1)) * 2 + (bz & 1)) * B3 + ((bx >> 1) * BY + (by >> 1)) * BZ + (bz >> 1)] = v;
+  }
+  for (int i = threadIdx.x; i < 343; i += NT) {
+    const int dx = i / 49 - 3, dy = (i / 7) % 7 - 3, dz = i % 7 - 3;
+    const bool near = abs(dx) <= 1 && abs(dy) <= 1 && abs(dz) <= 1;
+    kk[(dx + 3) * KX + i % 49] = near ? make_double2(0.0, 0.0) : khatT[(int64_t)(chunk * kFC + f) * kKT + i];
   }
   __syncthreads();
-  const int cls = threadIdx.x / LPC, lane = threadIdx.x % LPC;
-  const int cx = cls >> 2, cy = (cls >> 1) & 1, cz = cls & 1;
-  const int kx = lane / (4 * KZ), ky = (lane / KZ) % 4, kz = 2 * (lane % KZ);
-  const int base = (kx * HX + ky) * HZ + kz;
-  double r1 = 0.0, i1 = 0.0, r2 = 0.0, i2 = 0.0;
-  const int dz0 = -2 - cz;
-  for (int dx = -2 - cx; dx <= 3 - cx; ++dx) {
-    const int sx = cx + dx + 3;
-    for (int dy = -2 - cy; dy <= 3 - cy; ++dy) {
-      const int sy = cy + dy + 3;
-      const int pxy = ((sx & 1) * 2 + (sy & 1)) * 2;
-      const int col = base + ((sx >> 1) * HX + (sy >> 1)) * HZ;
-      const double2* kc = kk + (dx + 3) * 49 + (dy + 3) * 7 + (dz0 + 3);
-      if (abs(dx) > 1 || abs(dy) > 1) {
-        // dz0 + 2m: source z 1 + 2m (odd plane, h = m); dz0 + 2m + 1: z 2 + 2m (even, h = m + 1)
-        const double2* pa = box + (pxy + 1) * H3 + col;
-        const double2* pb = box + pxy * H3 + col + 1;
-        double2 a[4], b[4];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int col = lane & 15;                              // row of a, column of b
+  const int cs = (lane >> 4) & 1, pz = lane >> 5;         // step column: source component and z child
+  // a's row: target t = (tx, ty, tz) = (reg / 2, quad / 2, quad % 2), component reg % 2
+  const int ra = col >> 2, qa = col & 3;
+  const double* ka = &kk[0].x + (((3 - (ra >> 1)) * KX + (3 - (qa >> 1)) * 7 + 3 - (qa & 1) + pz) * 2 + ((ra & 1) ^ cs));
+  const bool neg = (ra & 1) == 0 && cs == 1;              // -im in the real rows
+  // b's column: a parent of each group
+  const int p0 = wave * G * 16;
+  const int hx = p0 / (HY * HZ), hz = col % HZ;
+  auto at = [](int h, int q, int H) { return WRAP ? (h + q) & (H - 1) : h + q + 1; };  // parent h + q
+  int zi[3], yi[G][3];
 #pragma unroll
-        for (int m = 0; m < 4; ++m) {
-          a[m] = pa[m];
-          b[m] = pb[m];
-        }
+  for (int q = 0; q < 3; ++q) {
+    zi[q] = (pz * B3 + at(hz, q - 1, HZ)) * 2 + cs;
 #pragma unroll
-        for (int m = 0; m < 3; ++m) {
-          const double2 ka = kc[2 * m], kb = kc[2 * m + 1];
-          cmac(r1, i1, ka, a[m]);
-          cmac(r1, i1, kb, b[m]);
-          cmac(r2, i2, ka, a[m + 1]);
-          cmac(r2, i2, kb, b[m + 1]);
-        }
-      } else {
+    for (int g = 0; g < G; ++g) yi[g][q] = at((p0 / HZ + (g * 16 + col) / HZ) % HY, q - 1, HY) * (BZ * 2);
+  }
+  v4d acc[G];
 #pragma unroll
-        for (int q = 0; q < 6; ++q) {
-          const int dz = dz0 + q;
-          if (dz >= -1 && dz <= 1) continue;
-          const int sz = 1 + q;
-          const double2* ps = box + (pxy + (sz & 1)) * H3 + col + (sz >> 1);
-          const double2 kd = kc[q], s1 = ps[0], s2 = ps[1];
-          cmac(r1, i1, kd, s1);
-          cmac(r2, i2, kd, s2);
-        }
+  for (int g = 0; g < G; ++g) acc[g] = v4d{0.0, 0.0, 0.0, 0.0};
+  for (int sx = -2; sx <= 3; ++sx) {
+    const double* bx = &box[0].x + ((sx & 1) * 4 * B3 + at(hx, sx >> 1, HX) * BY * BZ) * 2;
+    const double* kx = ka + sx * (2 * KX);
+#pragma unroll
+    for (int sy = -2; sy <= 3; ++sy) {
+      const double* by = bx + (sy & 1) * 4 * B3;
+#pragma unroll
+      for (int m = 0; m < 3; ++m) {  // sources s_z = 2 m - 2, 2 m - 1
+        double a = kx[sy * 14 + (2 * m - 2) * 2];
+        a = neg ? -a : a;
+#pragma unroll
+        for (int g = 0; g < G; ++g) acc[g] = mma(a, by[yi[g][(sy >> 1) + 1] + zi[m]], acc[g]);
       }
     }
   }
-  const int tx = ox + 2 * kx + cx, ty = oy + 2 * ky + cy, tz = oz + 2 * kz + cz;
-  double2* o = out + sidx(k, ((int64_t)tx * n + ty) * n + tz, nn);
-  o[0] = make_double2(r1, i1);
-  o[16] = make_double2(r2, i2);  // node tz + 2
+  double2* o = out + (int64_t)chunk * nn * kFC + f;
+  const int q = lane >> 4;  // results: target (reg / 2, q / 2, q % 2), component reg % 2
+#pragma unroll
+  for (int g = 0; g < G; ++g) {
+    const int hy = (p0 / HZ + (g * 16 + col) / HZ) % HY;
+#pragma unroll
+    for (int tx = 0; tx < 2; ++tx) {
+      const int x = 2 * (ox + hx) + tx, y = 2 * (oy + hy) + (q >> 1), z = 2 * (oz + hz) + (q & 1);
+      o[(((int64_t)x * n + y) * n + z) * kFC] = make_double2(acc[g][2 * tx], acc[g][2 * tx + 1]);
+    }
+  }
 }
 
 // Whole-level stencil, targets in runs along y (used for the 16^3 level, n =
@@ -645,137 +570,36 @@ __global__ void __launch_bounds__(8 * (H * H * H / TY), sizeof(T) == 4 ? 4 : 8) 
   }
 }
 
-// Whole-level stencil, targets in runs along z (used for the 8^3 level, n =
-// 2H = 8): one workgroup per frequency holds the level's whole spectrum at that
-// frequency in LDS (n^3 values: periodic wrap, no halo) and sums every
-// target's zone.  Stored split by parity ([px][py][pz][hx][hy][hz], node
-// coordinate 2h + p), rows of H values (hz) XOR-swizzled by the row index so
-// that the lanes of a wave, which read one hz from H different rows, hit
-// distinct banks.  Two (H = 8) or one (H = 4) waves per parity class: the
-// class, the zone's offsets and so every kernel value are uniform across a
-// wave, and the kernel values come from the frequency's contiguous row of
-// khatT by scalar loads, leaving LDS to the sources.  A lane owns TZ targets
-// of its class consecutive in hz (2 apart in z); walking the zone by (dx, dy)
-// columns, each parity plane of a column is one run of TZ + 2 source values
-// shared by the TZ targets (three offsets per target and plane).  Columns
-// next to the target (|dx|, |dy| <= 1) skip the three dz of the near zone.
-// Blocks are dealt to the 8 XCDs so that the 8 frequencies of a chunk, which
-// share every 128-byte line of the spectra, run on one XCD back to back.
-template <int H, int TZ>
-__global__ void __launch_bounds__(8 * (H * H * H / TZ), 8) k_zone_level_z(
-    const double2* __restrict__ spec, const double2* __restrict__ khatT, int64_t F, int nchunk,
-    double2* __restrict__ out) {
-  constexpr int n = 2 * H, nn = n * n * n;
-  constexpr int LPC = H * H * H / TZ;   // lanes per class
-  constexpr int NT = 8 * LPC;
-  static_assert(LPC % 64 == 0, "a class fills whole waves");
-  static_assert(H % TZ == 0, "whole target runs");
-  __shared__ double2 box[nn];
-  const int g = blockIdx.x;
-  const int chunk = ((g >> 3) >> 3) * 8 + (g & 7);
-  if (chunk >= nchunk) return;
-  const int k = chunk * 8 + ((g >> 3) & 7);
-  const double2* sk = spec + (int64_t)(k >> 3) * nn * 8 + (k & 7);  // node v at sk[8 v]
-  // stage: node (x, y, z) -> parity block, row (hx, hy), swizzled hz
-  for (int v = threadIdx.x; v < nn; v += NT) {
-    const int x = v / (n * n), y = (v / n) % n, z = v % n;
-    const int row = (((x & 1) * 2 + (y & 1)) * 2 + (z & 1)) * H * H + (x >> 1) * H + (y >> 1);
-    box[row * H + ((z >> 1) ^ (row & (H - 1)))] = sk[(int64_t)v * 8];
-  }
-  __syncthreads();
-  const int cls = __builtin_amdgcn_readfirstlane(threadIdx.x / LPC);
-  const int cx = cls >> 2, cy = (cls >> 1) & 1, cz = cls & 1;
-  const int lane = threadIdx.x % LPC;
-  const int hx = lane / (H * (H / TZ)), hy = (lane / (H / TZ)) % H, hz0 = (lane % (H / TZ)) * TZ;
-  const double2* kf = khatT + (int64_t)k * kKT;
-  double re[TZ], im[TZ];
-#pragma unroll
-  for (int t = 0; t < TZ; ++t) re[t] = im[t] = 0.0;
-  // one parity plane of a column: source half-z hz0 - 1 + j (j < TZ + 2);
-  // target t reads j = t + m with the kernel of offset index kidx[m]
-  auto plane = [&](int rowbase, int kbase, int pz, bool m0, bool m1, bool m2) {
-    double2 src[TZ + 2];
-    const int row = rowbase + pz * H * H;
-#pragma unroll
-    for (int j = 0; j < TZ + 2; ++j)
-      src[j] = box[row * H + (((hz0 - 1 + j) & (H - 1)) ^ (row & (H - 1)))];
-    // offset dz = sz - cz with sz = 2 m - 2 + pz (m = 0, 1, 2)
-#pragma unroll
-    for (int m = 0; m < 3; ++m) {
-      if ((m == 0 && !m0) || (m == 1 && !m1) || (m == 2 && !m2)) continue;
-      const double2 kd = kf[kbase + (2 * m - 2 + pz - cz + 3)];
-#pragma unroll
-      for (int t = 0; t < TZ; ++t) cmac(re[t], im[t], kd, src[t + m]);
-    }
-  };
-  for (int sx = -2; sx <= 3; ++sx) {      // source x = 2 hx + cx + dx, sx = cx + dx
-    const int dx = sx - cx;
-    const int rx = ((hx + (sx >> 1)) & (H - 1)) * H;
-    for (int sy = -2; sy <= 3; ++sy) {
-      const int dy = sy - cy;
-      const int rowbase = ((sx & 1) * 4 + (sy & 1) * 2) * H * H + rx + ((hy + (sy >> 1)) & (H - 1));
-      const int kbase = (dx + 3) * 49 + (dy + 3) * 7;
-      if (abs(dx) > 1 || abs(dy) > 1) {
-        plane(rowbase, kbase, 0, true, true, true);
-        plane(rowbase, kbase, 1, true, true, true);
-      } else if (cz == 0) {  // keep sz = -2, 2 (even) and 3 (odd)
-        plane(rowbase, kbase, 0, true, false, true);
-        plane(rowbase, kbase, 1, false, false, true);
-      } else {               // keep sz = -2 (even), -1 and 3 (odd)
-        plane(rowbase, kbase, 0, true, false, false);
-        plane(rowbase, kbase, 1, true, false, true);
-      }
-    }
-  }
-  double2* o = out + (int64_t)(k >> 3) * nn * 8 + (k & 7);
-#pragma unroll
-  for (int t = 0; t < TZ; ++t) {
-    const int z = 2 * (hz0 + t) + cz;
-    const int v = ((2 * hx + cx) * n + (2 * hy + cy)) * n + z;
-    o[(int64_t)v * 8] = make_double2(re[t], im[t]);
-  }
-}
-
-// The 4^3 level (37 offsets periodic, 316 isolated), one workgroup per
-// 8-frequency chunk: each thread loads one node's 8 frequencies (one 128-byte
-// line) and then sums one target's zone at one frequency.  Kernel values of
-// the zone's offsets for the chunk come from khatT.
-__global__ void __launch_bounds__(512) k_zone_l2(const double2* __restrict__ spec,
+// The 4^3 level (37 offsets periodic, 316 isolated): one wave per frequency,
+// lane t the target node t, sources and kernel values in LDS.  The zone:
+// periodic, each of the level's nodes once, d_i in [-2, 1]; isolated, d_i in
+// [-3, 3] and sources inside the box; always max |d_i| > 1 (Sec. 2).
+template <bool ISO>
+__global__ void __launch_bounds__(256) k_zone_l2(const double2* __restrict__ spec,
                                                  const double2* __restrict__ khatT,
-                                                 const int* __restrict__ offs, int noff, int isolated,
-                                                 int nchunk, double2* __restrict__ out) {
-  __shared__ double2 box[8 * 64];        // [frequency in chunk][node]
-  __shared__ double2 kk[8 * 316];        // [frequency in chunk][zone offset]
-  __shared__ int so[316];                // packed offsets
-  const int chunk = blockIdx.x;
-  if (chunk >= nchunk) return;
-  const double2* sk = spec + (int64_t)chunk * 64 * 8;
-  for (int i = threadIdx.x; i < 512; i += 512) box[(i & 7) * 64 + (i >> 3)] = sk[i];
-  for (int i = threadIdx.x; i < noff; i += 512) so[i] = offs[i];
+                                                 double2* __restrict__ out) {
+  __shared__ double2 box[4][64];
+  __shared__ double2 kk[4][kKT];
+  const int w = threadIdx.x >> 6, t = threadIdx.x & 63, k = blockIdx.x * 4 + w;
+  box[w][t] = spec[sidx(k, t, 64)];
+  for (int i = t; i < kKT; i += 64) kk[w][i] = khatT[(int64_t)k * kKT + i];
   __syncthreads();
-  for (int i = threadIdx.x; i < 8 * noff; i += 512) {
-    const int f = i / noff, d = i % noff;
-    const int pk = so[d];
-    const int dx = ((pk >> 16) & 255) - 128, dy = ((pk >> 8) & 255) - 128, dz = (pk & 255) - 128;
-    kk[f * 316 + d] = khatT[(int64_t)(chunk * 8 + f) * kKT + (dx + 3) * 49 + (dy + 3) * 7 + (dz + 3)];
-  }
-  __syncthreads();
-  const int f = threadIdx.x >> 6, t = threadIdx.x & 63;
   const int tx = t >> 4, ty = (t >> 2) & 3, tz = t & 3;
+  constexpr int D0 = ISO ? -3 : -2, D1 = ISO ? 3 : 1;
   double re = 0.0, im = 0.0;
-  for (int d = 0; d < noff; ++d) {
-    const int pk = so[d];
-    const int x = tx + ((pk >> 16) & 255) - 128, y = ty + ((pk >> 8) & 255) - 128,
-              z = tz + (pk & 255) - 128;
-    if (isolated && ((unsigned)x > 3u || (unsigned)y > 3u || (unsigned)z > 3u)) continue;
-    const double2 kd = kk[f * 316 + d];
-    const double2 sv = box[f * 64 + (((x & 3) * 4 + (y & 3)) * 4 + (z & 3))];
-    re = fma(kd.x, sv.x, re);
-    re = fma(-kd.y, sv.y, re);
-    im = fma(kd.x, sv.y, im);
-    im = fma(kd.y, sv.x, im);
-  }
-  out[(int64_t)chunk * 64 * 8 + t * 8 + f] = make_double2(re, im);
+#pragma unroll
+  for (int dx = D0; dx <= D1; ++dx)
+#pragma unroll
+    for (int dy = D0; dy <= D1; ++dy)
+#pragma unroll
+      for (int dz = D0; dz <= D1; ++dz) {
+        if (dx >= -1 && dx <= 1 && dy >= -1 && dy <= 1 && dz >= -1 && dz <= 1) continue;
+        const int x = tx + dx, y = ty + dy, z = tz + dz;
+        double2 sv = box[w][((x & 3) * 4 + (y & 3)) * 4 + (z & 3)];
+        if (ISO && ((unsigned)x > 3u || (unsigned)y > 3u || (unsigned)z > 3u)) sv = make_double2(0.0, 0.0);
+        cmac(re, im, kk[w][(dx + 3) * 49 + (dy + 3) * 7 + dz + 3], sv);
+      }
+  out[sidx(k, t, 64)] = make_double2(re, im);
 }
 
 // khatT in FP32.
@@ -784,20 +608,10 @@ __global__ void k_khat_f32(const double2* __restrict__ in, int64_t n, float2* __
   if (i < n) out[i] = make_float2((float)in[i].x, (float)in[i].y);
 }
 
-// khatT[f][d] = khat[d][f] (d < 343; the pad entry is zero).
-__global__ void k_khat_transpose(const double2* __restrict__ khat, int64_t F,
-                                 double2* __restrict__ khatT) {
-  const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (i >= F * kKT) return;
-  const int64_t f = i / kKT;
-  const int d = (int)(i % kKT);
-  khatT[i] = d < 343 ? khat[(int64_t)d * F + f] : make_double2(0.0, 0.0);
-}
-
 // Kernel spectrum of offset d (FP64 separable DFT): first pass along z of
 // K_d[x][y][z] = tab[w(x) - p dx][w(y) - p dy][w(z) - p dz] (tab centred at
-// C), zero on the unused slot p; then y and x (k_sdft_axis); stored scaled in
-// the frequency order of k_node_fwd.
+// C), zero on the unused slot p; then y and x (k_sdft_axis); stored scaled
+// frequency by frequency, in the order of k_node_fwd (k_sdft_store).
 __global__ void k_sdft_z(const double* __restrict__ tab, int p, int C, double2* __restrict__ A) {
   const int M = 2 * p, H = p + 1;
   const int64_t F = (int64_t)M * M * H;
@@ -844,16 +658,17 @@ __global__ void k_sdft_axis(const double2* __restrict__ in, int p, int axis, dou
   out[i] = make_double2(re, im);
 }
 
-__global__ void k_sdft_store(const double2* __restrict__ in, int p, double scale, double2* __restrict__ out) {
+__global__ void k_sdft_store(const double2* __restrict__ in, int p, double scale, double2* __restrict__ khatT) {
   const int M = 2 * p, H = p + 1;
   const int64_t F = (int64_t)M * M * H;
-  in += blockIdx.y * F;
-  out += blockIdx.y * F;
+  const int di = blockIdx.y;
+  in += di * F;
   const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   if (i >= F) return;
   const int kz = (int)(i % H), ky = (int)((i / H) % M), kx = (int)(i / ((int64_t)H * M));
   const int64_t d = ((int64_t)(kx * 2 + (ky & 1)) * p + (ky >> 1)) * H + kz;
-  out[d] = make_double2(in[i].x * scale, in[i].y * scale);
+  khatT[d * kKT + di] = make_double2(in[i].x * scale, in[i].y * scale);
+  if (di == 342) khatT[d * kKT + 343] = make_double2(0.0, 0.0);  // padding
 }
 
 inline hipError_t tbegin(KernelTimer* kt, hipStream_t st) { return kt ? kt->begin(st) : hipSuccess; }
@@ -862,9 +677,31 @@ inline hipError_t tend(KernelTimer* kt, hipStream_t st, int part, hipError_t e) 
   return kt->end(st, part);
 }
 
+template <int HX, int HY, int HZ, int G, bool WRAP>
+void zone_oct_as(const M2LSpectral* f, int l, int n, int isolated, int nchunk, hipStream_t st) {
+  const int hn = n / 2, tiles = (hn / HX) * (hn / HY) * (hn / HZ);
+  // the chunks rounded up to a multiple of 8, times their frequencies, per tile
+  const unsigned grid = (unsigned)((nchunk + 7) / 8 * 8 * kFC) * (unsigned)tiles;
+  k_zone_oct<HX, HY, HZ, G, WRAP><<<grid, HX * HY * HZ * 4 / G, 0, st>>>(f->spec, f->khatT[l], n,
+                                                                         isolated, nchunk, f->out);
+}
+
+// The octet products of a level of n >= 8 nodes per axis: the periodic 8^3
+// level is one tile; other levels take tiles of 4 x 4 x 8 parents (4^3 on the
+// isolated 8^3 level) with a halo (46 KiB, three tiles per CU: while one
+// stages its sources another multiplies).
+void zone_oct(const M2LSpectral* f, int l, int n, int isolated, int nchunk, hipStream_t st) {
+  if (n == 8 && !isolated)
+    zone_oct_as<4, 4, 4, 1, true>(f, l, n, isolated, nchunk, st);
+  else if (n == 8)
+    zone_oct_as<4, 4, 4, 1, false>(f, l, n, isolated, nchunk, st);
+  else
+    zone_oct_as<4, 4, 8, 2, false>(f, l, n, isolated, nchunk, st);
+}
+
 template <int P>
 hipError_t run_level(M2LSpectral* f, int l, const void* Ml, int m64, void* Pl, int p64,
-                     int accumulate, const int* offs, int noff, int isolated, hipStream_t st,
+                     int accumulate, int isolated, hipStream_t st,
                      KernelTimer* kt) {
   const int n = 1 << l;
   const int64_t nn = (int64_t)n * n * n;
@@ -886,30 +723,19 @@ hipError_t run_level(M2LSpectral* f, int l, const void* Ml, int m64, void* Pl, i
   e = tend(kt, st, 0, hipGetLastError());
   if (e == hipSuccess) e = tbegin(kt, st);
   if (e != hipSuccess) return e;
-  const int classes = l == 2 ? 1 : 8;
-  // blocks per tile: the 8-frequency chunks rounded up to a multiple of 8, times 8
-  const int64_t per_tile = (f->F / 8 + 7) / 8 * 64;
-  const int nchunk = (int)(f->F / 8);
+  const int nchunk = (int)(f->F / kFC);
   const unsigned cgrid = (unsigned)((nchunk + 7) / 8 * 64);  // chunks rounded up to 8, times 8
   if (f32) {  // FP32 columns
     k_zone_level_y<8, 8, float, float2><<<cgrid, 512, 0, st>>>(spec32, f->khatT32, f->F, nchunk, out32);
   } else if (n == 16 && !isolated) {  // the whole level per frequency, eight targets per lane
     k_zone_level_y<8, 8><<<cgrid, 512, 0, st>>>(f->spec, f->khatT[l], f->F, nchunk, f->out);
-  } else if (n == 8 && !isolated) {
-    k_zone_level_z<4, 1><<<cgrid, 512, 0, st>>>(f->spec, f->khatT[l], f->F, nchunk, f->out);
   } else if (n == 4) {
-    k_zone_l2<<<(unsigned)nchunk, 512, 0, st>>>(f->spec, f->khatT[l], offs, noff, isolated, nchunk,
-                                                 f->out);
-  } else if (n >= 16) {  // 8 x 8 x 16 tiles, two targets per lane
-    const unsigned grid = (unsigned)(per_tile * (n / 8) * (n / 8) * (n / 16));
-    k_zone_spec2<16><<<grid, 512, 0, st>>>(f->spec, f->khat[l], n, isolated, f->F, f->out);
-  } else if (n == 8) {  // the 8^3 level as one tile, two targets per lane
-    k_zone_spec2<8><<<(unsigned)per_tile, 256, 0, st>>>(f->spec, f->khat[l], n, isolated, f->F, f->out);
+    if (isolated)
+      k_zone_l2<true><<<(unsigned)(f->F / 4), 256, 0, st>>>(f->spec, f->khatT[l], f->out);
+    else
+      k_zone_l2<false><<<(unsigned)(f->F / 4), 256, 0, st>>>(f->spec, f->khatT[l], f->out);
   } else {
-    const int T = n < 8 ? n : 8;
-    const unsigned grid = (unsigned)(per_tile * (n / T) * (n / T) * (n / T));
-    k_zone_spec<<<grid, classes == 8 ? 512 : 64, 0, st>>>(f->spec, f->khat[l], offs, noff, n, classes,
-                                                           isolated, f->F, f->out);
+    zone_oct(f, l, n, isolated, nchunk, st);
   }
   e = tend(kt, st, 1, hipGetLastError());
   if (e == hipSuccess) e = tbegin(kt, st);
@@ -931,7 +757,6 @@ void m2l_spectral_destroy(M2LSpectral* f) {
   if (!f) return;
   (void)hipFree(f->spec);
   (void)hipFree(f->out);
-  for (double2* k : f->khat) (void)hipFree(k);
   for (double2* k : f->khatT) (void)hipFree(k);
   (void)hipFree(f->khatT32);
   for (double2* d : f->dft) (void)hipFree(d);
@@ -946,13 +771,10 @@ hipError_t m2l_spectral_create(int L, int p, M2LSpectral** out) {
   f->p = p;
   f->F = (int64_t)(2 * p) * (2 * p) * (p + 1);
   const int64_t nodes = (int64_t)1 << (3 * L);
-  f->khat.assign(L + 1, nullptr);
   f->khatT.assign(L + 1, nullptr);
   hipError_t e = hipMalloc(&f->spec, (size_t)(f->F * nodes) * sizeof(double2));
   if (e == hipSuccess) e = hipMalloc(&f->out, (size_t)(f->F * nodes) * sizeof(double2));
   for (int d = 0; d < 2 && e == hipSuccess; ++d) e = hipMalloc(&f->dft[d], (size_t)(343 * f->F) * sizeof(double2));
-  for (int l = 2; l <= L && e == hipSuccess; ++l)
-    e = hipMalloc(&f->khat[l], (size_t)(343 * f->F) * sizeof(double2));
   for (int l = 2; l <= L && e == hipSuccess; ++l)
     e = hipMalloc(&f->khatT[l], (size_t)(kKT * f->F) * sizeof(double2));
   if (e == hipSuccess && L == 4) e = hipMalloc(&f->khatT32, (size_t)(kKT * f->F) * sizeof(float2));
@@ -975,8 +797,7 @@ hipError_t m2l_spectral_tables(M2LSpectral* f, const std::vector<double*>& tab64
     k_sdft_z<<<grid, kThreads, 0, st>>>(tab64[l], p, C, f->dft[0]);
     k_sdft_axis<<<grid, kThreads, 0, st>>>(f->dft[0], p, 1, f->dft[1]);
     k_sdft_axis<<<grid, kThreads, 0, st>>>(f->dft[1], p, 0, f->dft[0]);
-    k_sdft_store<<<grid, kThreads, 0, st>>>(f->dft[0], p, scale, f->khat[l]);
-    k_khat_transpose<<<nblk(f->F * kKT), kThreads, 0, st>>>(f->khat[l], f->F, f->khatT[l]);
+    k_sdft_store<<<grid, kThreads, 0, st>>>(f->dft[0], p, scale, f->khatT[l]);
     if (l == f->L && f->khatT32)
       k_khat_f32<<<nblk(f->F * kKT), kThreads, 0, st>>>(f->khatT[l], f->F * kKT, f->khatT32);
     e = hipGetLastError();
@@ -986,12 +807,12 @@ hipError_t m2l_spectral_tables(M2LSpectral* f, const std::vector<double*>& tab64
 }
 
 hipError_t m2l_spectral_level(M2LSpectral* f, int l, const void* Ml, int m64, void* Pl, int p64,
-                              int accumulate, const int* offs, int noff, int isolated, hipStream_t st,
+                              int accumulate, int isolated, hipStream_t st,
                               KernelTimer* kt) {
   if (l < 2 || l > f->L) return hipErrorInvalidValue;
-  if (f->p == 4) return run_level<4>(f, l, Ml, m64, Pl, p64, accumulate, offs, noff, isolated, st, kt);
-  if (f->p == 6) return run_level<6>(f, l, Ml, m64, Pl, p64, accumulate, offs, noff, isolated, st, kt);
-  return run_level<8>(f, l, Ml, m64, Pl, p64, accumulate, offs, noff, isolated, st, kt);
+  if (f->p == 4) return run_level<4>(f, l, Ml, m64, Pl, p64, accumulate, isolated, st, kt);
+  if (f->p == 6) return run_level<6>(f, l, Ml, m64, Pl, p64, accumulate, isolated, st, kt);
+  return run_level<8>(f, l, Ml, m64, Pl, p64, accumulate, isolated, st, kt);
 }
 
 }  // namespace pfmm

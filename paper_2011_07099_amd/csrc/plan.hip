@@ -1032,8 +1032,8 @@ pfmm_status solve_impl(pfmm_plan_s* pl, const void* rho_in, void* phi_out, void*
     if (pl->m2l_fft)  // the FFT-convolution comparator, in the level's precision
       return m2l_fft_level(pl->fft, l, ta.X, ta.Y, ta.fp64, ta.accumulate, st);
     if (pl->m2l_spectral)  // spectral stencils, FP64 throughout; each kernel timed
-      return m2l_spectral_level(pl->mspec, l, ta.X, ta.fp64, ta.Y, ta.fp64, ta.accumulate, ta.offs,
-                                ta.noff, ta.isolated, st, tm.on ? &tm : nullptr);
+      return m2l_spectral_level(pl->mspec, l, ta.X, ta.fp64, ta.Y, ta.fp64, ta.accumulate,
+                                ta.isolated, st, tm.on ? &tm : nullptr);
     if (ta.fp64 && ta.q == 8 && ta.C >= 31) {  // FP64 coarse level on the matrix cores
       ToepF64Args fa{};
       fa.n = ta.n;
@@ -1732,8 +1732,8 @@ hipError_t batch_chain_solve(pfmm_batch_s* b, size_t f, hipStream_t st) {
       e = launch_l2l(pl->P[l - 1], level64(pl, l - 1), pl->P[l], level64(pl, l), T, 1 << (l - 1),
                      pl->p, st);
     if (e == hipSuccess)
-      e = m2l_spectral_level(pl->mspec, l, pl->M[l], level64(pl, l), pl->P[l], level64(pl, l), l > 2,
-                             l == 2 ? pl->offs_l2 : pl->offs_iz, l == 2 ? pl->nl2 : 189, 0, st);
+      e = m2l_spectral_level(pl->mspec, l, pl->M[l], level64(pl, l), pl->P[l], level64(pl, l), l > 2, 0,
+                             st);
   }
   if (e == hipSuccess)
     e = launch_l2p(pl->P[pl->L], level64(pl, pl->L), b->phi[f], wts(pl->dA, pl->dA64), pl->N, pl->s,
@@ -1798,7 +1798,7 @@ hipError_t batch_enqueue(pfmm_batch_s* b, int part) {
       }
       for (int l = 2; l <= pl->L && e == hipSuccess && pl->m2l_spectral; ++l)
         e = m2l_spectral_level(pl->mspec, l, pl->M[l], level64(pl, l), pl->P[l], level64(pl, l), 0,
-                               l == 2 ? pl->offs_l2 : pl->offs_iz, l == 2 ? pl->nl2 : 189, 0, st);
+                               0, st);
     }
     if (e == hipSuccess) e = launch_batch_toeplitz(b->items, b->nitems, b->counter, b->grid, st);
     if (e == hipSuccess) e = hipEventRecord(b->ev_split, b->s_split);
