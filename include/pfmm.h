@@ -110,7 +110,7 @@ typedef enum {
    * cores with FP32 accumulation. */
   PFMM_PREC_BF16X3 = 1,
   /* FP64 throughout: every level's gridlets and interaction zones, the mesh
-   * transfers and the near zone (direct summation in FP64, whatever
+   * transfers and the near zone (PFMM_NEAR_DIRECT in FP64, whatever
    * PFMM_OPT_NEAR says).  pfmm_solve then rounds only its FP32 result;
    * pfmm_solve_f64 takes and returns FP64 arrays.  Needs the leaf's FP64
    * transfers to fit in 64 KiB of LDS (p (s + 1) + s^2 (s + 1) + s^2 p + s p^2
@@ -214,8 +214,13 @@ typedef enum {
 
 /* Leaf near-zone algorithm (the 27 neighbour leaves, Sec. 2). */
 typedef enum {
-  /* Direct summation as a block-Toeplitz GEMM over the 27 leaf offsets
-   * (matrix cores or the portable kernel, as PFMM_OPT_PRECISION selects). */
+  /* The sum over the 27 leaf offsets with every cell pair's G.  FP32 and FP64
+   * plans with leaf edges 4, 8 or 16 sum it in FP64, each leaf pair as a cyclic
+   * convolution on the doubled grid (exact up to FP64 rounding; buffers of
+   * about 140 bytes per cell, at most 3 GiB unless two planes of leaves need
+   * more).  Split precision, other leaf edges, batches, and plans without the
+   * memory for those buffers use a block-Toeplitz GEMM (matrix cores or the
+   * portable kernel, as PFMM_OPT_PRECISION selects).  Any alignment. */
   PFMM_NEAR_DIRECT = 0,
   /* FFT convolution on the doubled grid, the route the paper takes (Sec. 2
    * and 3): each leaf's cells zero-padded to (2s)^3 and transformed once
@@ -223,7 +228,7 @@ typedef enum {
    * transformed kernels G(h (m - s e)) (FP64 DFT at plan time, stored FP32)
    * and added per frequency, one inverse transform per leaf.  The cyclic
    * convolution on 2s points equals the linear one at the target cells.
-   * Same sums as the direct route up to rounding; the precision option
+   * Same sums as the direct route up to FP32 rounding; the precision option
    * does not apply to it.  With PFMM_ACCEL_EXPANSION the three acceleration
    * kernels reuse the forward transforms.  For leaf edges s = 4, 8, 16 the
    * transforms are the library's own (one workgroup per leaf, in LDS, reading

@@ -327,6 +327,25 @@ hipError_t near_fft_end(NearFft* f, float* out0, const LeafTree& tree, hipStream
                         KernelTimer* kt = nullptr);
 
 // ---------------------------------------------------------------------------
+// The leaf near zone in FP64 throughout (leaf edges 4, 8, 16): the near zone
+// of FP32 and FP64 plans (near64.hip)
+// ---------------------------------------------------------------------------
+struct Near64;
+// Buffers for N^3 cells in leaves of s^3 (about 140 bytes per cell, at most
+// 3 GiB unless two leaf planes need more); allocates.
+hipError_t near64_create(int N, int s, Near64** out);
+void near64_destroy(Near64* f);
+// Transform the near-zone kernels of `ntabs` (1 .. 4) FP64 tables (as
+// near_fft_tables); allocates the kernels on first use, enqueued on `st`.
+hipError_t near64_tables(Near64* f, const double* const* tabs, int ntabs, double scale, hipStream_t st);
+// out[t] = the near zone of rho with kernel t, t < nout (written, not added);
+// isolated: sources outside the box are absent.  Any alignment.
+hipError_t near64_run(const Near64* f, const float* rho, float* const* out, int nout, int isolated,
+                      hipStream_t st);
+hipError_t near64_run_f64(const Near64* f, const double* rho, double* const* out, int nout, int isolated,
+                          hipStream_t st);
+
+// ---------------------------------------------------------------------------
 // Interaction zones as spectral stencils (per-node transforms, FP64)
 // ---------------------------------------------------------------------------
 struct M2LSpectral;

@@ -71,6 +71,7 @@ struct pfmm_plan_s {
   int fold = 0;                   // P2M and L2P inside its leaf transforms (PFMM_OPT_FOLD)
   int zones_f32 = 0;              // FP32 columns in the 16^3 spectral stencil (PFMM_OPT_ZONES_FP32)
   NearFft* nfft = nullptr;        // its plans, buffers and transformed kernels
+  Near64* n64 = nullptr;          // the direct near zone of FP32 and FP64 plans, by FP64 transforms
   uint16_t* zero = nullptr;       // 512 zero bf16 values: the source outside an isolated box
   // accelerations from the expansion (PFMM_OPT_ACCEL; tables on first use)
   int accel_mode = 0;
@@ -295,6 +296,8 @@ void release(pfmm_plan_s* pl) {
   pl->fft = nullptr;
   if (pl->nfft) near_fft_destroy(pl->nfft);
   pl->nfft = nullptr;
+  if (pl->n64) near64_destroy(pl->n64);
+  pl->n64 = nullptr;
   if (pl->mspec) m2l_spectral_destroy(pl->mspec);
   pl->mspec = nullptr;
   if (pl->gfft) gstar_fft_destroy(pl->gfft);
@@ -358,6 +361,40 @@ pfmm_status refresh_near_fft(pfmm_plan_s* pl) {
   return PFMM_OK;
 }
 
+// The FP64 near zone of a plan whose options ask for it (direct, not split
+// precision; FP64 precision whatever PFMM_OPT_NEAR says) at the leaf edges it
+// serves: made or released, its kernels transformed.  Without the memory for
+// it the plan keeps the block-Toeplitz sum.
+pfmm_status refresh_near64(pfmm_plan_s* pl) {
+  const bool want = pl->prec == PFMM_PREC_FP64 || (pl->prec == PFMM_PREC_FP32 && !pl->near_fft);
+  if (!want || (pl->s != 4 && pl->s != 8 && pl->s != 16)) {
+    if (!pl->n64) return PFMM_OK;
+    hipError_t e = hipStreamSynchronize(pl->stream);
+    if (e == hipSuccess && pl->side) e = hipStreamSynchronize(pl->side);
+    near64_destroy(pl->n64);
+    pl->n64 = nullptr;
+    return e == hipSuccess ? PFMM_OK : hip_fail(e, "FP64 near zone");
+  }
+  const double* tabs[4] = {pl->ntab64, pl->ndtab64[0], pl->ndtab64[1], pl->ndtab64[2]};
+  const double h3 = 1.0 / ((double)pl->N * pl->N * pl->N);
+  hipError_t e = pl->n64 ? hipSuccess : near64_create(pl->N, pl->s, &pl->n64);
+  if (e == hipSuccess) e = near64_tables(pl->n64, tabs, pl->accel_mode ? 4 : 1, h3, pl->stream);
+  if (e == hipSuccess) e = hipStreamSynchronize(pl->stream);
+  if (e == hipErrorOutOfMemory) {
+    (void)hipGetLastError();
+    if (pl->n64) near64_destroy(pl->n64);
+    pl->n64 = nullptr;
+    return PFMM_OK;
+  }
+  return e == hipSuccess ? PFMM_OK : hip_fail(e, "FP64 near zone");
+}
+
+// Every transformed near-zone kernel follows the tables.
+pfmm_status refresh_near(pfmm_plan_s* pl) {
+  const pfmm_status r = refresh_near_fft(pl);
+  return r == PFMM_OK ? refresh_near64(pl) : r;
+}
+
 // Near-zone acceleration kernels of the plan's G (allocated on first use)
 pfmm_status tabulate_accel_tables(pfmm_plan_s* pl) {
   const int Cn = 2 * pl->s - 1;
@@ -378,7 +415,7 @@ pfmm_status tabulate_accel_tables(pfmm_plan_s* pl) {
   }
   if (e == hipSuccess) e = hipStreamSynchronize(pl->stream);
   if (e != hipSuccess) return hip_fail(e, "acceleration tables");
-  return refresh_near_fft(pl);
+  return refresh_near(pl);
 }
 
 hipError_t gstar_base(pfmm_plan_s* pl);
@@ -418,7 +455,7 @@ pfmm_status tabulate_all(pfmm_plan_s* pl) {
     e = m2l_spectral_tables(pl->mspec, pl->tab64, pl->stream);
     if (e != hipSuccess) return hip_fail(e, "spectral zone kernels");
   }
-  pfmm_status s0 = pl->accel_mode ? tabulate_accel_tables(pl) : refresh_near_fft(pl);
+  pfmm_status s0 = pl->accel_mode ? tabulate_accel_tables(pl) : refresh_near(pl);
   if (s0 != PFMM_OK || !pl->gdelta) return s0;
   // G_* follows the new G: new uncorrected copies, the correction applied again
   e = gstar_base(pl);
@@ -766,8 +803,9 @@ pfmm_status pfmm_plan_set(pfmm_plan_t h, int option, const void* value, size_t b
           return fail(PFMM_ERR_UNSUPPORTED, "PFMM_PREC_FP64: the leaf's FP64 mesh transfers do not fit "
                                             "in 64 KiB of LDS at this leaf width and p");
       }
+      if (pl->prec == v) return PFMM_OK;
       pl->prec = v;
-      return PFMM_OK;
+      return refresh_near64(pl);
     }
     case PFMM_OPT_ZONES_FP32: {
       if (bytes != sizeof(int32_t)) return fail(PFMM_ERR_INVALID_ARG, "zones_fp32 is an int32");
@@ -918,8 +956,9 @@ pfmm_status pfmm_plan_set(pfmm_plan_t h, int option, const void* value, size_t b
           return r;
         }
       }
+      if (pl->near_fft == v) return PFMM_OK;
       pl->near_fft = v;
-      return PFMM_OK;
+      return refresh_near64(pl);
     }
     case PFMM_OPT_FP64_LEVELS: {
       if (bytes != sizeof(int32_t)) return fail(PFMM_ERR_INVALID_ARG, "fp64 levels is an int32");
@@ -1149,6 +1188,22 @@ pfmm_status solve_impl(pfmm_plan_s* pl, const void* rho_in, void* phi_out, void*
         ma.Y = accel + (size_t)c * N * N * N;
         e = launch_toep8_split(ma, kNearTerms, sn);
       }
+    }
+    if (e == hipSuccess) e = tm.end(sn, 0);
+  } else if (pl->n64) {
+    void* outs[4] = {phi_out, nullptr, nullptr, nullptr};
+    int nout = 1;
+    if (accel && pl->accel_mode)
+      for (int c = 0; c < 3; ++c) outs[nout++] = acc_c(c);
+    e = tm.begin(sn);
+    if (e == hipSuccess && io64) {
+      double* o[4];
+      for (int t = 0; t < nout; ++t) o[t] = static_cast<double*>(outs[t]);
+      e = near64_run_f64(pl->n64, static_cast<const double*>(rho_in), o, nout, pl->isolated, sn);
+    } else if (e == hipSuccess) {
+      float* o[4];
+      for (int t = 0; t < nout; ++t) o[t] = static_cast<float*>(outs[t]);
+      e = near64_run(pl->n64, rho, o, nout, pl->isolated, sn);
     }
     if (e == hipSuccess) e = tm.end(sn, 0);
   } else {
@@ -2547,7 +2602,7 @@ pfmm_status gstar_apply(pfmm_plan_s* pl) {
   if (e == hipSuccess && pl->mspec) e = m2l_spectral_tables(pl->mspec, pl->tab64, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   if (e != hipSuccess) return hip_fail(e, "apply G_*");
-  return refresh_near_fft(pl);
+  return refresh_near(pl);
 }
 
 // Forward solve with G_*, its PM potential, and the residual statistics.
