@@ -533,9 +533,10 @@ def kernel_work(name, N, L, p, route=None):
     (operands read once, results written once); spectra are complex FP64 at
     the interaction zones ((2p)^2 (p + 1) frequencies per node), complex FP32
     at the near zone ((2s)^2 (s + 1) per leaf).  GEMM zones and the direct
-    near zone in split precision: 2 p^6 flops per offset and target node, 2 s^6
-    per neighbour leaf and target leaf, on the unit the precision puts them on
-    (in FP32 the direct near zone sums per frequency in FP64); `products`
+    near zone of other leaf edges than 4, 8, 16: 2 p^6 flops per offset and
+    target node, 2 s^6 per neighbour leaf and target leaf, on the unit the
+    precision puts them on (at s = 4, 8, 16 the direct near zone sums per
+    frequency in FP64); `products`
     is the number of bf16 products the split issues per algorithmic product
     (the matrix cores' peak applies to issued flops)."""
     s = N >> L
@@ -550,8 +551,6 @@ def kernel_work(name, N, L, p, route=None):
         return fl, "f32 valu", None, 1
     if name == "near" and route["near"] == "direct":
         fl = 27 * 2.0 * s ** 6 * 8 ** L
-        if route["precision"] == "bf16x3" and s in (8, 16):
-            return fl, "bf16 mfma", None, 3
         if s in (4, 8, 16):  # FP64 transforms: density in, spectra out and in twice, potential out
             F, leaves = (2 * s) ** 2 * (s + 1), 8 ** L
             return 27 * 8.0 * F * leaves, "f64 valu", 8.0 * N ** 3 + 4 * 16.0 * F * leaves, 1

@@ -214,13 +214,13 @@ typedef enum {
 
 /* Leaf near-zone algorithm (the 27 neighbour leaves, Sec. 2). */
 typedef enum {
-  /* The sum over the 27 leaf offsets with every cell pair's G.  FP32 and FP64
-   * plans with leaf edges 4, 8 or 16 sum it in FP64, each leaf pair as a cyclic
-   * convolution on the doubled grid (exact up to FP64 rounding; buffers of
-   * about 140 bytes per cell, at most 3 GiB unless two planes of leaves need
-   * more).  Split precision, other leaf edges, batches, and plans without the
-   * memory for those buffers use a block-Toeplitz GEMM (matrix cores or the
-   * portable kernel, as PFMM_OPT_PRECISION selects).  Any alignment. */
+  /* The sum over the 27 leaf offsets with every cell pair's G.  Plans with
+   * leaf edges 4, 8 or 16 sum it in FP64 in every precision, each leaf pair as
+   * a cyclic convolution on the doubled grid (exact up to FP64 rounding;
+   * buffers of about 140 bytes per cell, at most 3 GiB unless two planes of
+   * leaves need more).  Other leaf edges, batches, and plans without the memory
+   * for those buffers use a block-Toeplitz GEMM (matrix cores or the portable
+   * kernel, as PFMM_OPT_PRECISION selects).  Any alignment. */
   PFMM_NEAR_DIRECT = 0,
   /* FFT convolution on the doubled grid, the route the paper takes (Sec. 2
    * and 3): each leaf's cells zero-padded to (2s)^3 and transformed once

@@ -327,8 +327,7 @@ hipError_t near_fft_end(NearFft* f, float* out0, const LeafTree& tree, hipStream
                         KernelTimer* kt = nullptr);
 
 // ---------------------------------------------------------------------------
-// The leaf near zone in FP64 throughout (leaf edges 4, 8, 16): the near zone
-// of FP32 and FP64 plans (near64.hip)
+// The direct leaf near zone in FP64 throughout (leaf edges 4, 8, 16; near64.hip)
 // ---------------------------------------------------------------------------
 struct Near64;
 // Buffers for N^3 cells in leaves of s^3 (about 140 bytes per cell, at most

@@ -1,4 +1,4 @@
-// The leaf near zone of FP32 and FP64 plans (the 27 neighbour leaves, Sec. 2),
+// The direct leaf near zone of single solves (the 27 neighbour leaves, Sec. 2),
 // every sum in FP64, for leaf edges s = 4, 8, 16.
 //
 // Target leaf b, source leaf b + e, e in {-1, 0, 1}^3, cells c and c':
@@ -11,7 +11,8 @@
 // sum, whose FP32 products cost 54 s^6 flops per leaf at 0.5 of the FP32 rate,
 // takes (128^3, s = 16) 7.0 ms per kernel and 0.78 ms at 64^3, s = 8; this takes
 // 0.19 and 0.045 ms (0.66 ms for the four kernels of the expansion accelerations
-// against 28), and 1.44 ms against 45 at 256^3.  Its error against 64 bits is that of
+// against 28), and 1.44 ms at 256^3 against 45 in FP32 and 8 in split bf16 on the
+// matrix cores.  Its error against 64 bits is that of
 // rounding the result (4.5e-8 of the norm at 128^3; the FP32 sums 9.8e-7).  The
 // transforms and sums are bound by HBM (144 B per cell of spectra, written and read
 // twice) and, below 64 leaves an axis plane, by latency.
