@@ -500,9 +500,11 @@ pfmm_status pfmm_solve_batch(int n, const pfmm_plan_t* plans, const float* const
 /*
  * Direct periodic convolution  potential_i = h^3 sum_j G((x_i - x_j) wrapped) rho_j
  * over the whole box with the plan's G (Eq. 4, "PM with G": the exact result
- * the FMM approximates), by the block-Toeplitz kernel in FP32 with FP64
- * per-offset totals.  O(N^6) work: a reference for moderate N.  Allocates
- * its table on the first call; enqueued on the plan's stream.
+ * the FMM approximates), by FP64 transforms of the mesh: exact up to FP64
+ * rounding, rounded once to FP32.  Allocates its table and about 16 bytes per
+ * cell of spectra on the first call; enqueued on the plan's stream.  Calls on
+ * one plan share the spectrum: a call after a change of PFMM_OPT_STREAM waits
+ * for the last one; a captured call must not overlap with another.
  */
 pfmm_status pfmm_plan_direct(pfmm_plan_t plan, const float* density, float* potential);
 
@@ -512,7 +514,7 @@ pfmm_status pfmm_plan_direct(pfmm_plan_t plan, const float* density, float* pote
  * hipMalloc).  Same arguments and result as pfmm_plan_direct, bit for bit,
  * without its first-call allocation: the lattice table of G is tabulated on
  * every call into a static device array of the library (8 MiB, one per
- * device, held until the process ends), which limits it to N <= 64
+ * device, held until the process ends), with the spectra, which limits it to N <= 64
  * (PFMM_ERR_UNSUPPORTED above; isolated plans too).  Allocates and
  * synchronises nothing; enqueued on the plan's stream.  Every call on a
  * device shares that device's array: calls that overlap on one device (two

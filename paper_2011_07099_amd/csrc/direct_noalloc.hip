@@ -5,8 +5,9 @@
 // every call into a file-scope device array instead, and allocates nothing.
 //
 // The array holds, one after another (256-byte aligned): the FP64 lattice
-// table G(h j), j in [-C, C]^3; its FP32 copy; the n^3 packed block offsets;
-// and the partial Fourier sums of G_K / G_E.  Each device holds its own copy
+// table G(h j), |j_i| <= N / 2; the transform of G; the density's spectrum
+// (before it the separations' values of G); and the partial Fourier sums of
+// G_K / G_E.  Each device holds its own copy
 // of the array, at its own address, looked up once per device with
 // hipGetSymbolAddress; host code uses only that address.  Every call on a
 // device overwrites the whole table before it is read (stream order), so
@@ -51,15 +52,6 @@ hipError_t scratch_address(void** out) {
 
 inline size_t up256(size_t b) { return (b + 255) / 256 * 256; }
 
-// The source blocks of the whole box, d in [-n/2, n/2)^3, packed as the
-// block-Toeplitz kernel reads them (pack_offset's byte layout), x slowest.
-__global__ void k_direct_offsets(int n, int* __restrict__ offs) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n * n * n) return;
-  const int dx = i / (n * n) - n / 2, dy = (i / n) % n - n / 2, dz = i % n - n / 2;
-  offs[i] = ((dx + 128) & 255) << 16 | ((dy + 128) & 255) << 8 | ((dz + 128) & 255);
-}
-
 }  // namespace
 
 extern "C" pfmm_status pfmm_plan_direct_noalloc(pfmm_plan_t plan, const float* density,
@@ -77,14 +69,12 @@ extern "C" pfmm_status pfmm_plan_direct_noalloc(pfmm_plan_t plan, const float* d
     return (pfmm_status)set_error(PFMM_ERR_UNSUPPORTED,
                                   "pfmm_plan_direct_noalloc serves N <= 64 (its 8 MiB device array)");
   const int N = sp.N;
-  const int q = N >= 16 ? 8 : N / 2, n = N / q;
-  const int C = N / 2 + q - 1;
+  const int C = N / 2;
   const int64_t E3 = (int64_t)(2 * C + 1) * (2 * C + 1) * (2 * C + 1);
   const size_t b64 = up256((size_t)E3 * sizeof(double));
-  const size_t b32 = up256((size_t)E3 * sizeof(float));
-  const size_t boffs = up256((size_t)n * n * n * sizeof(int));
+  const size_t bspec = up256(pm_values(N) * sizeof(double2));
   const size_t bws = tabulate_workspace_doubles(sp.green.kind, N, C) * sizeof(double);
-  if (b64 + b32 + boffs + bws > kScratchBytes)
+  if (b64 + 2 * bspec + bws > kScratchBytes)
     return (pfmm_status)set_error(PFMM_ERR_UNSUPPORTED, "table larger than the device array");
   void* base = nullptr;
   hipError_t e = scratch_address(&base);
@@ -92,34 +82,13 @@ extern "C" pfmm_status pfmm_plan_direct_noalloc(pfmm_plan_t plan, const float* d
     return (pfmm_status)set_error(PFMM_ERR_HIP, std::string("scratch address: ") + hipGetErrorString(e));
   unsigned char* b = static_cast<unsigned char*>(base);
   double* tab64 = reinterpret_cast<double*>(b);
-  float* tab32 = reinterpret_cast<float*>(b + b64);
-  int* offs = reinterpret_cast<int*>(b + b64 + b32);
-  double* ws = bws ? reinterpret_cast<double*>(b + b64 + b32 + boffs) : nullptr;
+  double2* ghat = reinterpret_cast<double2*>(b + b64);
+  double2* work = reinterpret_cast<double2*>(b + b64 + bspec);
+  double* ws = bws ? reinterpret_cast<double*>(b + b64 + 2 * bspec) : nullptr;
   hipStream_t st = sp.stream;
   e = tabulate_green_ws(sp.green, N, C, N, 1.0 / N, tab64, ws, st);
-  if (e == hipSuccess) e = cast_f64_f32(tab64, tab32, E3, st);
-  if (e == hipSuccess) {
-    hipLaunchKernelGGL(k_direct_offsets, dim3((n * n * n + 255) / 256), dim3(256), 0, st, n, offs);
-    e = hipGetLastError();
-  }
-  if (e == hipSuccess) {
-    ToepArgs a{};
-    a.n = n;
-    a.m = 1;
-    a.q = q;
-    a.noff = n * n * n;
-    a.offs = offs;
-    a.tab = tab32;
-    a.C = C;
-    a.X = density;
-    a.Y = potential;
-    a.grid_in = 1;
-    a.grid_out = 1;
-    a.xscale = 1.0 / ((double)N * N * N);
-    a.accumulate = 0;
-    a.groups = 1;
-    e = launch_toeplitz(a, st);
-  }
+  if (e == hipSuccess) e = pm_kernel(tab64, C, N, work, ghat, st);
+  if (e == hipSuccess) e = pm_convolve(density, ghat, work, N, potential, st);
   if (e != hipSuccess)
     return (pfmm_status)set_error(PFMM_ERR_HIP, std::string("direct solve: ") + hipGetErrorString(e));
   return PFMM_OK;

@@ -182,12 +182,25 @@ hipError_t launch_batch_toeplitz(const BatchItem* items, int nitems, unsigned* c
                                  hipStream_t st);
 
 // ---------------------------------------------------------------------------
+// The exact periodic convolution with G by FP64 transforms (pmfft.hip)
+// ---------------------------------------------------------------------------
+// Values of a half spectrum of N^3 (N a power of two, 8 .. 1024).
+size_t pm_values(int N);
+// ghat = the transform of h^3 G at every mesh separation, from a centred FP64
+// table of extent C >= N / 2; `work` and `ghat` hold pm_values(N) values.
+hipError_t pm_kernel(const double* tab, int C, int N, double2* work, double2* ghat, hipStream_t st);
+// phi = rho convolved with it (any alignment); `work` is overwritten.
+hipError_t pm_convolve(const float* rho, const double2* ghat, double2* work, int N, float* phi,
+                       hipStream_t st);
+
+// ---------------------------------------------------------------------------
 // Learned correction of the interaction-zone tables (learned.hip)
 // ---------------------------------------------------------------------------
 constexpr int kMlpIn = 8;          // network inputs per table entry
 constexpr int kMlpParams = 4801;  // 8 -> 64 -> 64 -> 1
 hipError_t mlp_forward(const float* theta, const float* feats, int n, int bf16, float* delta,
                        hipStream_t st);
+// T = G0 (1 + delta[uidx]) in FP64 and, unless t32 is null, FP32
 hipError_t apply_correction(const double* g0, const float* delta, const int* uidx, int64_t n,
                             double* t64, float* t32, hipStream_t st);
 hipError_t residual(const float* phi, const float* t, int64_t n, double* part, double* stats,

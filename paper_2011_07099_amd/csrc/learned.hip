@@ -70,7 +70,7 @@ __global__ void k_mlp_forward(const float* __restrict__ theta, const float* __re
   delta[e] = kKappa * out;
 }
 
-// T[j] = G0[j] (1 + delta[uidx[j]]) in FP64 and FP32
+// T[j] = G0[j] (1 + delta[uidx[j]]) in FP64 and, unless t32 is null, FP32
 __global__ void k_apply_correction(const double* __restrict__ g0, const float* __restrict__ delta,
                                    const int* __restrict__ uidx, int64_t n,
                                    double* __restrict__ t64, float* __restrict__ t32) {
@@ -78,7 +78,7 @@ __global__ void k_apply_correction(const double* __restrict__ g0, const float* _
   if (i >= n) return;
   const double v = g0[i] * (1.0 + (double)delta[uidx[i]]);
   t64[i] = v;
-  t32[i] = (float)v;
+  if (t32) t32[i] = (float)v;
 }
 
 // Partial sums over the mesh of d = phi - t, d^2, t, t^2 (FP64), one block each.

@@ -137,10 +137,12 @@ struct pfmm_plan_s {
   GStarFft* gfft = nullptr;
   int gacc_n = 0;                 // fields accumulated
   // direct periodic convolution over the whole box (allocated on first use)
-  double* dtab64 = nullptr;
-  float* dtab32 = nullptr;
-  int* doffs = nullptr;
-  int dq = 0, dC = 0, dnoff = 0;
+  double* dtab64 = nullptr;       // G at the mesh separations, |j_i| <= dC = N / 2
+  int dC = 0;
+  double2* dghat = nullptr;       // its transform
+  double2* dwork = nullptr;       // the density's spectrum: calls on other streams wait
+  hipStream_t dstream = nullptr;  // for ev_direct of the last one
+  hipEvent_t ev_direct = nullptr;
   std::vector<void*> owned;
   // stage timing (PFMM_OPT_PROFILE): a ring of event sets, one per solve;
   // each timed launch (or group of launches) has a start and an end event
@@ -309,6 +311,7 @@ void release(pfmm_plan_s* pl) {
     (void)hipStreamSynchronize(pl->side);
     (void)hipStreamDestroy(pl->side);
   }
+  if (pl->ev_direct) (void)hipEventDestroy(pl->ev_direct);
   if (pl->ev_fork) (void)hipEventDestroy(pl->ev_fork);
   if (pl->ev_join) (void)hipEventDestroy(pl->ev_join);
   if (pl->ev_mass) (void)hipEventDestroy(pl->ev_mass);
@@ -444,7 +447,7 @@ pfmm_status tabulate_all(pfmm_plan_s* pl) {
   if (e != hipSuccess) return hip_fail(e, "tabulate near table");
   if (pl->dtab64) {  // the direct solve's table, once it exists, follows G too
     e = tabulate_green(green_spec(pl), pl->N, pl->dC, pl->N, 1.0 / pl->N, pl->dtab64, pl->stream);
-    if (e == hipSuccess) e = cast_f64_f32(pl->dtab64, pl->dtab32, cube(2 * pl->dC + 1), pl->stream);
+    if (e == hipSuccess) e = pm_kernel(pl->dtab64, pl->dC, pl->N, pl->dwork, pl->dghat, pl->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(pl->stream);
     if (e != hipSuccess) return hip_fail(e, "direct solve tables");
   }
@@ -2406,51 +2409,37 @@ hipError_t adjoint_tables(pfmm_plan_s* pl, const float* target) {
 
 pfmm_status direct_prepare(pfmm_plan_s* pl) {
   if (pl->dtab64) return PFMM_OK;
-  const int N = pl->N;
-  const int q = N >= 16 ? 8 : N / 2, n = N / q;
-  const int C = N / 2 + q - 1;
-  std::vector<int> offs;
-  for (int dx = -n / 2; dx < n / 2; ++dx)
-    for (int dy = -n / 2; dy < n / 2; ++dy)
-      for (int dz = -n / 2; dz < n / 2; ++dz) offs.push_back(pack_offset(dx, dy, dz));
-  const int64_t ntab = cube(2 * C + 1);
-  hipError_t e = dalloc(pl, &pl->dtab64, (size_t)ntab);
-  if (e == hipSuccess) e = dalloc(pl, &pl->dtab32, (size_t)ntab);
-  if (e == hipSuccess) e = dalloc(pl, &pl->doffs, offs.size());
-  if (e == hipSuccess)
-    e = hipMemcpy(pl->doffs, offs.data(), offs.size() * 4, hipMemcpyHostToDevice);
+  const int N = pl->N, C = N / 2;
+  const size_t nf = pm_values(N);
+  double2* spec = nullptr;
+  hipError_t e = pl->ev_direct ? hipSuccess : hipEventCreateWithFlags(&pl->ev_direct, hipEventDisableTiming);
+  if (e == hipSuccess) e = dalloc(pl, &pl->dtab64, (size_t)cube(2 * C + 1));
+  if (e == hipSuccess) e = dalloc(pl, &spec, 2 * nf);
   if (e == hipSuccess)
     e = tabulate_green(green_spec(pl), N, C, N, 1.0 / N, pl->dtab64, pl->stream);
-  if (e == hipSuccess) e = cast_f64_f32(pl->dtab64, pl->dtab32, ntab, pl->stream);
+  if (e == hipSuccess) e = pm_kernel(pl->dtab64, C, N, spec, spec + nf, pl->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(pl->stream);
   if (e != hipSuccess) {
     pl->dtab64 = nullptr;
     return hip_fail(e, "direct solve tables");
   }
-  pl->dq = q;
   pl->dC = C;
-  pl->dnoff = (int)offs.size();
+  pl->dwork = spec;
+  pl->dghat = spec + nf;
   return PFMM_OK;
 }
 
 // The exact periodic convolution with the plan's direct table (prepared).
+// Calls on one plan share its spectrum: a call on another stream than the last
+// one waits for it (a captured call does not: its order is the caller's).
 hipError_t direct_launch(pfmm_plan_s* pl, const float* rho, float* phi) {
-  ToepArgs a{};
-  a.n = pl->N / pl->dq;
-  a.m = 1;
-  a.q = pl->dq;
-  a.noff = pl->dnoff;
-  a.offs = pl->doffs;
-  a.tab = pl->dtab32;
-  a.C = pl->dC;
-  a.X = rho;
-  a.Y = phi;
-  a.grid_in = 1;
-  a.grid_out = 1;
-  a.xscale = 1.0 / ((double)pl->N * pl->N * pl->N);
-  a.accumulate = 0;
-  a.groups = 1;
-  return launch_toeplitz(a, pl->stream);
+  const bool cap = capturing(pl->stream);
+  hipError_t e = hipSuccess;
+  if (!cap && pl->dstream != pl->stream) e = hipStreamWaitEvent(pl->stream, pl->ev_direct, 0);
+  if (e == hipSuccess) e = pm_convolve(rho, pl->dghat, pl->dwork, pl->N, phi, pl->stream);
+  if (e == hipSuccess && !cap) e = hipEventRecord(pl->ev_direct, pl->stream);
+  if (!cap) pl->dstream = pl->stream;
+  return e;
 }
 
 // --- G_* on the whole mesh -------------------------------------------------
@@ -2599,7 +2588,8 @@ pfmm_status gstar_apply(pfmm_plan_s* pl) {
   if (e == hipSuccess && pl->nwin)
     e = make_windows(pl->ntab64, 2 * pl->s - 1, kNearTerms, pl->nwin, st);
   if (e == hipSuccess)
-    e = apply_correction(pl->gd0, pl->gdelta, pl->gduidx, ndir, pl->dtab64, pl->dtab32, st);
+    e = apply_correction(pl->gd0, pl->gdelta, pl->gduidx, ndir, pl->dtab64, nullptr, st);
+  if (e == hipSuccess) e = pm_kernel(pl->dtab64, pl->dC, pl->N, pl->dwork, pl->dghat, st);
   if (e == hipSuccess && pl->mspec) e = m2l_spectral_tables(pl->mspec, pl->tab64, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   if (e != hipSuccess) return hip_fail(e, "apply G_*");

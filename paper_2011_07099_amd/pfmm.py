@@ -280,7 +280,7 @@ class Plan:
                                     w.nbytes))
 
     def direct(self, rho, phi):
-        """Exact periodic convolution with the plan's G on the device (O(N^6))."""
+        """Exact periodic convolution with the plan's G on the device (FP64 transforms)."""
         _check(load().pfmm_plan_direct(self._h, _ptr(rho), _ptr(phi)))
 
     def direct_noalloc(self, rho, phi):
