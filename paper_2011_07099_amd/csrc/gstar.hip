@@ -15,8 +15,8 @@
 // (B = sum (phi_PM - mean)^2, which also moves with G_*),
 //   d loss / d G_*(x) = [FMM adjoint at x] - h^3 sum_t q_t rho(t - x).
 // The FMM adjoint of the level tables is the learned tables' (adjoint sweep
-// and table gradient); this file adds the near-zone table's, a direct sum
-// over the pairs of neighbouring leaves, and the PM side, a periodic
+// and table gradient), that of the near-zone table the same gradient over the
+// pairs of neighbouring leaves; this file adds the PM side, a periodic
 // cross-correlation by FP64 FFT.
 #include "internal.h"
 
@@ -30,38 +30,6 @@ namespace {
 inline unsigned nb(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
 
 hipError_t ferr(hipfftResult r) { return r == HIPFFT_SUCCESS ? hipSuccess : hipErrorUnknown; }
-
-// floor(a / s) for a > -4s
-__device__ __forceinline__ int fdiv(int a, int s) { return (a + 4 * s) / s - 4; }
-
-// Near-zone table gradient: g[m] = h^3 sum over target cells t whose source
-// cell t - m lies in one of the 27 leaves around t's leaf of r[t] rho[t - m],
-// for every separation m of the table (|m_i| <= C = 2s - 1), one block each.
-__global__ __launch_bounds__(256) void k_near_grad(const float* __restrict__ r,
-                                                   const float* __restrict__ rho, int N, int s,
-                                                   int C, double h3, double* __restrict__ g) {
-  const int E = 2 * C + 1;
-  const int id = blockIdx.x;
-  const int mx = id / (E * E) - C, my = (id / E) % E - C, mz = id % E - C;
-  const int64_t n3 = (int64_t)N * N * N;
-  double acc = 0.0;
-  for (int64_t t = threadIdx.x; t < n3; t += blockDim.x) {
-    const int tx = (int)(t / ((int64_t)N * N)), ty = (int)((t / N) % N), tz = (int)(t % N);
-    const int ux = tx - mx, uy = ty - my, uz = tz - mz;
-    const int ex = tx / s - fdiv(ux, s), ey = ty / s - fdiv(uy, s), ez = tz / s - fdiv(uz, s);
-    if (ex < -1 || ex > 1 || ey < -1 || ey > 1 || ez < -1 || ez > 1) continue;
-    const int sx = (ux + N) % N, sy = (uy + N) % N, sz = (uz + N) % N;
-    acc += (double)r[t] * (double)rho[((int64_t)sx * N + sy) * N + sz];
-  }
-  __shared__ double red[256];
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int k = 128; k > 0; k >>= 1) {
-    if ((int)threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) g[id] = h3 * red[0];
-}
 
 // q = r + 2 (loss / B) (t - mean t) and the density, both in FP64;
 // stats = {mean(phi - t), loss, B, mean t}
@@ -159,13 +127,6 @@ hipError_t gstar_fft_create(int N, GStarFft** out) {
   }
   *out = f;
   return hipSuccess;
-}
-
-hipError_t gstar_near_grad(const float* r, const float* rho, int N, int s, double h3, double* g,
-                           hipStream_t st) {
-  const int C = 2 * s - 1, E = 2 * C + 1;
-  hipLaunchKernelGGL(k_near_grad, dim3(E * E * E), dim3(256), 0, st, r, rho, N, s, C, h3, g);
-  return hipGetLastError();
 }
 
 hipError_t gstar_pm_corr(GStarFft* f, const float* r, const float* t, const float* rho,

@@ -205,9 +205,13 @@ hipError_t apply_correction(const double* g0, const float* delta, const int* uid
                             double* t64, float* t32, hipStream_t st);
 hipError_t residual(const float* phi, const float* t, int64_t n, double* part, double* stats,
                     float* r, hipStream_t st);
-size_t table_grad_partial_doubles(int m, int q, int noff);
+size_t table_grad_partial_doubles(int n, int m, int q, int noff);
 hipError_t table_grad(int n, int m, int q, int noff, const int* offs, const void* lam,
                       const void* M, int fp64, int C, double* part, double* g, hipStream_t st);
+// The same over blocks of q^3 cells of two meshes [n q]^3, times `scale` (the
+// near zone's table).
+hipError_t mesh_table_grad(int n, int m, int q, int noff, const int* offs, const float* lam, const float* M,
+                           int C, double scale, double* part, double* g, hipStream_t st);
 hipError_t orbit_gather(const double* g, const double* g0, const int* ptr, const int* pos, int nu,
                         float* ddelta, hipStream_t st);
 size_t mlp_backward_partial_floats(int n);
@@ -226,9 +230,6 @@ int gstar_orbits(int N);                      // number of orbits
 struct GStarFft;
 hipError_t gstar_fft_create(int N, GStarFft** out);
 void gstar_fft_destroy(GStarFft* f);
-// near-zone table gradient (FP64 per entry of the (4s-1)^3 table)
-hipError_t gstar_near_grad(const float* r, const float* rho, int N, int s, double h3, double* g,
-                           hipStream_t st);
 // N^3 sum_t q_t rho(t - x) with q = r + 2 (loss / B)(t - mean t), stats as residual()'s
 hipError_t gstar_pm_corr(GStarFft* f, const float* r, const float* t, const float* rho,
                          const double* stats, double* corr, hipStream_t st);

@@ -132,6 +132,7 @@ struct pfmm_plan_s {
   double* gmesh0 = nullptr;       // -G(x) / N^6 at every mesh point (PM-side gather weights)
   int *gmptr = nullptr, *gmpos = nullptr;
   double* gnear = nullptr;        // near-table gradient of one field
+  double* gnpart = nullptr;       // its partial sums
   double* gcorr = nullptr;        // PM-side correlation (N^3)
   float* gtarget = nullptr;       // PM potential with G_*
   GStarFft* gfft = nullptr;
@@ -2354,7 +2355,7 @@ pfmm_status adjoint_alloc(pfmm_plan_s* pl) {
     e = dalloc(pl, &b, ((size_t)1 << (3 * l)) * p3 * sizeof(double));
     pl->lam[l] = b;
     if (e == hipSuccess) e = dalloc(pl, &pl->tgrad[l], (size_t)ntab);
-    tg = std::max(tg, table_grad_partial_doubles(l == 2 ? 1 : 2, p, l == 2 ? 37 : 189));
+    tg = std::max(tg, table_grad_partial_doubles(1 << l, l == 2 ? 1 : 2, p, l == 2 ? 37 : 189));
   }
   if (e == hipSuccess) e = dalloc(pl, &pl->tgpart, tg);
   if (e != hipSuccess) {
@@ -2533,6 +2534,9 @@ pfmm_status gstar_prepare(pfmm_plan_s* pl) {
     if (e == hipSuccess) e = upload(pl, &pl->gnpos, pos);
     if (e == hipSuccess) e = dalloc(pl, &pl->gn0, u.size());
     if (e == hipSuccess) e = dalloc(pl, &pl->gnear, u.size());
+    if (e == hipSuccess)
+      e = dalloc(pl, &pl->gnpart,
+                 table_grad_partial_doubles(N / pl->qn, pl->mn, pl->qn, (int)cube(3 * pl->mn)));
   }
   // direct table (periodic images of the same separations share an orbit)
   if (e == hipSuccess) {
@@ -2976,7 +2980,9 @@ pfmm_status pfmm_gstar_accumulate(pfmm_plan_t h, const float* rho, double* loss)
   for (int l = 2; l <= pl->L && e == hipSuccess; ++l)
     e = orbit_gather(pl->tgrad[l], pl->gl0[l], pl->glptr[l], pl->glpos[l], nu, pl->gdd, st);
   const double h3 = 1.0 / ((double)N * N * N);
-  if (e == hipSuccess) e = gstar_near_grad(pl->resid, rho, N, pl->s, h3, pl->gnear, st);
+  if (e == hipSuccess)
+    e = mesh_table_grad(N / pl->qn, pl->mn, pl->qn, (int)cube(3 * pl->mn), pl->offs_near, pl->resid, rho,
+                        2 * pl->s - 1, h3, pl->gnpart, pl->gnear, st);
   if (e == hipSuccess) e = orbit_gather(pl->gnear, pl->gn0, pl->gnptr, pl->gnpos, nu, pl->gdd, st);
   // the PM side (its weights carry -1 / N^6: h^3 and the unnormalised FFT)
   if (e == hipSuccess)
