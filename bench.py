@@ -16,9 +16,9 @@ Prints one JSON line:
     timed run of the same number of steps with every stage alone on the
     device ("serial"); the roofline of the dominant single kernel uses its
     serial duration, with its live one beside it;
-  - m2l_mfma: the interaction zones as block-Toeplitz GEMMs on the matrix
-    cores, timed in the same run on the same density, per level against the
-    peak of the matrix-core instruction it uses;
+  - m2l_mfma: the default (GEMM) interaction zones in split precision, on the
+    matrix cores, timed in the same run on the same density, per level
+    against the peak of the matrix-core instruction it uses;
   - the CPU FP64 oracle timed on a bounded sample of the same workload (which
     also checks the GPU potential: sampled cells against the reference FMM,
     the full mesh against PM with the same G).
@@ -532,11 +532,11 @@ def kernel_work(name, N, L, p, route=None):
     per complex multiply-add; bytes are the kernel's compulsory HBM traffic
     (operands read once, results written once); spectra are complex FP64 at
     the interaction zones ((2p)^2 (p + 1) frequencies per node), complex FP32
-    at the near zone ((2s)^2 (s + 1) per leaf).  GEMM zones and the direct
-    near zone of other leaf edges than 4, 8, 16: 2 p^6 flops per offset and
-    target node, 2 s^6 per neighbour leaf and target leaf, on the unit the
-    precision puts them on (at s = 4, 8, 16 the direct near zone sums per
-    frequency in FP64); `products`
+    at the near zone ((2s)^2 (s + 1) per leaf).  The split levels of GEMM zones
+    and the direct near zone of other leaf edges than 4, 8, 16: 2 p^6 flops per
+    offset and target node, 2 s^6 per neighbour leaf and target leaf, on the unit
+    the precision puts them on (the other levels of GEMM zones and, at s = 4, 8,
+    16, the direct near zone sum per frequency in FP64); `products`
     is the number of bf16 products the split issues per algorithmic product
     (the matrix cores' peak applies to issued flops)."""
     s = N >> L
@@ -544,11 +544,13 @@ def kernel_work(name, N, L, p, route=None):
     if name.startswith("m2l L") and len(name.split()) == 2 and route["m2l"] == "gemm":
         lv = int(name.split()[1][1:])
         fl = (37 if lv == 2 else 189) * 2.0 * p ** 6 * 8 ** lv
-        if lv in FP64_LEVELS:
-            return fl, ("f64 mfma" if p == 8 else "f64 valu"), None, 1
-        if route["precision"] == "bf16x3" and p == 8:
+        if route["precision"] == "bf16x3" and p == 8 and lv not in FP64_LEVELS:
             return fl, "bf16 mfma", None, 6
-        return fl, "f32 valu", None, 1
+        # p >= 3: FP64 transforms and a sum per frequency on the FP64 matrix
+        # cores; gridlets in and out, spectra out and in twice
+        F, nodes = (2 * p) ** 2 * (p + 1), 8 ** lv
+        gl = 2 * (8.0 if lv in FP64_LEVELS else 4.0) * p ** 3 * nodes
+        return (37 if lv == 2 else 189) * 8.0 * F * nodes, "f64 mfma", gl + 4 * 16.0 * F * nodes, 1
     if name == "near" and route["near"] == "direct":
         fl = 27 * 2.0 * s ** 6 * 8 ** L
         if s in (4, 8, 16):  # FP64 transforms: density in, spectra out and in twice, potential out
@@ -591,13 +593,14 @@ def _default_work(name, N, L, p, s, fold=False, zones_fp32_level=None):
 
 
 def gemm_m2l_mfma(rho, args):
-    """The interaction zones as block-Toeplitz GEMMs on the matrix cores, on
-    the same density: split BF16 (three bf16 terms per operand, six products)
-    at the leaf level, FP64 matrix cores at the FP64 levels 2-3.  Per level:
-    HIP-event time of its launches (stages one after another), algorithmic
-    flops (2 p^6 per offset and target node), issued flops (times the
-    products; equal to the MOPS counters) and the fraction of the peak of the
-    matrix-core instruction that level runs on."""
+    """The default interaction zones in split precision on the same density: a
+    block-Toeplitz GEMM of split BF16 (three bf16 terms per operand, six
+    products) at the leaf level, FP64 sums per frequency at the FP64 levels
+    2-3.  Per level: HIP-event time of its launches (stages one after another),
+    algorithmic flops (2 p^6 per offset and target node of the GEMM, 8 per
+    offset, target node and frequency of the others), issued flops (times the
+    products) and the fraction of the peak of the instruction that level's
+    sums run on."""
     import torch
     from paper_2011_07099_amd.pfmm import Plan
     phi = torch.empty_like(rho)
@@ -619,8 +622,7 @@ def gemm_m2l_mfma(rho, args):
         torch.cuda.synchronize()
     levels, issued, budget = {}, 0.0, 0.0
     for lv, ms in sorted(lv_ms.items()):
-        fl = (37 if lv == 2 else 189) * 2.0 * P ** 6 * 8 ** lv
-        unit, products = ("f64 mfma", 1) if lv in FP64_LEVELS else ("bf16 mfma", 6)
+        fl, unit, _, products = kernel_work("m2l L%d" % lv, N, L, P, {"m2l": "gemm", "precision": "bf16x3"})
         peak = PEAK_UNIT[unit]
         tf = fl / (ms * 1e-3) / 1e12
         levels[str(lv)] = {"ms": ms, "unit": unit, "products": products, "flops": fl,
@@ -628,10 +630,10 @@ def gemm_m2l_mfma(rho, args):
                            "algorithmic_frac": tf / peak, "issued_frac": tf * products / peak}
         issued += fl * products
         budget += ms * 1e-3 * peak * 1e12
-    return {"route": "block-Toeplitz GEMM zones (split bf16 at level 4, FP64 matrix cores at "
-                     "levels 2-3), timed on the same density in this run",
-            "util": issued / budget, "util_note": "issued matrix-core flops of all levels over "
-            "the time-weighted peak of the instruction each level uses",
+    return {"route": "default zones in split precision (block-Toeplitz split bf16 at level 4, FP64 "
+                     "sums per frequency at levels 2-3), timed on the same density in this run",
+            "util": issued / budget, "util_note": "issued flops of all levels over the "
+            "time-weighted peak of the instruction each level uses",
             "levels": levels, "m2l_ms": sum(lv_ms.values()),
             "solve_ms_with_direct_near_zone": route_ms,
             "phi": phi}

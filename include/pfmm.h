@@ -240,8 +240,13 @@ typedef enum {
 
 /* Interaction-zone (M2L, Eq. 6) algorithm. */
 typedef enum {
-  /* Block-Toeplitz GEMM over the zone's offsets (matrix cores or the
-   * portable kernel, as PFMM_OPT_PRECISION selects). */
+  /* The sum over the zone's offsets with every pair's G.  Single solves with p
+   * >= 3 sum it in FP64, per frequency as PFMM_M2L_SPECTRAL does (exact up to
+   * FP64 rounding; every level in PFMM_PREC_FP32 and PFMM_PREC_FP64, the levels
+   * kept in FP64 in PFMM_PREC_BF16X3), on the levels whose spectra fit in 3 GiB
+   * (allocated with the plan: 0.3 GB at 16^3 nodes, p = 8).  Other levels,
+   * batches, and plans without that memory use block-Toeplitz GEMMs (matrix
+   * cores or the portable kernel, as PFMM_OPT_PRECISION selects). */
   PFMM_M2L_GEMM = 0,
   /* The Hierarchical Particle-Mesh form the paper runs (Sec. 2): per target
    * node the effective masses of its whole zone on one uniform grid, one FFT
@@ -256,7 +261,7 @@ typedef enum {
    * Eq. 6, whose separations |a - a'| <= p - 1 have distinct residues), the
    * zone's offsets (189 per parity class, the level-2 zone) summed per
    * frequency with the transformed kernels G(eta_l (m - p d)), one inverse
-   * per node.  All in FP64 on the vector ALUs, whatever
+   * per node.  All in FP64, whatever
    * PFMM_OPT_PRECISION and PFMM_OPT_FP64_LEVELS say; masses are read and
    * potentials added in each level's precision.  Allocates about
    * 2 (2p)^2 (p + 1) x 16 bytes per leaf-level node (0.3 GB at 16^3 nodes,

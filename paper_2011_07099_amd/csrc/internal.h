@@ -362,20 +362,26 @@ hipError_t near64_run_f64(const Near64* f, const double* rho, double* const* out
 // Interaction zones as spectral stencils (per-node transforms, FP64)
 // ---------------------------------------------------------------------------
 struct M2LSpectral;
-// Buffers for levels 2 .. L at gridlet size p (4 or 8); allocates.
+// Buffers for levels 2 .. L at gridlet size p (1 .. 10), m2l_spectral_bytes in
+// one allocation.
+size_t m2l_spectral_bytes(int L, int p);
 hipError_t m2l_spectral_create(int L, int p, M2LSpectral** out);
 void m2l_spectral_destroy(M2LSpectral* f);
+int m2l_spectral_levels(const M2LSpectral* f);  // L
 // Transform the kernels of every offset in [-3, 3]^3 from the FP64 level
 // tables; synchronises `st`.
 hipError_t m2l_spectral_tables(M2LSpectral* f, const std::vector<double*>& tab64, hipStream_t st);
-// on = 1: the 16^3 leaf level's stencil (L = 4) sums each zone column in
-// FP32 (FP32 sources and kernel values) and the column sums in FP64.
-void m2l_spectral_set_f32(M2LSpectral* f, int on);
+// Whether the 16^3 leaf level's FP32 kernel values are kept (see cols32);
+// synchronises `st` where that changes.
+hipError_t m2l_spectral_set_f32(M2LSpectral* f, int on, hipStream_t st);
 // Pl (+)= the level-l zone sums of Ml (Sec. 2's zones, or the isolated
-// twin's); m64 / p64: the buffers hold doubles.
+// twin's); m64 / p64: the buffers hold doubles.  cols32, with the FP32 kernel
+// values kept: the periodic 16^3 leaf level's stencil (L = 4) sums each zone
+// column in FP32 (FP32 sources and kernel values) and the column sums in FP64.
 // Parts for a timer: 0 the node transforms, 1 the stencil, 2 the inverse.
-hipError_t m2l_spectral_level(M2LSpectral* f, int l, const void* Ml, int m64, void* Pl, int p64,
-                              int accumulate, int isolated, hipStream_t st, KernelTimer* kt = nullptr);
+hipError_t m2l_spectral_level(const M2LSpectral* f, int l, const void* Ml, int m64, void* Pl, int p64,
+                              int accumulate, int isolated, int cols32, hipStream_t st,
+                              KernelTimer* kt = nullptr);
 
 // FP64 -> FP32 copy of n elements.
 hipError_t launch_cast_d2f(const double* src, float* dst, int64_t n, hipStream_t st);

@@ -13,10 +13,10 @@
 // GEMM's 2 p^6 flops per target and offset this is 8 flops per frequency
 // ((2p)^2 (p + 1) of them) plus the transforms.
 //
-// Everything here is FP64 (transforms, kernel spectra, stencil), on the
-// vector ALUs; masses are read and potentials added in the level's own
-// precision.  Kernel spectra (all 343 offsets of [-3, 3]^3) are transformed
-// once per table by the same separable FP64 DFT as the near zone's.
+// Everything here is FP64 (transforms, kernel spectra, stencil); masses are read
+// and potentials added in the level's own precision.  Kernel spectra (all 343
+// offsets of [-3, 3]^3) are transformed once per table.  PFMM_M2L_SPECTRAL and
+// most levels of the default zones run this way.
 //
 // Layout: spectra of a level as [frequency / 8][node][frequency % 8]: a
 // node's transform writes (and its inverse reads) 128-byte runs, and the 8
@@ -25,6 +25,8 @@
 #include "dft64.h"
 #include "internal.h"
 
+#include <algorithm>
+#include <type_traits>
 #include <vector>
 
 namespace pfmm {
@@ -37,7 +39,7 @@ struct M2LSpectral {
   std::vector<double2*> khatT;   // per level: [F][kKT] kernel values, offsets of [-3, 3]^3 innermost
   float2* khatT32 = nullptr;     // the leaf level's khatT in FP32 (the FP32 16^3 stencil)
   int f32 = 0;                   // the 16^3 level's stencil in FP32 with FP64 column totals
-  double2* dft[2] = {nullptr, nullptr};  // [343][F] DFT passes of the kernels
+  void* mem = nullptr;           // the one allocation that holds the arrays above
 };
 
 namespace {
@@ -94,11 +96,7 @@ __global__ void __launch_bounds__(node_threads<P>()) k_node_fwd(const TIN* __res
     ddft<P, false>(o);
     double2* row = A1 + r * H;
 #pragma unroll
-    for (int m = 0; m < P / 2; ++m) {
-      row[2 * m] = e[m];
-      row[2 * m + 1] = o[m];
-    }
-    row[P] = e[P / 2];
+    for (int k = 0; k < H; ++k) row[k] = (k & 1) ? o[k >> 1] : e[k >> 1];
   }
   __syncthreads();
 #pragma unroll
@@ -520,67 +518,130 @@ __global__ void k_khat_f32(const double2* __restrict__ in, int64_t n, float2* __
   if (i < n) out[i] = make_float2((float)in[i].x, (float)in[i].y);
 }
 
-// Kernel spectrum of offset d (FP64 separable DFT): first pass along z of
-// K_d[x][y][z] = tab[w(x) - p dx][w(y) - p dy][w(z) - p dz] (tab centred at
-// C), zero on the unused slot p; then y and x (k_sdft_axis); stored scaled
-// frequency by frequency, in the order of k_node_fwd (k_sdft_store).
-__global__ void k_sdft_z(const double* __restrict__ tab, int p, int C, double2* __restrict__ A) {
-  const int M = 2 * p, H = p + 1;
-  const int64_t F = (int64_t)M * M * H;
-  const int di = blockIdx.y;  // offset (dx, dy, dz) in [-3, 3]^3
-  const int dx = di / 49 - 3, dy = (di / 7) % 7 - 3, dz = di % 7 - 3;
-  A += di * F;
-  const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (i >= F) return;
-  const int kz = (int)(i % H), y = (int)((i / H) % M), x = (int)(i / ((int64_t)H * M));
-  const int E = 2 * C + 1;
-  double re = 0.0, im = 0.0;
-  if (x != p && y != p) {
-    const int jx = (x < p ? x : x - M) - p * dx, jy = (y < p ? y : y - M) - p * dy;
-    const double* row = tab + ((int64_t)(jx + C) * E + (jy + C)) * E;
-    for (int z = 0; z < M; ++z) {
-      if (z == p) continue;
-      const double v = row[(z < p ? z : z - M) - p * dz + C];
-      double sn, cs;
-      sincospi(-(double)((kz * z) % M) / p, &sn, &cs);
-      re += v * cs;
-      im += v * sn;
-    }
+// Kernel spectra of a level, in place in khatT: [x][y][kz] rows of 344 offsets,
+// the layout of the finished table.  Along z of K_d[x][y][z] = tab[w(x) - p dx]
+// [w(y) - p dy][w(z) - p dz] (tab centred at C), zero on the unused slot p; along
+// y, whose results go to their place in the order of k_node_fwd; along x with
+// the normalisation.  One thread per offset and column, the column in
+// registers, so that every access is a run over the offsets; blockIdx.z takes
+// the levels.
+//
+// In twice FP64's precision, rounded once at the end (`low` holds the low parts
+// between the passes, laid out as khatT): the kernel is smooth, so its high
+// frequencies are small, but in FP64 they would carry rounding of the size of
+// the low ones, which the alternating effective masses of a gridlet amplify.
+// Measured on 16^3 cells, two levels, p = 8, against extended precision: relative
+// error of the FP64 potential 9.9e-14 with spectra in FP64, 5.2e-14 with these,
+// 5.6e-14 by block-Toeplitz products.
+//
+// Bound: the passes' traffic, 3 writes and 2 reads of twice 12.7 MB a level at p
+// = 8, and the sums' own latency: 55 us for two levels (one thread per frequency
+// with its twiddles computed for each term and a scattered store, in FP64: 155).
+struct KhatLevels {
+  const double* tab[16];
+  double2 *khat[16], *low[16];
+};
+
+// DFT of 2P values in registers, natural order
+template <int P, class T>
+__device__ __forceinline__ void ddft2(T (&v)[2 * P]) {
+  T e[P], o[P];
+#pragma unroll
+  for (int j = 0; j < P; ++j) {
+    e[j] = v[2 * j];
+    o[j] = v[2 * j + 1];
   }
-  A[i] = make_double2(re, im);
+  ddft<P, false>(e);
+  ddft<P, false>(o);
+#pragma unroll
+  for (int j = 0; j < P; ++j) {
+    const T t = j ? dtwiddle<2 * P, false>(o[j], j) : o[j];
+    v[j] = dadd(e[j], t);
+    v[j + P] = dsub(e[j], t);
+  }
 }
 
-__global__ void k_sdft_axis(const double2* __restrict__ in, int p, int axis, double2* __restrict__ out) {
-  const int M = 2 * p, H = p + 1;
-  const int64_t F = (int64_t)M * M * H;
-  in += blockIdx.y * F;
-  out += blockIdx.y * F;
-  const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (i >= F) return;
-  const int kz = (int)(i % H), b = (int)((i / H) % M), a = (int)(i / ((int64_t)H * M));
-  const int kk = axis ? b : a;
-  double re = 0.0, im = 0.0;
-  for (int j = 0; j < M; ++j) {
-    const double2 v = in[axis ? ((int64_t)a * M + j) * H + kz : ((int64_t)j * M + b) * H + kz];
-    double sn, cs;
-    sincospi(-(double)((kk * j) % M) / p, &sn, &cs);
-    re += v.x * cs - v.y * sn;
-    im += v.x * sn + v.y * cs;
-  }
-  out[i] = make_double2(re, im);
+__device__ __forceinline__ wide2 load_wide(const double2* h, const double2* l, int64_t i) {
+  const double2 a = h[i], b = l[i];
+  return {{a.x, b.x}, {a.y, b.y}};
+}
+__device__ __forceinline__ void store_wide(double2* h, double2* l, int64_t i, wide2 v) {
+  h[i] = make_double2(v.x.h, v.y.h);
+  l[i] = make_double2(v.x.l, v.y.l);
 }
 
-__global__ void k_sdft_store(const double2* __restrict__ in, int p, double scale, double2* __restrict__ khatT) {
-  const int M = 2 * p, H = p + 1;
-  const int64_t F = (int64_t)M * M * H;
-  const int di = blockIdx.y;
-  in += di * F;
-  const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (i >= F) return;
-  const int kz = (int)(i % H), ky = (int)((i / H) % M), kx = (int)(i / ((int64_t)H * M));
-  const int64_t d = ((int64_t)(kx * 2 + (ky & 1)) * p + (ky >> 1)) * H + kz;
-  khatT[d * kKT + di] = make_double2(in[i].x * scale, in[i].y * scale);
-  if (di == 342) khatT[d * kKT + 343] = make_double2(0.0, 0.0);  // padding
+constexpr int kKB = 64;  // offsets per workgroup of the kernel transforms
+
+template <int P>
+__global__ void __launch_bounds__(kKB) k_khat_z(KhatLevels lv) {
+  constexpr int M = 2 * P, H = P + 1, C = 4 * P - 1, E = 2 * C + 1;
+  const int di = blockIdx.y * kKB + threadIdx.x;
+  if (di >= kKT) return;
+  const int y = blockIdx.x % M, x = blockIdx.x / M;
+  wide2 v[M];
+#pragma unroll
+  for (int z = 0; z < M; ++z) v[z] = wide2{{0.0, 0.0}, {0.0, 0.0}};
+  if (x != P && y != P && di < 343) {  // offset 343 is padding
+    const int dx = di / 49 - 3, dy = (di / 7) % 7 - 3, dz = di % 7 - 3;
+    const int jx = (x < P ? x : x - M) - P * dx, jy = (y < P ? y : y - M) - P * dy;
+    const double* row = lv.tab[blockIdx.z] + ((int64_t)(jx + C) * E + (jy + C)) * E + (C - P * dz);
+#pragma unroll
+    for (int z = 0; z < M; ++z)
+      if (z != P) v[z].x.h = row[z < P ? z : z - M];
+    ddft2<P>(v);
+  }
+  const int64_t o = (int64_t)blockIdx.x * H * kKT + di;
+#pragma unroll
+  for (int k = 0; k < H; ++k) store_wide(lv.khat[blockIdx.z], lv.low[blockIdx.z], o + k * kKT, v[k]);
+}
+
+template <int P>
+__global__ void __launch_bounds__(kKB) k_khat_y(KhatLevels lv) {
+  constexpr int M = 2 * P, H = P + 1;
+  const int di = blockIdx.y * kKB + threadIdx.x;
+  if (di >= kKT) return;
+  const int kz = blockIdx.x % H, x = blockIdx.x / H;
+  double2 *h = lv.khat[blockIdx.z], *l = lv.low[blockIdx.z];
+  const int64_t c = ((int64_t)x * M * H + kz) * kKT + di;
+  wide2 v[M];
+#pragma unroll
+  for (int y = 0; y < M; ++y) v[y] = load_wide(h, l, c + (int64_t)y * H * kKT);
+  ddft2<P>(v);
+#pragma unroll
+  for (int k = 0; k < M; ++k) store_wide(h, l, c + (int64_t)((k & 1) * P + (k >> 1)) * H * kKT, v[k]);
+}
+
+template <int P>
+__global__ void __launch_bounds__(kKB) k_khat_x(KhatLevels lv) {
+  constexpr int M = 2 * P, H = P + 1;
+  constexpr double scale = 1.0 / (M * M * M);
+  const int di = blockIdx.y * kKB + threadIdx.x;
+  if (di >= kKT) return;
+  double2 *h = lv.khat[blockIdx.z], *l = lv.low[blockIdx.z];
+  const int64_t c = (int64_t)blockIdx.x * kKT + di;  // row y' H + kz
+  wide2 v[M];
+#pragma unroll
+  for (int x = 0; x < M; ++x) v[x] = load_wide(h, l, c + (int64_t)x * M * H * kKT);
+  ddft2<P>(v);
+#pragma unroll
+  for (int k = 0; k < M; ++k)
+    h[c + (int64_t)k * M * H * kKT] = make_double2(v[k].x.h * scale, v[k].y.h * scale);
+}
+
+template <int P>
+hipError_t khat_levels(const M2LSpectral* f, const std::vector<double*>& tab64, hipStream_t st) {
+  constexpr int M = 2 * P, H = P + 1, nb = (kKT + kKB - 1) / kKB;
+  KhatLevels lv{};
+  for (int l = 2; l <= f->L; ++l) {
+    lv.tab[l - 2] = tab64[l];
+    lv.khat[l - 2] = f->khatT[l];
+    lv.low[l - 2] = f->spec + (l - 2) * f->F * kKT;  // before the level's spectra
+  }
+  const unsigned nl = f->L - 1;
+  k_khat_z<P><<<dim3(M * M, nb, nl), kKB, 0, st>>>(lv);
+  k_khat_y<P><<<dim3(M * H, nb, nl), kKB, 0, st>>>(lv);
+  k_khat_x<P><<<dim3(M * H, nb, nl), kKB, 0, st>>>(lv);
+  return hipGetLastError();
 }
 
 inline hipError_t tbegin(KernelTimer* kt, hipStream_t st) { return kt ? kt->begin(st) : hipSuccess; }
@@ -612,14 +673,13 @@ void zone_oct(const M2LSpectral* f, int l, int n, int isolated, int nchunk, hipS
 }
 
 template <int P>
-hipError_t run_level(M2LSpectral* f, int l, const void* Ml, int m64, void* Pl, int p64,
-                     int accumulate, int isolated, hipStream_t st,
-                     KernelTimer* kt) {
+hipError_t run_level(const M2LSpectral* f, int l, const void* Ml, int m64, void* Pl, int p64,
+                     int accumulate, int isolated, int cols32, hipStream_t st, KernelTimer* kt) {
   const int n = 1 << l;
   const int64_t nn = (int64_t)n * n * n;
   constexpr int NT = node_threads<P>();
   // the 16^3 leaf level in FP32 columns: its spectra stored as float2
-  const bool f32 = n == 16 && !isolated && f->f32 && l == f->L && f->khatT32;
+  const bool f32 = n == 16 && !isolated && cols32 && f->f32 && l == f->L;
   float2* spec32 = reinterpret_cast<float2*>(f->spec);
   float2* out32 = reinterpret_cast<float2*>(f->out);
   hipError_t e = tbegin(kt, st);
@@ -665,66 +725,99 @@ hipError_t run_level(M2LSpectral* f, int l, const void* Ml, int m64, void* Pl, i
 
 }  // namespace
 
+// f(P) for the gridlet size p of 1 .. 10 as a template argument
+template <class F>
+hipError_t with_p(int p, F&& f) {
+  switch (p) {
+    case 1: return f(std::integral_constant<int, 1>());
+    case 2: return f(std::integral_constant<int, 2>());
+    case 3: return f(std::integral_constant<int, 3>());
+    case 4: return f(std::integral_constant<int, 4>());
+    case 5: return f(std::integral_constant<int, 5>());
+    case 6: return f(std::integral_constant<int, 6>());
+    case 7: return f(std::integral_constant<int, 7>());
+    case 8: return f(std::integral_constant<int, 8>());
+    case 9: return f(std::integral_constant<int, 9>());
+    case 10: return f(std::integral_constant<int, 10>());
+    default: return hipErrorInvalidValue;
+  }
+}
+
 void m2l_spectral_destroy(M2LSpectral* f) {
   if (!f) return;
-  (void)hipFree(f->spec);
-  (void)hipFree(f->out);
-  for (double2* k : f->khatT) (void)hipFree(k);
-  (void)hipFree(f->khatT32);
-  for (double2* d : f->dft) (void)hipFree(d);
+  (void)hipFree(f->mem);
   delete f;
 }
 
+namespace {
+// Values per frequency of the two node spectra, which also hold the low parts
+// of every level's kernels while these are transformed
+size_t spectra_per_freq(int L) { return std::max((size_t)2 << (3 * L), (size_t)(L - 1) * kKT); }
+}  // namespace
+
+size_t m2l_spectral_bytes(int L, int p) {
+  const size_t F = (size_t)(2 * p) * (2 * p) * (p + 1);
+  return F * ((spectra_per_freq(L) + (size_t)(L - 1) * kKT) * sizeof(double2) +
+              (L == 4 ? kKT * sizeof(float2) : 0));
+}
+
+int m2l_spectral_levels(const M2LSpectral* f) { return f->L; }
+
 hipError_t m2l_spectral_create(int L, int p, M2LSpectral** out) {
   *out = nullptr;
-  if (p != 4 && p != 6 && p != 8) return hipErrorInvalidValue;
+  if (p < 1 || p > 10 || L < 2) return hipErrorInvalidValue;
+  void* mem = nullptr;
+  const hipError_t e = hipMalloc(&mem, m2l_spectral_bytes(L, p));
+  if (e != hipSuccess) return e;
   M2LSpectral* f = new M2LSpectral;
   f->L = L;
   f->p = p;
   f->F = (int64_t)(2 * p) * (2 * p) * (p + 1);
-  const int64_t nodes = (int64_t)1 << (3 * L);
+  f->mem = mem;
+  double2* at = static_cast<double2*>(mem);
+  auto take = [&](int64_t n) {
+    double2* a = at;
+    at += n;
+    return a;
+  };
+  f->spec = take(f->F * (int64_t)spectra_per_freq(L));
+  f->out = f->spec + (f->F << (3 * L));
   f->khatT.assign(L + 1, nullptr);
-  hipError_t e = hipMalloc(&f->spec, (size_t)(f->F * nodes) * sizeof(double2));
-  if (e == hipSuccess) e = hipMalloc(&f->out, (size_t)(f->F * nodes) * sizeof(double2));
-  for (int d = 0; d < 2 && e == hipSuccess; ++d) e = hipMalloc(&f->dft[d], (size_t)(343 * f->F) * sizeof(double2));
-  for (int l = 2; l <= L && e == hipSuccess; ++l)
-    e = hipMalloc(&f->khatT[l], (size_t)(kKT * f->F) * sizeof(double2));
-  if (e == hipSuccess && L == 4) e = hipMalloc(&f->khatT32, (size_t)(kKT * f->F) * sizeof(float2));
-  if (e != hipSuccess) {
-    m2l_spectral_destroy(f);
-    return e;
-  }
+  for (int l = 2; l <= L; ++l) f->khatT[l] = take(f->F * kKT);
+  if (L == 4) f->khatT32 = reinterpret_cast<float2*>(at);
   *out = f;
   return hipSuccess;
 }
 
-void m2l_spectral_set_f32(M2LSpectral* f, int on) { f->f32 = on; }
+namespace {
+hipError_t khat_f32(const M2LSpectral* f, hipStream_t st) {
+  if (!f->f32 || !f->khatT32) return hipSuccess;
+  k_khat_f32<<<nblk(f->F * kKT), kThreads, 0, st>>>(f->khatT[f->L], f->F * kKT, f->khatT32);
+  return hipGetLastError();
+}
+}  // namespace
+
+hipError_t m2l_spectral_set_f32(M2LSpectral* f, int on, hipStream_t st) {
+  if (f->f32 == on) return hipSuccess;
+  f->f32 = on;
+  const hipError_t e = khat_f32(f, st);
+  return e == hipSuccess ? hipStreamSynchronize(st) : e;
+}
 
 hipError_t m2l_spectral_tables(M2LSpectral* f, const std::vector<double*>& tab64, hipStream_t st) {
-  const int p = f->p, C = 4 * p - 1;
-  const double scale = 1.0 / (double)((2 * p) * (2 * p) * (2 * p));
-  hipError_t e = hipSuccess;
-  const dim3 grid(nblk(f->F), 343);  // all offsets of [-3, 3]^3 at once
-  for (int l = 2; l <= f->L && e == hipSuccess; ++l) {
-    k_sdft_z<<<grid, kThreads, 0, st>>>(tab64[l], p, C, f->dft[0]);
-    k_sdft_axis<<<grid, kThreads, 0, st>>>(f->dft[0], p, 1, f->dft[1]);
-    k_sdft_axis<<<grid, kThreads, 0, st>>>(f->dft[1], p, 0, f->dft[0]);
-    k_sdft_store<<<grid, kThreads, 0, st>>>(f->dft[0], p, scale, f->khatT[l]);
-    if (l == f->L && f->khatT32)
-      k_khat_f32<<<nblk(f->F * kKT), kThreads, 0, st>>>(f->khatT[l], f->F * kKT, f->khatT32);
-    e = hipGetLastError();
-  }
+  hipError_t e = with_p(f->p, [&](auto P) { return khat_levels<decltype(P)::value>(f, tab64, st); });
+  if (e == hipSuccess) e = khat_f32(f, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   return e;
 }
 
-hipError_t m2l_spectral_level(M2LSpectral* f, int l, const void* Ml, int m64, void* Pl, int p64,
-                              int accumulate, int isolated, hipStream_t st,
+hipError_t m2l_spectral_level(const M2LSpectral* f, int l, const void* Ml, int m64, void* Pl, int p64,
+                              int accumulate, int isolated, int cols32, hipStream_t st,
                               KernelTimer* kt) {
   if (l < 2 || l > f->L) return hipErrorInvalidValue;
-  if (f->p == 4) return run_level<4>(f, l, Ml, m64, Pl, p64, accumulate, isolated, st, kt);
-  if (f->p == 6) return run_level<6>(f, l, Ml, m64, Pl, p64, accumulate, isolated, st, kt);
-  return run_level<8>(f, l, Ml, m64, Pl, p64, accumulate, isolated, st, kt);
+  return with_p(f->p, [&](auto P) {
+    return run_level<decltype(P)::value>(f, l, Ml, m64, Pl, p64, accumulate, isolated, cols32, st, kt);
+  });
 }
 
 }  // namespace pfmm

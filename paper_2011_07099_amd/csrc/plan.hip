@@ -66,7 +66,9 @@ struct pfmm_plan_s {
   int m2l_fft = 0;                // interaction zones by FFT convolution (PFMM_OPT_M2L)
   M2LFft* fft = nullptr;          // its plans, grids and transformed kernels
   int m2l_spectral = 0;           // interaction zones as spectral stencils (PFMM_OPT_M2L)
-  M2LSpectral* mspec = nullptr;   // its spectra and transformed kernels
+  M2LSpectral* mspec = nullptr;   // spectra and transformed kernels of its levels, and of the
+                                  // default zones' (single solves)
+  int zone_top = 0;               // the default zones' finest level by transforms
   int near_fft = 0;               // leaf near zone by FFT convolution (PFMM_OPT_NEAR)
   int fold = 0;                   // P2M and L2P inside its leaf transforms (PFMM_OPT_FOLD)
   int zones_f32 = 0;              // FP32 columns in the 16^3 spectral stencil (PFMM_OPT_ZONES_FP32)
@@ -392,6 +394,36 @@ pfmm_status refresh_near64(pfmm_plan_s* pl) {
     return PFMM_OK;
   }
   return e == hipSuccess ? PFMM_OK : hip_fail(e, "FP64 near zone");
+}
+
+// The default zones (PFMM_M2L_GEMM) of a single solve go by per-node FP64
+// transforms and a sum per frequency too, where that is the better route:
+//  * gridlets of p >= 3.  A solve at s = 4, L = 4, FP32 leaf level: p = 3 174 us
+//    against 240 by block-Toeplitz products, p = 8 0.59 ms against 6.7; p = 2, s =
+//    2: 142 against 140 (the 16^3 level's stencil alone 40 against 23 us), so p =
+//    1 and 2 keep the products;
+//  * every level in FP32 and FP64 precision (the FP32 products' rounding goes, at
+//    no point more error); in split precision the levels kept in FP64 only: the
+//    split level's own rounding is as large as what its results may move by;
+//  * levels whose spectra fit in 3 GiB (p = 8: up to 32^3 nodes).
+// Else, without the memory, and in batches: block-Toeplitz products.
+constexpr int kZoneMinP = 3;
+bool zones_by_transforms(const pfmm_plan_s* pl, int l) {
+  return pl->mspec && l <= pl->zone_top &&
+         (pl->prec != PFMM_PREC_BF16X3 || level64(pl, l));
+}
+pfmm_status create_zones(pfmm_plan_s* pl) {
+  if (pl->p < kZoneMinP) return PFMM_OK;
+  int top = pl->L;
+  while (top >= 2 && m2l_spectral_bytes(top, pl->p) > ((size_t)3 << 30)) --top;
+  if (top < 2) return PFMM_OK;
+  const hipError_t e = m2l_spectral_create(top, pl->p, &pl->mspec);
+  if (e == hipSuccess) pl->zone_top = top;
+  if (e == hipErrorOutOfMemory) {
+    (void)hipGetLastError();
+    return PFMM_OK;
+  }
+  return e == hipSuccess ? PFMM_OK : hip_fail(e, "zone buffers");
 }
 
 // Every transformed near-zone kernel follows the tables.
@@ -730,6 +762,7 @@ pfmm_status build(pfmm_plan_s* pl) {
   if (e == hipSuccess) e = hipEventCreateWithFlags(&pl->ev_mass, hipEventDisableTiming);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&pl->ev_local, hipEventDisableTiming);
   if ((st = chk("fork events"))) return st;
+  if ((st = create_zones(pl))) return st;
   return tabulate_all(pl);
 }
 
@@ -818,7 +851,10 @@ pfmm_status pfmm_plan_set(pfmm_plan_t h, int option, const void* value, size_t b
       std::memcpy(&v, value, sizeof v);
       if (v != 0 && v != 1) return fail(PFMM_ERR_INVALID_ARG, "zones_fp32 is 0 or 1");
       pl->zones_f32 = v;
-      if (pl->mspec) m2l_spectral_set_f32(pl->mspec, v);
+      if (pl->mspec) {
+        const hipError_t e = m2l_spectral_set_f32(pl->mspec, v, pl->stream);
+        if (e != hipSuccess) return hip_fail(e, "FP32 zone kernels");
+      }
       return PFMM_OK;
     }
     case PFMM_OPT_FOLD: {
@@ -911,14 +947,18 @@ pfmm_status pfmm_plan_set(pfmm_plan_t h, int option, const void* value, size_t b
       if (v == PFMM_M2L_SPECTRAL) {
         if (pl->p != 4 && pl->p != 6 && pl->p != 8)
           return fail(PFMM_ERR_UNSUPPORTED, "the spectral interaction zones need p = 4, 6 or 8");
-        if (!pl->mspec) {
+        if (!pl->mspec || m2l_spectral_levels(pl->mspec) < pl->L) {
           M2LSpectral* f = nullptr;
           hipError_t e = m2l_spectral_create(pl->L, pl->p, &f);
           if (e == hipErrorOutOfMemory) return fail(PFMM_ERR_OUT_OF_MEMORY, "spectral zone buffers");
           if (e != hipSuccess) return hip_fail(e, "spectral zone buffers");
-          m2l_spectral_set_f32(f, pl->zones_f32);
+          if (pl->mspec) {
+            (void)hipStreamSynchronize(pl->stream);
+            m2l_spectral_destroy(pl->mspec);
+          }
           pl->mspec = f;
           e = m2l_spectral_tables(pl->mspec, pl->tab64, pl->stream);
+          if (e == hipSuccess) e = m2l_spectral_set_f32(pl->mspec, pl->zones_f32, pl->stream);
           if (e != hipSuccess) return hip_fail(e, "spectral zone kernels");
         }
         pl->m2l_fft = 0;
@@ -1077,7 +1117,10 @@ pfmm_status solve_impl(pfmm_plan_s* pl, const void* rho_in, void* phi_out, void*
       return m2l_fft_level(pl->fft, l, ta.X, ta.Y, ta.fp64, ta.accumulate, st);
     if (pl->m2l_spectral)  // spectral stencils, FP64 throughout; each kernel timed
       return m2l_spectral_level(pl->mspec, l, ta.X, ta.fp64, ta.Y, ta.fp64, ta.accumulate,
-                                ta.isolated, st, tm.on ? &tm : nullptr);
+                                ta.isolated, pl->zones_f32, st, tm.on ? &tm : nullptr);
+    if (zones_by_transforms(pl, l))
+      return m2l_spectral_level(pl->mspec, l, ta.X, ta.fp64, ta.Y, ta.fp64, ta.accumulate,
+                                ta.isolated, 0, st);
     if (ta.fp64 && ta.q == 8 && ta.C >= 31) {  // FP64 coarse level on the matrix cores
       ToepF64Args fa{};
       fa.n = ta.n;
@@ -1793,7 +1836,7 @@ hipError_t batch_chain_solve(pfmm_batch_s* b, size_t f, hipStream_t st) {
                      pl->p, st);
     if (e == hipSuccess)
       e = m2l_spectral_level(pl->mspec, l, pl->M[l], level64(pl, l), pl->P[l], level64(pl, l), l > 2, 0,
-                             st);
+                             pl->zones_f32, st);
   }
   if (e == hipSuccess)
     e = launch_l2p(pl->P[pl->L], level64(pl, pl->L), b->phi[f], wts(pl->dA, pl->dA64), pl->N, pl->s,
@@ -1858,7 +1901,7 @@ hipError_t batch_enqueue(pfmm_batch_s* b, int part) {
       }
       for (int l = 2; l <= pl->L && e == hipSuccess && pl->m2l_spectral; ++l)
         e = m2l_spectral_level(pl->mspec, l, pl->M[l], level64(pl, l), pl->P[l], level64(pl, l), 0,
-                               0, st);
+                               0, pl->zones_f32, st);
     }
     if (e == hipSuccess) e = launch_batch_toeplitz(b->items, b->nitems, b->counter, b->grid, st);
     if (e == hipSuccess) e = hipEventRecord(b->ev_split, b->s_split);
