@@ -19,6 +19,8 @@
 // children); each kernel computes in the wider of its operand types.
 #include "internal.h"
 
+#include <type_traits>
+
 namespace pfmm {
 namespace {
 
@@ -80,27 +82,9 @@ __global__ __launch_bounds__(kThreads) void k_p2m(const TR* __restrict__ rho,
     __syncthreads();
   } else {
     for (int i = tid; i < p * s; i += kThreads) sA[(i / s) * sp + i % s] = A[i];
-    if constexpr (S % 4 == 0 && S > 0) {  // rows of s cells as float4 (16-byte aligned: s | N)
-      for (int i = tid; i < s * s * (s / 4); i += kThreads) {
-        const int row = i / (s / 4), q = i % (s / 4);
-        const int cx = row / s, cy = row % s;
-        const TR* src = rho + ((size_t)(bx * s + cx) * N + (by * s + cy)) * N + (size_t)bz * s + 4 * q;
-        W* dst = sr + row * sp + 4 * q;
-        if constexpr (sizeof(TR) == 4) {
-          const float4 v = *reinterpret_cast<const float4*>(src);
-          dst[0] = (W)v.x;
-          dst[1] = (W)v.y;
-          dst[2] = (W)v.z;
-          dst[3] = (W)v.w;
-        } else {
-          for (int c = 0; c < 4; ++c) dst[c] = (W)src[c];
-        }
-      }
-    } else {
-      for (int i = tid; i < s * s * s; i += kThreads) {
-        const int cx = i / (s * s), cy = (i / s) % s, cz = i % s;
-        sr[(cx * s + cy) * sp + cz] = (W)rho[((size_t)(bx * s + cx) * N + (by * s + cy)) * N + (bz * s + cz)];
-      }
+    for (int i = tid; i < s * s * s; i += kThreads) {
+      const int cx = i / (s * s), cy = (i / s) % s, cz = i % s;
+      sr[(cx * s + cy) * sp + cz] = (W)rho[((size_t)(bx * s + cx) * N + (by * s + cy)) * N + (bz * s + cz)];
     }
     __syncthreads();
     for (int i = tid; i < s * s * p; i += kThreads) {
@@ -124,224 +108,6 @@ __global__ __launch_bounds__(kThreads) void k_p2m(const TR* __restrict__ rho,
     W acc = 0;
     for (int cx = 0; cx < s; ++cx) acc += sA[ax * sp + cx] * t2[cx * p * p + ayz];
     M[(size_t)b * p3 + i] = (TO)(h3 * acc);
-  }
-}
-
-template <class TI, class TO, class W, int PP = 0>
-__global__ __launch_bounds__(kThreads) void k_m2m(const TI* __restrict__ Mc,
-                                                   TO* __restrict__ Mp, Weights Tw, int np,
-                                                   int p_) {
-  const int p = PP ? PP : p_;
-  extern __shared__ __align__(8) unsigned char smraw[];
-  W* sm = reinterpret_cast<W*>(smraw);
-  const int p3 = p * p * p;
-  W* sT = sm;  // [o][a][a']
-  W* c = sT + 2 * p * p;
-  W* u1 = c + p3;
-  W* u2 = u1 + p3;
-  const W* T = wsel<W>(Tw);
-  const int tid = threadIdx.x;
-  for (int i = tid; i < 2 * p * p; i += kThreads) sT[i] = T[i];
-  const int B = blockIdx.x;
-  const int Bx = B / (np * np), By = (B / np) % np, Bz = B % np;
-  const int nc = 2 * np;
-  W acc[4] = {0, 0, 0, 0};  // p^3 <= 1000 <= 4 * kThreads
-  for (int o = 0; o < 8; ++o) {
-    const int ox = o >> 2, oy = (o >> 1) & 1, oz = o & 1;
-    const size_t child = ((size_t)(2 * Bx + ox) * nc + (2 * By + oy)) * nc + (2 * Bz + oz);
-    __syncthreads();
-    for (int i = tid; i < p3; i += kThreads) c[i] = (W)Mc[child * p3 + i];
-    __syncthreads();
-    const W* Tz = sT + oz * p * p;
-    const W* Ty = sT + oy * p * p;
-    const W* Tx = sT + ox * p * p;
-    for (int i = tid; i < p3; i += kThreads) {  // u1[a'x][a'y][az]
-      const int xy = i / p, az = i % p;
-      W v = 0;
-      for (int k = 0; k < p; ++k) v += Tz[az * p + k] * c[xy * p + k];
-      u1[i] = v;
-    }
-    __syncthreads();
-    for (int i = tid; i < p3; i += kThreads) {  // u2[a'x][ay][az]
-      const int x = i / (p * p), ay = (i / p) % p, az = i % p;
-      W v = 0;
-      for (int k = 0; k < p; ++k) v += Ty[ay * p + k] * u1[(x * p + k) * p + az];
-      u2[i] = v;
-    }
-    __syncthreads();
-    for (int i = tid, r = 0; i < p3; i += kThreads, ++r) {  // out[ax][ay][az]
-      const int ax = i / (p * p), yz = i % (p * p);
-      W v = 0;
-      for (int k = 0; k < p; ++k) v += Tx[ax * p + k] * u2[k * p * p + yz];
-      acc[r] += v;
-    }
-  }
-  for (int i = tid, r = 0; i < p3; i += kThreads, ++r) Mp[(size_t)B * p3 + i] = (TO)acc[r];
-}
-
-template <class TI, class TO, class W, int PP = 0>
-__global__ __launch_bounds__(kThreads) void k_l2l(const TI* __restrict__ Pp,
-                                                   TO* __restrict__ Pc, Weights Tw, int np,
-                                                   int p_, int accumulate) {
-  const int p = PP ? PP : p_;
-  extern __shared__ __align__(8) unsigned char smraw[];
-  W* sm = reinterpret_cast<W*>(smraw);
-  const int p3 = p * p * p;
-  W* sT = sm;
-  W* par = sT + 2 * p * p;
-  W* v1 = par + p3;
-  W* v2 = v1 + p3;
-  const W* T = wsel<W>(Tw);
-  const int tid = threadIdx.x;
-  const int B = blockIdx.x;
-  const int Bx = B / (np * np), By = (B / np) % np, Bz = B % np;
-  const int nc = 2 * np;
-  for (int i = tid; i < 2 * p * p; i += kThreads) sT[i] = T[i];
-  for (int i = tid; i < p3; i += kThreads) par[i] = (W)Pp[(size_t)B * p3 + i];
-  for (int o = 0; o < 8; ++o) {
-    const int ox = o >> 2, oy = (o >> 1) & 1, oz = o & 1;
-    const W* Tz = sT + oz * p * p;
-    const W* Ty = sT + oy * p * p;
-    const W* Tx = sT + ox * p * p;
-    __syncthreads();
-    for (int i = tid; i < p3; i += kThreads) {  // v1[ax][ay][a'z] = sum_az Tz[az][a'z] par
-      const int xy = i / p, bz = i % p;
-      W v = 0;
-      for (int k = 0; k < p; ++k) v += Tz[k * p + bz] * par[xy * p + k];
-      v1[i] = v;
-    }
-    __syncthreads();
-    for (int i = tid; i < p3; i += kThreads) {  // v2[ax][a'y][a'z]
-      const int x = i / (p * p), by = (i / p) % p, bz = i % p;
-      W v = 0;
-      for (int k = 0; k < p; ++k) v += Ty[k * p + by] * v1[(x * p + k) * p + bz];
-      v2[i] = v;
-    }
-    __syncthreads();
-    const size_t child = ((size_t)(2 * Bx + ox) * nc + (2 * By + oy)) * nc + (2 * Bz + oz);
-    for (int i = tid; i < p3; i += kThreads) {  // out[a'x][a'y][a'z]
-      const int bx = i / (p * p), yz = i % (p * p);
-      W v = 0;
-      for (int k = 0; k < p; ++k) v += Tx[k * p + bx] * v2[k * p * p + yz];
-      Pc[child * p3 + i] = accumulate ? (TO)((W)Pc[child * p3 + i] + v) : (TO)v;
-    }
-  }
-}
-
-// M2M and L2L with the gridlet size fixed at compile time, the eight
-// children in one pass per axis instead of one child after another.  The
-// child operators are T_o = T_ox (x) T_oy (x) T_oz with two 1D matrices
-// T_0, T_1, so along each axis the two children of a pair share the pass:
-// M2M contracts x over (ox, kx) for the four (oy, oz), then y over (oy, ky)
-// for the two oz, then z over (oz, kz) (14 p^4 multiply-adds against
-// 24 p^4 child by child, three barriers against 32); L2L expands x into the
-// two ox, y into four (ox, oy), z into the eight children.
-template <class TI, class TO, class W, int P>
-__global__ __launch_bounds__(kThreads) void k_m2m_pairs(const TI* __restrict__ Mc,
-                                                         TO* __restrict__ Mp, Weights Tw, int np) {
-  constexpr int P2 = P * P, P3 = P2 * P;
-  extern __shared__ __align__(8) unsigned char smraw[];
-  W* sT = reinterpret_cast<W*>(smraw);  // [o][a][k]
-  W* sTt = sT + 2 * P2;                 // [o][k][a]
-  W* c = sTt + 2 * P2;                  // children [ox][oy][oz][kx][ky][kz]
-  W* w = c + 8 * P3;                    // [oy][oz][ax][ky][kz]
-  W* v = c;                             // [oz][ax][ay][kz], over the children
-  const W* T = wsel<W>(Tw);
-  const int tid = threadIdx.x;
-  for (int i = tid; i < 2 * P2; i += kThreads) {
-    const int o = i / P2, a = (i / P) % P, k = i % P;
-    sT[i] = T[i];
-    sTt[(o * P + k) * P + a] = T[i];
-  }
-  const int B = blockIdx.x;
-  const int Bx = B / (np * np), By = (B / np) % np, Bz = B % np;
-  const int nc = 2 * np;
-  for (int i = tid; i < 8 * P3; i += kThreads) {
-    const int o = i / P3;
-    const size_t child = ((size_t)(2 * Bx + (o >> 2)) * nc + (2 * By + ((o >> 1) & 1))) * nc +
-                         (2 * Bz + (o & 1));
-    c[i] = (W)Mc[child * P3 + i % P3];
-  }
-  __syncthreads();
-  for (int i = tid; i < 4 * P3; i += kThreads) {
-    const int q = i / P3, ax = (i / P2) % P, kyz = i % P2;
-    W acc = 0;
-#pragma unroll
-    for (int ox = 0; ox < 2; ++ox)
-#pragma unroll
-      for (int kx = 0; kx < P; ++kx)
-        acc += sT[(ox * P + ax) * P + kx] * c[((ox * 4 + q) * P + kx) * P2 + kyz];
-    w[i] = acc;
-  }
-  __syncthreads();
-  for (int i = tid; i < 2 * P3; i += kThreads) {
-    const int oz = i / P3, ax = (i / P2) % P, ay = (i / P) % P, kz = i % P;
-    W acc = 0;
-#pragma unroll
-    for (int oy = 0; oy < 2; ++oy)
-#pragma unroll
-      for (int ky = 0; ky < P; ++ky)
-        acc += sT[(oy * P + ay) * P + ky] * w[(oy * 2 + oz) * P3 + (ax * P + ky) * P + kz];
-    v[i] = acc;
-  }
-  __syncthreads();
-  for (int i = tid; i < P3; i += kThreads) {
-    const int axy = i / P, az = i % P;
-    W acc = 0;
-#pragma unroll
-    for (int oz = 0; oz < 2; ++oz)
-#pragma unroll
-      for (int kz = 0; kz < P; ++kz) acc += sTt[(oz * P + kz) * P + az] * v[oz * P3 + axy * P + kz];
-    Mp[(size_t)B * P3 + i] = (TO)acc;
-  }
-}
-
-template <class TI, class TO, class W, int P>
-__global__ __launch_bounds__(kThreads) void k_l2l_pairs(const TI* __restrict__ Pp,
-                                                         TO* __restrict__ Pc, Weights Tw, int np,
-                                                         int accumulate) {
-  constexpr int P2 = P * P, P3 = P2 * P;
-  extern __shared__ __align__(8) unsigned char smraw[];
-  W* sT = reinterpret_cast<W*>(smraw);  // [o][a][b]: child node b from parent node a
-  W* par = sT + 2 * P2;                 // [ax][ay][az]
-  W* w = par + P3;                      // [ox][bx][ay][az]
-  W* v = w + 2 * P3;                    // [ox][oy][bx][by][az]
-  const W* T = wsel<W>(Tw);
-  const int tid = threadIdx.x;
-  const int B = blockIdx.x;
-  const int Bx = B / (np * np), By = (B / np) % np, Bz = B % np;
-  const int nc = 2 * np;
-  for (int i = tid; i < 2 * P2; i += kThreads) sT[i] = T[i];
-  for (int i = tid; i < P3; i += kThreads) par[i] = (W)Pp[(size_t)B * P3 + i];
-  __syncthreads();
-  for (int i = tid; i < 2 * P3; i += kThreads) {
-    const int ox = i / P3, bx = (i / P2) % P, ayz = i % P2;
-    W acc = 0;
-#pragma unroll
-    for (int ax = 0; ax < P; ++ax) acc += sT[(ox * P + ax) * P + bx] * par[ax * P2 + ayz];
-    w[i] = acc;
-  }
-  __syncthreads();
-  for (int i = tid; i < 4 * P3; i += kThreads) {
-    const int q = i / P3, bx = (i / P2) % P, by = (i / P) % P, az = i % P;
-    const int ox = q >> 1, oy = q & 1;
-    W acc = 0;
-#pragma unroll
-    for (int ay = 0; ay < P; ++ay)
-      acc += sT[(oy * P + ay) * P + by] * w[ox * P3 + (bx * P + ay) * P + az];
-    v[i] = acc;
-  }
-  __syncthreads();
-  for (int i = tid; i < 8 * P3; i += kThreads) {
-    const int o = i / P3, bxy = (i / P) % P2, bz = i % P;
-    const int oz = o & 1;
-    W acc = 0;
-#pragma unroll
-    for (int az = 0; az < P; ++az) acc += sT[(oz * P + az) * P + bz] * v[(o >> 1) * P3 + bxy * P + az];
-    const size_t child = ((size_t)(2 * Bx + (o >> 2)) * nc + (2 * By + ((o >> 1) & 1))) * nc +
-                         (2 * Bz + oz);
-    TO* dst = Pc + child * P3 + i % P3;
-    *dst = accumulate ? (TO)((W)*dst + acc) : (TO)acc;
   }
 }
 
@@ -447,24 +213,351 @@ __global__ __launch_bounds__(kThreads) void k_l2p(const TI* __restrict__ P,
   }
 }
 
-template <class T>
+// M2M and L2L, the eight children in one pass per axis.  The child operators
+// are T_o = T_ox (x) T_oy (x) T_oz with two 1D matrices T_0, T_1, so along each
+// axis the two children of a pair share the pass: M2M contracts x over (ox, kx)
+// for the four (oy, oz), then y over (oy, ky) for the two oz, then z over (oz,
+// kz) (14 p^4 multiply-adds against 24 p^4 child by child); L2L expands x into
+// the two ox, y into four (ox, oy), z into the eight children.
+//
+// A lane takes whole columns (the values along the contracted axis in
+// registers, from memory in the first pass), a wave the outputs whose weights
+// it reads as scalars: an LDS value is read once for several outputs and no
+// weight is read from LDS.  Reading both factors of every product from LDS was
+// the bound, and child by child (p other than 4 and 8) the barriers.  Measured
+// before / after: 64 parents in FP64 M2M 33 / 5 us at p = 7, 17 / 4.5 at p = 6, 11 /
+// 5.5 at p = 8, L2L 23 / 4.0, 13 / 3.9 and 7.5 / 5.5; 4096 parents of FP32 children, p =
+// 8, M2M 207 / 27 us.
+// LDS rows are padded to an odd number of values.
+template <class TI, class TO, class W, int P>
+__global__ __launch_bounds__(kThreads) void k_m2m(const TI* __restrict__ Mc, TO* __restrict__ Mp,
+                                                   Weights Tw, int np) {
+  constexpr int P2 = P * P, P3 = P2 * P, Q = P | 1;
+  __shared__ W w[4 * P2 * Q];  // [oy][oz][ax][ky][kz]
+  __shared__ W v[2 * P2 * Q];  // [oz][ax][ay][kz]
+  const W* __restrict__ T = wsel<W>(Tw);  // [o][a][k]
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int B = blockIdx.x;
+  const int Bx = B / (np * np), By = (B / np) % np, Bz = B % np;
+  const int nc = 2 * np;
+  for (int c = lane; c < P2; c += 64) {  // (ky, kz) of the wave's (oy, oz)
+    W in[2 * P];
+#pragma unroll
+    for (int ox = 0; ox < 2; ++ox) {
+      const size_t child = ((size_t)(2 * Bx + ox) * nc + (2 * By + (wave >> 1))) * nc + (2 * Bz + (wave & 1));
+#pragma unroll
+      for (int kx = 0; kx < P; ++kx) in[ox * P + kx] = (W)Mc[child * P3 + kx * P2 + c];
+    }
+#pragma unroll
+    for (int ax = 0; ax < P; ++ax) {
+      W acc = 0;
+#pragma unroll
+      for (int k = 0; k < 2 * P; ++k) acc += T[((k / P) * P + ax) * P + k % P] * in[k];
+      w[((wave * P + ax) * P + c / P) * Q + c % P] = acc;
+    }
+  }
+  __syncthreads();
+  for (int c = lane; c < P2; c += 64) {  // (ax, kz) of oz = wave % 2, every other ay
+    const int oz = wave & 1, ax = c / P, kz = c % P;
+    W in[2 * P];
+#pragma unroll
+    for (int k = 0; k < 2 * P; ++k) in[k] = w[((((k / P) * 2 + oz) * P + ax) * P + k % P) * Q + kz];
+#pragma unroll
+    for (int i = 0; i < (P + 1) / 2; ++i) {
+      const int ay = 2 * i + (wave >> 1);
+      if (ay >= P) break;
+      W acc = 0;
+#pragma unroll
+      for (int k = 0; k < 2 * P; ++k) acc += T[((k / P) * P + ay) * P + k % P] * in[k];
+      v[((oz * P + ax) * P + ay) * Q + kz] = acc;
+    }
+  }
+  __syncthreads();
+  for (int c = lane; c < P2; c += 64) {  // (ax, ay), every fourth az
+    W in[2 * P];
+#pragma unroll
+    for (int k = 0; k < 2 * P; ++k) in[k] = v[((k / P) * P2 + c) * Q + k % P];
+#pragma unroll
+    for (int i = 0; i < (P + 3) / 4; ++i) {
+      const int az = 4 * i + wave;
+      if (az >= P) break;
+      W acc = 0;
+#pragma unroll
+      for (int k = 0; k < 2 * P; ++k) acc += T[((k / P) * P + az) * P + k % P] * in[k];
+      Mp[(size_t)B * P3 + c * P + az] = (TO)acc;
+    }
+  }
+}
+
+template <class TI, class TO, class W, int P>
+__global__ __launch_bounds__(kThreads) void k_l2l(const TI* __restrict__ Pp, TO* __restrict__ Pc,
+                                                   Weights Tw, int np, int accumulate) {
+  constexpr int P2 = P * P, P3 = P2 * P, Q = P | 1;
+  __shared__ W w[2 * P2 * Q];  // [ox][bx][ay][az]
+  __shared__ W v[4 * P2 * Q];  // [ox][oy][bx][by][az]
+  const W* __restrict__ T = wsel<W>(Tw);  // [o][a][b]: child node b from parent node a
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int B = blockIdx.x;
+  const int Bx = B / (np * np), By = (B / np) % np, Bz = B % np;
+  const int nc = 2 * np;
+  for (int c = lane; c < P2; c += 64) {  // (ay, az) of ox = wave % 2, every other bx
+    const int ox = wave & 1;
+    W in[P];
+#pragma unroll
+    for (int a = 0; a < P; ++a) in[a] = (W)Pp[(size_t)B * P3 + a * P2 + c];
+#pragma unroll
+    for (int i = 0; i < (P + 1) / 2; ++i) {
+      const int bx = 2 * i + (wave >> 1);
+      if (bx >= P) break;
+      W acc = 0;
+#pragma unroll
+      for (int a = 0; a < P; ++a) acc += T[(ox * P + a) * P + bx] * in[a];
+      w[((ox * P + bx) * P + c / P) * Q + c % P] = acc;
+    }
+  }
+  __syncthreads();
+  for (int c = lane; c < P2; c += 64) {  // (bx, az) of (ox, oy) = wave
+    const int bx = c / P, az = c % P;
+    W in[P];
+#pragma unroll
+    for (int a = 0; a < P; ++a) in[a] = w[(((wave >> 1) * P + bx) * P + a) * Q + az];
+#pragma unroll
+    for (int by = 0; by < P; ++by) {
+      W acc = 0;
+#pragma unroll
+      for (int a = 0; a < P; ++a) acc += T[((wave & 1) * P + a) * P + by] * in[a];
+      v[((wave * P + bx) * P + by) * Q + az] = acc;
+    }
+  }
+  __syncthreads();
+  for (int c = lane; c < P2; c += 64) {  // (bx, by) of (ox, oy) = wave
+    W in[P];
+#pragma unroll
+    for (int a = 0; a < P; ++a) in[a] = v[(wave * P2 + c) * Q + a];
+#pragma unroll
+    for (int oz = 0; oz < 2; ++oz) {
+      const size_t child = ((size_t)(2 * Bx + (wave >> 1)) * nc + (2 * By + (wave & 1))) * nc + (2 * Bz + oz);
+      TO* dst = Pc + child * P3 + c * P;
+#pragma unroll
+      for (int bz = 0; bz < P; ++bz) {
+        W acc = 0;
+#pragma unroll
+        for (int a = 0; a < P; ++a) acc += T[(oz * P + a) * P + bz] * in[a];
+        dst[bz] = accumulate ? (TO)((W)dst[bz] + acc) : (TO)acc;
+      }
+    }
+  }
+}
+
+// P2M and L2P of leaves of 8 or 16 cells by columns, as M2M and L2L: a lane
+// holds a column of cells or nodes in registers, the weights are scalars.  P2M
+// contracts z, y, x (mesh rows in the first pass), L2P expands z, y, x (the last
+// pass writes the mesh, its prior values read before the first).  Any
+// alignment.  FP32 gridlets of p = 4 and 8 keep the kernels above, whose rows
+// move as float4 (256^3, p = 8: P2M 29 us there and 24 here, L2P 35 and 34, 512^3 175
+// and 159, 247 and 262; p = 4 alike).  Bound: latency of the three passes up to some
+// 10^3 leaves, then the mesh's traffic.  Measured before (one output a thread,
+// both factors of every product from LDS) / after, FP64 gridlets, 512 leaves of s
+// = 16, p = 6: P2M 18 / 8 us, L2P 20 / 6; p = 8, 19 / 6 and 23 / 5.5.
+template <class TR, class TO, class W, int S, int P>
+__global__ __launch_bounds__(kThreads) void k_p2m_cols(const TR* __restrict__ rho, TO* __restrict__ M,
+                                                        Weights Aw, int N, W h3, int vec) {
+  constexpr int P2 = P * P, Q = P | 1, G = kThreads / (S * S);  // waves per row set: 1 or 4 share the az
+  constexpr bool kHalves = S * P <= kThreads / 2;
+  __shared__ W t1[S * S * Q];  // [cx][cy][az]
+  __shared__ W t2[S * P * Q];  // [cx][ay][az]
+  const W* __restrict__ A = wsel<W>(Aw);  // [a][c]
+  const int nL = N / S;
+  const int b = (int)xcd_leaf(blockIdx.x, (int64_t)nL * nL * nL);
+  const int bx = b / (nL * nL), by = (b / nL) % nL, bz = b % nL;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  {
+    const int r = tid % (S * S), g = G == 1 ? 0 : wave;
+    const TR* src = rho + ((size_t)(bx * S + r / S) * N + (by * S + r % S)) * N + (size_t)bz * S;
+    TR row[S];
+    if (vec) {
+      constexpr int V = 16 / sizeof(TR);
+      typedef TR vec_t __attribute__((ext_vector_type(V)));
+#pragma unroll
+      for (int q = 0; q < S / V; ++q) {
+        const vec_t x = reinterpret_cast<const vec_t*>(src)[q];
+#pragma unroll
+        for (int i = 0; i < V; ++i) row[V * q + i] = x[i];
+      }
+    } else {
+#pragma unroll
+      for (int c = 0; c < S; ++c) row[c] = src[c];
+    }
+#pragma unroll
+    for (int i = 0; i < (P + G - 1) / G; ++i) {
+      const int az = G * i + g;
+      if (az >= P) break;
+      W acc = 0;
+#pragma unroll
+      for (int c = 0; c < S; ++c) acc += A[az * S + c] * (W)row[c];
+      t1[r * Q + az] = acc;
+    }
+  }
+  __syncthreads();
+  const int col = kHalves ? tid % (kThreads / 2) : tid, h = kHalves ? wave >> 1 : 0;
+  if (col < S * P) {
+    const int cx = col / P, az = col % P;
+    W in[S];
+#pragma unroll
+    for (int c = 0; c < S; ++c) in[c] = t1[(cx * S + c) * Q + az];
+    constexpr int step = kHalves ? 2 : 1;
+#pragma unroll
+    for (int i = 0; i < (P + step - 1) / step; ++i) {
+      const int ay = step * i + h;
+      if (ay >= P) break;
+      W acc = 0;
+#pragma unroll
+      for (int c = 0; c < S; ++c) acc += A[ay * S + c] * in[c];
+      t2[(cx * P + ay) * Q + az] = acc;
+    }
+  }
+  __syncthreads();
+  for (int c = lane; c < P2; c += 64) {  // (ay, az), every fourth ax
+    W in[S];
+#pragma unroll
+    for (int x = 0; x < S; ++x) in[x] = t2[(x * P + c / P) * Q + c % P];
+#pragma unroll
+    for (int i = 0; i < (P + 3) / 4; ++i) {
+      const int ax = 4 * i + wave;
+      if (ax >= P) break;
+      W acc = 0;
+#pragma unroll
+      for (int x = 0; x < S; ++x) acc += A[ax * S + x] * in[x];
+      M[(size_t)b * (P2 * P) + ax * P2 + c] = (TO)(h3 * acc);
+    }
+  }
+}
+
+template <class TI, class TP, class W, int S, int P>
+__global__ __launch_bounds__(kThreads) void k_l2p_cols(const TI* __restrict__ Pl, TP* __restrict__ phi,
+                                                        Weights Wxw, Weights Wyw, Weights Wzw, W scale,
+                                                        int N, int accumulate) {
+  constexpr int P2 = P * P, G = kThreads / (S * S), SX = S / G;  // cx per thread of the last pass
+  constexpr bool kHalves = S * P <= kThreads / 2;
+  constexpr int step = kHalves ? 2 : 1;
+  __shared__ W w1[P2 * (S + 1)];  // [ax][ay][cz]
+  __shared__ W w2[P * S * S];     // [ax][cy][cz]
+  const W* __restrict__ Ax = wsel<W>(Wxw);
+  const W* __restrict__ Ay = wsel<W>(Wyw);
+  const W* __restrict__ Az = wsel<W>(Wzw);
+  const int nL = N / S;
+  const int b = (int)xcd_leaf(blockIdx.x, (int64_t)nL * nL * nL);
+  const int bx = b / (nL * nL), by = (b / nL) % nL, bz = b % nL;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int yz = tid % (S * S), x0 = (G == 1 ? 0 : wave) * SX;
+  TP* dst = phi + ((size_t)(bx * S + x0) * N + (by * S + yz / S)) * N + (size_t)bz * S + yz % S;
+  TP prior[SX];
+  if (accumulate) {
+#pragma unroll
+    for (int x = 0; x < SX; ++x) prior[x] = dst[(size_t)x * N * N];
+  }
+  for (int c = lane; c < P2; c += 64) {  // (ax, ay), every fourth cz
+    W in[P];
+#pragma unroll
+    for (int a = 0; a < P; ++a) in[a] = (W)Pl[(size_t)b * (P2 * P) + c * P + a];
+#pragma unroll
+    for (int i = 0; i < S / 4; ++i) {
+      const int cz = 4 * i + wave;
+      W acc = 0;
+#pragma unroll
+      for (int a = 0; a < P; ++a) acc += Az[a * S + cz] * in[a];
+      w1[c * (S + 1) + cz] = acc;
+    }
+  }
+  __syncthreads();
+  const int col = kHalves ? tid % (kThreads / 2) : tid, h = kHalves ? wave >> 1 : 0;
+  if (col < S * P) {
+    const int ax = col / S, cz = col % S;
+    W in[P];
+#pragma unroll
+    for (int a = 0; a < P; ++a) in[a] = w1[(ax * P + a) * (S + 1) + cz];
+#pragma unroll
+    for (int i = 0; i < S / step; ++i) {
+      const int cy = step * i + h;
+      W acc = 0;
+#pragma unroll
+      for (int a = 0; a < P; ++a) acc += Ay[a * S + cy] * in[a];
+      w2[(ax * S + cy) * S + cz] = acc;
+    }
+  }
+  __syncthreads();
+  W in[P];
+#pragma unroll
+  for (int a = 0; a < P; ++a) in[a] = w2[a * S * S + yz];
+#pragma unroll
+  for (int x = 0; x < SX; ++x) {
+    W acc = 0;
+#pragma unroll
+    for (int a = 0; a < P; ++a) acc += Ax[a * S + x0 + x] * in[a];
+    acc *= scale;
+    dst[(size_t)x * N * N] = accumulate ? (TP)((W)prior[x] + acc) : (TP)acc;
+  }
+}
+
+// V consecutive cells along z per thread, their rows read and written as
+// vectors (V = 1: any alignment).  Bound: 16 bytes a cell from and to memory in
+// FP32; 128^3 14 us with one cell per thread, 9
+// by vectors.
+template <class T, int V>
 __global__ __launch_bounds__(kThreads) void k_fd4(const T* __restrict__ phi,
                                                    T* __restrict__ acc, int N) {
+  typedef T vec_t __attribute__((ext_vector_type(V)));
   const size_t n3 = (size_t)N * N * N;
-  const size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x;
+  const size_t i = ((size_t)blockIdx.x * kThreads + threadIdx.x) * V;
   if (i >= n3) return;
   const int z = (int)(i % N), y = (int)((i / N) % N), x = (int)(i / ((size_t)N * N));
   const int mk = N - 1;
   const T inv12h = (T)N / (T)12;
-  auto at = [&](int xx, int yy, int zz) {
-    return phi[((size_t)(xx & mk) * N + (yy & mk)) * N + (zz & mk)];
+  auto row = [&](int xx, int yy, int zz, T* v) {  // V cells from zz on
+    const T* p = phi + ((size_t)(xx & mk) * N + (yy & mk)) * N + (zz & mk);
+    if constexpr (V > 1) {
+      const vec_t q = *reinterpret_cast<const vec_t*>(p);
+#pragma unroll
+      for (int c = 0; c < V; ++c) v[c] = q[c];
+    } else {
+      v[0] = *p;
+    }
   };
-  const T gx = -at(x + 2, y, z) + (T)8 * at(x + 1, y, z) - (T)8 * at(x - 1, y, z) + at(x - 2, y, z);
-  const T gy = -at(x, y + 2, z) + (T)8 * at(x, y + 1, z) - (T)8 * at(x, y - 1, z) + at(x, y - 2, z);
-  const T gz = -at(x, y, z + 2) + (T)8 * at(x, y, z + 1) - (T)8 * at(x, y, z - 1) + at(x, y, z - 2);
-  acc[i] = -gx * inv12h;
-  acc[n3 + i] = -gy * inv12h;
-  acc[2 * n3 + i] = -gz * inv12h;
+  T xp2[V], xp1[V], xm1[V], xm2[V], yp2[V], yp1[V], ym1[V], ym2[V];
+  row(x + 2, y, z, xp2);
+  row(x + 1, y, z, xp1);
+  row(x - 1, y, z, xm1);
+  row(x - 2, y, z, xm2);
+  row(x, y + 2, z, yp2);
+  row(x, y + 1, z, yp1);
+  row(x, y - 1, z, ym1);
+  row(x, y - 2, z, ym2);
+  constexpr int K = V > 1 ? 1 : 2;  // vectors on either side that hold the two next cells
+  T w[(2 * K + 1) * V];             // cells z - K V ... of the row
+#pragma unroll
+  for (int k = -K; k <= K; ++k) row(x, y, z + k * V, w + (k + K) * V);
+  T g[3][V];
+#pragma unroll
+  for (int c = 0; c < V; ++c) {
+    const T* o = w + K * V + c;
+    const T gx = -xp2[c] + (T)8 * xp1[c] - (T)8 * xm1[c] + xm2[c];
+    const T gy = -yp2[c] + (T)8 * yp1[c] - (T)8 * ym1[c] + ym2[c];
+    const T gz = -o[2] + (T)8 * o[1] - (T)8 * o[-1] + o[-2];
+    g[0][c] = -gx * inv12h;
+    g[1][c] = -gy * inv12h;
+    g[2][c] = -gz * inv12h;
+  }
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    if constexpr (V > 1) {
+      vec_t q;
+#pragma unroll
+      for (int c = 0; c < V; ++c) q[c] = g[d][c];
+      *reinterpret_cast<vec_t*>(acc + d * n3 + i) = q;
+    } else {
+      acc[d * n3 + i] = g[d][0];
+    }
+  }
 }
 
 __global__ void k_d2f(const double* __restrict__ s, float* __restrict__ d, int64_t n) {
@@ -484,150 +577,144 @@ inline size_t p2m_words_rows(int s, int p) {
   return (size_t)(p * (s + 1) + s * s * p + s * p * p);
 }
 
+namespace {
+// f(P) for the gridlet size p of 1 .. 10 as a template argument
+template <class F>
+hipError_t with_p(int p, F&& f) {
+  switch (p) {
+    case 1: return f(std::integral_constant<int, 1>());
+    case 2: return f(std::integral_constant<int, 2>());
+    case 3: return f(std::integral_constant<int, 3>());
+    case 4: return f(std::integral_constant<int, 4>());
+    case 5: return f(std::integral_constant<int, 5>());
+    case 6: return f(std::integral_constant<int, 6>());
+    case 7: return f(std::integral_constant<int, 7>());
+    case 8: return f(std::integral_constant<int, 8>());
+    case 9: return f(std::integral_constant<int, 9>());
+    case 10: return f(std::integral_constant<int, 10>());
+    default: return hipErrorInvalidValue;
+  }
+}
+
+// P2M, L2P by columns where the leaf has 8 or 16 cells, else the general form
+template <class TR, class TO, class W>
+hipError_t p2m_any(const TR* rho, TO* M, Weights A, int N, int s, int p, W h3, hipStream_t st) {
+  const int nL = N / s;
+  const dim3 g(nL * nL * nL), b(kThreads);
+  if (s != 8 && s != 16) {
+    hipLaunchKernelGGL((k_p2m<TO, W, 0, 0, TR>), g, b, p2m_words(s, p) * sizeof(W), st, rho, M, A, N, s, p, h3);
+    return hipGetLastError();
+  }
+  const int vec = ((uintptr_t)rho & 15) == 0;
+  return with_p(p, [&](auto P) {
+    constexpr int p_ = decltype(P)::value;
+    if (s == 16)
+      hipLaunchKernelGGL((k_p2m_cols<TR, TO, W, 16, p_>), g, b, 0, st, rho, M, A, N, h3, vec);
+    else
+      hipLaunchKernelGGL((k_p2m_cols<TR, TO, W, 8, p_>), g, b, 0, st, rho, M, A, N, h3, vec);
+    return hipGetLastError();
+  });
+}
+
+template <class TI, class TP, class W>
+hipError_t l2p_any(const TI* P, TP* out, Weights Wx, Weights Wy, Weights Wz, W scale, int N, int s, int p,
+                   hipStream_t st, int accumulate) {
+  const int nL = N / s;
+  const dim3 g(nL * nL * nL), b(kThreads);
+  if (s != 8 && s != 16) {
+    const size_t words = (size_t)(3 * p * s + p * p * p + p * p * s + p * s * s);
+    hipLaunchKernelGGL((k_l2p<TI, W, 0, 0, TP>), g, b, words * sizeof(W), st, P, out, Wx, Wy, Wz, scale, N, s,
+                       p, accumulate);
+    return hipGetLastError();
+  }
+  return with_p(p, [&](auto Pc) {
+    constexpr int p_ = decltype(Pc)::value;
+    if (s == 16)
+      hipLaunchKernelGGL((k_l2p_cols<TI, TP, W, 16, p_>), g, b, 0, st, P, out, Wx, Wy, Wz, scale, N, accumulate);
+    else
+      hipLaunchKernelGGL((k_l2p_cols<TI, TP, W, 8, p_>), g, b, 0, st, P, out, Wx, Wy, Wz, scale, N, accumulate);
+    return hipGetLastError();
+  });
+}
+}  // namespace
+
 hipError_t launch_p2m(const float* rho, void* M, int m64, Weights A, int N, int s, int p,
                       double h3, hipStream_t st) {
+  if (m64) return p2m_any(rho, (double*)M, A, N, s, p, h3, st);
+  const float hf = (float)h3;
+  // FP32 gridlets of p = 4, 8: rows of cells as float4
+  if ((s != 8 && s != 16) || (p != 4 && p != 8) || ((uintptr_t)rho & 15))
+    return p2m_any(rho, (float*)M, A, N, s, p, hf, st);
   const int nL = N / s;
-  const size_t words = p2m_words(s, p);
-  if (m64)
-    hipLaunchKernelGGL((k_p2m<double, double>), dim3(nL * nL * nL), dim3(kThreads),
-                       words * sizeof(double), st, rho, (double*)M, A, N, s, p, h3);
-  else {
-    const dim3 g(nL * nL * nL), b(kThreads);
-    size_t sh = words * sizeof(float);
-    const float hf = (float)h3;
-    // the compile-time instances read rows of cells as float4
-    const bool aligned = ((uintptr_t)rho & 15) == 0;
-    if (aligned && (s == 16 || s == 8) && (p == 8 || p == 4))
-      sh = p2m_words_rows(s, p) * sizeof(float);
-    if (!aligned)
-      hipLaunchKernelGGL((k_p2m<float, float>), g, b, sh, st, rho, (float*)M, A, N, s, p, hf);
-    else if (s == 16 && p == 8)
-      hipLaunchKernelGGL((k_p2m<float, float, 16, 8>), g, b, sh, st, rho, (float*)M, A, N, s, p, hf);
-    else if (s == 8 && p == 8)
-      hipLaunchKernelGGL((k_p2m<float, float, 8, 8>), g, b, sh, st, rho, (float*)M, A, N, s, p, hf);
-    else if (s == 16 && p == 4)
-      hipLaunchKernelGGL((k_p2m<float, float, 16, 4>), g, b, sh, st, rho, (float*)M, A, N, s, p, hf);
-    else if (s == 8 && p == 4)
-      hipLaunchKernelGGL((k_p2m<float, float, 8, 4>), g, b, sh, st, rho, (float*)M, A, N, s, p, hf);
-    else
-      hipLaunchKernelGGL((k_p2m<float, float>), g, b, sh, st, rho, (float*)M, A, N, s, p, hf);
-  }
+  const dim3 g(nL * nL * nL), b(kThreads);
+  const size_t sh = p2m_words_rows(s, p) * sizeof(float);
+  if (s == 16 && p == 8)
+    hipLaunchKernelGGL((k_p2m<float, float, 16, 8>), g, b, sh, st, rho, (float*)M, A, N, s, p, hf);
+  else if (s == 8 && p == 8)
+    hipLaunchKernelGGL((k_p2m<float, float, 8, 8>), g, b, sh, st, rho, (float*)M, A, N, s, p, hf);
+  else if (s == 16)
+    hipLaunchKernelGGL((k_p2m<float, float, 16, 4>), g, b, sh, st, rho, (float*)M, A, N, s, p, hf);
+  else
+    hipLaunchKernelGGL((k_p2m<float, float, 8, 4>), g, b, sh, st, rho, (float*)M, A, N, s, p, hf);
   return hipGetLastError();
 }
 
-// M2M / L2L instance with the gridlet size fixed at compile time for p = 4
-// and 8 (index arithmetic folded, loops unrolled), else the generic one.
-#define PFMM_BY_P(KERNEL, TI, TO, W, ...)                        \
-  do {                                                            \
-    if (p == 8)                                                   \
-      hipLaunchKernelGGL((KERNEL<TI, TO, W, 8>), __VA_ARGS__);    \
-    else if (p == 4)                                              \
-      hipLaunchKernelGGL((KERNEL<TI, TO, W, 4>), __VA_ARGS__);    \
-    else                                                          \
-      hipLaunchKernelGGL((KERNEL<TI, TO, W>), __VA_ARGS__);       \
-  } while (0)
-
-// The pairwise kernels at p = 4, 8 (LDS words: the weights twice, eight
-// children and the four x-contracted pairs).
-#define PFMM_PAIRS(KERNEL, TI, TO, W, ...)                        \
-  do {                                                            \
-    if (p == 8)                                                   \
-      hipLaunchKernelGGL((KERNEL<TI, TO, W, 8>), __VA_ARGS__);    \
-    else                                                          \
-      hipLaunchKernelGGL((KERNEL<TI, TO, W, 4>), __VA_ARGS__);    \
-  } while (0)
-
 hipError_t launch_m2m(const void* Mc, int c64, void* Mp, int p64, Weights T, int np, int p,
                       hipStream_t st) {
+  if (c64 && !p64) return hipErrorInvalidValue;  // a finer level is never wider than its parent
   const dim3 g(np * np * np), b(kThreads);
-  if (p == 4 || p == 8) {
-    const size_t pw = (size_t)(4 * p * p + 12 * p * p * p);
-    if (!c64 && !p64)
-      PFMM_PAIRS(k_m2m_pairs, float, float, float, g, b, pw * 4, st, (const float*)Mc, (float*)Mp, T, np);
-    else if (!c64 && p64)
-      PFMM_PAIRS(k_m2m_pairs, float, double, double, g, b, pw * 8, st, (const float*)Mc, (double*)Mp, T, np);
-    else if (c64 && p64)
-      PFMM_PAIRS(k_m2m_pairs, double, double, double, g, b, pw * 8, st, (const double*)Mc, (double*)Mp, T,
-                 np);
+  return with_p(p, [&](auto P) {
+    constexpr int p_ = decltype(P)::value;
+    if (!p64)
+      hipLaunchKernelGGL((k_m2m<float, float, float, p_>), g, b, 0, st, (const float*)Mc, (float*)Mp, T, np);
+    else if (!c64)
+      hipLaunchKernelGGL((k_m2m<float, double, double, p_>), g, b, 0, st, (const float*)Mc, (double*)Mp, T, np);
     else
-      return hipErrorInvalidValue;
+      hipLaunchKernelGGL((k_m2m<double, double, double, p_>), g, b, 0, st, (const double*)Mc, (double*)Mp, T,
+                         np);
     return hipGetLastError();
-  }
-  const size_t words = (size_t)(2 * p * p + 3 * p * p * p);
-  if (!c64 && !p64)
-    PFMM_BY_P(k_m2m, float, float, float, g, b, words * 4, st, (const float*)Mc, (float*)Mp, T, np, p);
-  else if (!c64 && p64)
-    PFMM_BY_P(k_m2m, float, double, double, g, b, words * 8, st, (const float*)Mc, (double*)Mp, T, np, p);
-  else if (c64 && p64)
-    PFMM_BY_P(k_m2m, double, double, double, g, b, words * 8, st, (const double*)Mc, (double*)Mp, T,
-              np, p);
-  else
-    return hipErrorInvalidValue;  // a finer level is never wider than its parent
-  return hipGetLastError();
+  });
 }
 
 hipError_t launch_l2l(const void* Pp, int p64, void* Pc, int c64, Weights T, int np, int p,
                       hipStream_t st, int accumulate) {
+  if (c64 && !p64) return hipErrorInvalidValue;
   const dim3 g(np * np * np), b(kThreads);
-  if (p == 4 || p == 8) {
-    const size_t pw = (size_t)(2 * p * p + 7 * p * p * p);
-    if (!p64 && !c64)
-      PFMM_PAIRS(k_l2l_pairs, float, float, float, g, b, pw * 4, st, (const float*)Pp, (float*)Pc, T, np,
-                 accumulate);
-    else if (p64 && !c64)
-      PFMM_PAIRS(k_l2l_pairs, double, float, double, g, b, pw * 8, st, (const double*)Pp, (float*)Pc, T,
-                 np, accumulate);
-    else if (p64 && c64)
-      PFMM_PAIRS(k_l2l_pairs, double, double, double, g, b, pw * 8, st, (const double*)Pp, (double*)Pc,
-                 T, np, accumulate);
+  return with_p(p, [&](auto P) {
+    constexpr int p_ = decltype(P)::value;
+    if (!p64)
+      hipLaunchKernelGGL((k_l2l<float, float, float, p_>), g, b, 0, st, (const float*)Pp, (float*)Pc, T, np,
+                         accumulate);
+    else if (!c64)
+      hipLaunchKernelGGL((k_l2l<double, float, double, p_>), g, b, 0, st, (const double*)Pp, (float*)Pc, T, np,
+                         accumulate);
     else
-      return hipErrorInvalidValue;
+      hipLaunchKernelGGL((k_l2l<double, double, double, p_>), g, b, 0, st, (const double*)Pp, (double*)Pc, T,
+                         np, accumulate);
     return hipGetLastError();
-  }
-  const size_t words = (size_t)(2 * p * p + 3 * p * p * p);
-  if (!p64 && !c64)
-    PFMM_BY_P(k_l2l, float, float, float, g, b, words * 4, st, (const float*)Pp, (float*)Pc, T, np, p,
-              accumulate);
-  else if (p64 && !c64)
-    PFMM_BY_P(k_l2l, double, float, double, g, b, words * 8, st, (const double*)Pp, (float*)Pc, T, np,
-              p, accumulate);
-  else if (p64 && c64)
-    PFMM_BY_P(k_l2l, double, double, double, g, b, words * 8, st, (const double*)Pp, (double*)Pc, T,
-              np, p, accumulate);
-  else
-    return hipErrorInvalidValue;
-  return hipGetLastError();
+  });
 }
-#undef PFMM_BY_P
-#undef PFMM_PAIRS
 
 namespace {
 hipError_t l2p_axes(const void* P, int p64, float* out, Weights Wx, Weights Wy, Weights Wz,
                     double scale, int N, int s, int p, hipStream_t st, int accumulate) {
+  if (p64) return l2p_any((const double*)P, out, Wx, Wy, Wz, scale, N, s, p, st, accumulate);
+  const float sc = (float)scale;
+  const float* Pf = (const float*)P;
+  // FP32 gridlets of p = 4, 8: rows of cells as float4
+  if ((s != 8 && s != 16) || (p != 4 && p != 8) || ((uintptr_t)out & 15))
+    return l2p_any(Pf, out, Wx, Wy, Wz, sc, N, s, p, st, accumulate);
   const int nL = N / s;
-  const size_t words = (size_t)(3 * p * s + p * p * p + p * p * s + p * s * s);
-  if (p64)
-    hipLaunchKernelGGL((k_l2p<double, double>), dim3(nL * nL * nL), dim3(kThreads),
-                       words * sizeof(double), st, (const double*)P, out, Wx, Wy, Wz, scale, N, s,
-                       p, accumulate);
-  else {
-    const dim3 g(nL * nL * nL), b(kThreads);
-    const size_t sh = words * sizeof(float);
-    const float sc = (float)scale;
-    const float* Pf = (const float*)P;
-    if (((uintptr_t)out & 15) != 0)  // the compile-time instances write float4
-      hipLaunchKernelGGL((k_l2p<float, float>), g, b, sh, st, Pf, out, Wx, Wy, Wz, sc, N, s, p, accumulate);
-    else if (s == 16 && p == 8)
-      hipLaunchKernelGGL((k_l2p<float, float, 16, 8>), g, b, sh, st, Pf, out, Wx, Wy, Wz, sc, N, s, p, accumulate);
-    else if (s == 8 && p == 8)
-      hipLaunchKernelGGL((k_l2p<float, float, 8, 8>), g, b, sh, st, Pf, out, Wx, Wy, Wz, sc, N, s, p, accumulate);
-    else if (s == 16 && p == 4)
-      hipLaunchKernelGGL((k_l2p<float, float, 16, 4>), g, b, sh, st, Pf, out, Wx, Wy, Wz, sc, N, s, p, accumulate);
-    else if (s == 8 && p == 4)
-      hipLaunchKernelGGL((k_l2p<float, float, 8, 4>), g, b, sh, st, Pf, out, Wx, Wy, Wz, sc, N, s, p, accumulate);
-    else
-      hipLaunchKernelGGL((k_l2p<float, float>), g, b, sh, st, Pf, out, Wx, Wy, Wz, sc, N, s, p, accumulate);
-  }
+  const dim3 g(nL * nL * nL), b(kThreads);
+  const size_t sh = (size_t)(3 * p * s + p * p * p + p * p * s + p * s * s) * sizeof(float);
+  if (s == 16 && p == 8)
+    hipLaunchKernelGGL((k_l2p<float, float, 16, 8>), g, b, sh, st, Pf, out, Wx, Wy, Wz, sc, N, s, p, accumulate);
+  else if (s == 8 && p == 8)
+    hipLaunchKernelGGL((k_l2p<float, float, 8, 8>), g, b, sh, st, Pf, out, Wx, Wy, Wz, sc, N, s, p, accumulate);
+  else if (s == 16)
+    hipLaunchKernelGGL((k_l2p<float, float, 16, 4>), g, b, sh, st, Pf, out, Wx, Wy, Wz, sc, N, s, p, accumulate);
+  else
+    hipLaunchKernelGGL((k_l2p<float, float, 8, 4>), g, b, sh, st, Pf, out, Wx, Wy, Wz, sc, N, s, p, accumulate);
   return hipGetLastError();
 }
 }  // namespace
@@ -648,52 +735,43 @@ hipError_t launch_l2p_grad(const void* P, int p64, float* acc, Weights A, Weight
   return hipSuccess;
 }
 
-hipError_t launch_fd4(const float* phi, float* acc, int N, hipStream_t st) {
-  const size_t n3 = (size_t)N * N * N;
-  hipLaunchKernelGGL(k_fd4<float>, dim3((unsigned)((n3 + kThreads - 1) / kThreads)), dim3(kThreads), 0,
-                     st, phi, acc, N);
-  return hipGetLastError();
-}
-
-hipError_t launch_fd4_f64(const double* phi, double* acc, int N, hipStream_t st) {
-  const size_t n3 = (size_t)N * N * N;
-  hipLaunchKernelGGL(k_fd4<double>, dim3((unsigned)((n3 + kThreads - 1) / kThreads)), dim3(kThreads),
-                     0, st, phi, acc, N);
-  return hipGetLastError();
-}
-
-hipError_t launch_p2m_f64in(const double* rho, void* M, Weights A, int N, int s, int p, double h3,
-                            hipStream_t st) {
-  const int nL = N / s;
-  const size_t words = p2m_words(s, p);
-  hipLaunchKernelGGL((k_p2m<double, double, 0, 0, double>), dim3(nL * nL * nL), dim3(kThreads),
-                     words * sizeof(double), st, rho, (double*)M, A, N, s, p, h3);
-  return hipGetLastError();
-}
-
 namespace {
-hipError_t l2p_axes_f64out(const void* P, double* out, Weights Wx, Weights Wy, Weights Wz,
-                           double scale, int N, int s, int p, hipStream_t st, int accumulate) {
-  const int nL = N / s;
-  const size_t words = (size_t)(3 * p * s + p * p * p + p * p * s + p * s * s);
-  hipLaunchKernelGGL((k_l2p<double, double, 0, 0, double>), dim3(nL * nL * nL), dim3(kThreads),
-                     words * sizeof(double), st, (const double*)P, out, Wx, Wy, Wz, scale, N, s, p,
-                     accumulate);
+template <class T>
+hipError_t fd4_any(const T* phi, T* acc, int N, hipStream_t st) {
+  constexpr int V = 16 / sizeof(T);  // N is a multiple of 8
+  const size_t n3 = (size_t)N * N * N;
+  if ((((uintptr_t)phi | (uintptr_t)acc) & 15) == 0)
+    hipLaunchKernelGGL((k_fd4<T, V>), dim3((unsigned)((n3 / V + kThreads - 1) / kThreads)), dim3(kThreads), 0,
+                       st, phi, acc, N);
+  else
+    hipLaunchKernelGGL((k_fd4<T, 1>), dim3((unsigned)((n3 + kThreads - 1) / kThreads)), dim3(kThreads), 0, st,
+                       phi, acc, N);
   return hipGetLastError();
 }
 }  // namespace
 
+hipError_t launch_fd4(const float* phi, float* acc, int N, hipStream_t st) { return fd4_any(phi, acc, N, st); }
+
+hipError_t launch_fd4_f64(const double* phi, double* acc, int N, hipStream_t st) {
+  return fd4_any(phi, acc, N, st);
+}
+
+hipError_t launch_p2m_f64in(const double* rho, void* M, Weights A, int N, int s, int p, double h3,
+                            hipStream_t st) {
+  return p2m_any(rho, (double*)M, A, N, s, p, h3, st);
+}
+
 hipError_t launch_l2p_f64out(const void* P, double* phi, Weights A, int N, int s, int p,
                              hipStream_t st, int accumulate) {
-  return l2p_axes_f64out(P, phi, A, A, A, 1.0, N, s, p, st, accumulate);
+  return l2p_any((const double*)P, phi, A, A, A, 1.0, N, s, p, st, accumulate);
 }
 
 hipError_t launch_l2p_grad_f64out(const void* P, double* acc, Weights A, Weights Ad, double scale,
                                   int N, int s, int p, hipStream_t st) {
   const size_t n3 = (size_t)N * N * N;
   for (int c = 0; c < 3; ++c) {
-    const hipError_t e = l2p_axes_f64out(P, acc + c * n3, c == 0 ? Ad : A, c == 1 ? Ad : A,
-                                         c == 2 ? Ad : A, scale, N, s, p, st, 1);
+    const hipError_t e = l2p_any((const double*)P, acc + c * n3, c == 0 ? Ad : A, c == 1 ? Ad : A,
+                                 c == 2 ? Ad : A, scale, N, s, p, st, 1);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
