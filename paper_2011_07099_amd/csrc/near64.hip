@@ -10,8 +10,8 @@
 // (2s)^2 (s + 1) frequencies, one inverse per leaf and kernel.  The term-by-term
 // sum, whose FP32 products cost 54 s^6 flops per leaf at 0.5 of the FP32 rate,
 // takes (128^3, s = 16) 7.0 ms per kernel and 0.78 ms at 64^3, s = 8; this takes
-// 0.19 and 0.045 ms (0.66 ms for the four kernels of the expansion accelerations
-// against 28), and 1.44 ms at 256^3 against 45 in FP32 and 8 in split bf16 on the
+// 0.157 and 0.034 ms (0.52 ms for the four kernels of the expansion accelerations
+// against 28), and 1.21 ms at 256^3 against 45 in FP32 and 8 in split bf16 on the
 // matrix cores.  Its error against 64 bits is that of
 // rounding the result (4.5e-8 of the norm at 128^3; the FP32 sums 9.8e-7).  The
 // transforms and sums are bound by HBM (144 B per cell of spectra, written and read
@@ -42,6 +42,7 @@ struct Near64 {
 namespace {
 
 constexpr int kThreads = 256;
+constexpr int kMacWaves = 4;                    // waves of one workgroup of the sums (a power of two)
 constexpr size_t kSlabBytes = (size_t)3 << 30;  // source and target spectra of a slab
 
 inline unsigned nblk(int64_t n) { return (unsigned)((n + kThreads - 1) / kThreads); }
@@ -252,79 +253,108 @@ __global__ void __launch_bounds__(leaf_threads<S>()) k_inv64(const double2* __re
 // z-plane of the 4 x 4 source columns around the block (16 bytes a lane, 1 KiB
 // a wave; four reads an output) and adds it to the three target planes that
 // see it, so one source plane and three planes of sums are in registers.  The
-// 27 kernel values of the lane are in its own slots of LDS.  The pencil blocks
-// of one chunk run on one XCD, whose L2 serves the columns they share.
+// 27 kernel values of a frequency are in LDS, shared by the kMacWaves waves of
+// a workgroup, which take neighbouring blocks or segments (their number is a
+// multiple of it: at least two by two blocks).  The pencil blocks of one chunk
+// run on one XCD, whose L2 serves the columns they share.
+//
+// Bound: waiting for memory (three or four waves a SIMD; 284 MB in 85 us at 128^3,
+// s = 16).  One wave a workgroup, its 27 KiB of kernel values its own, left 1.25
+// waves a SIMD, and a branch around every load one load in flight: 125 us at
+// 128^3, 29 (17 now) at 64^3, s = 8, 860 (610) at 256^3.  A second source plane in flight
+// took more registers and was slower (the whole near zone at 128^3 165 against 157 us).
 //
 // Target planes x0 .. x0 + nx - 1 (nx even, slots from 0 in yhat); source plane x sits
 // in slot (x - xs) mod nb of rhat (xs = 0 and nb slots without slabs).
 template <bool ISO>
-__global__ void __launch_bounds__(64) k_mac64(const double2* __restrict__ rhat, const double2* __restrict__ khat,
+__global__ void __launch_bounds__(64 * kMacWaves, 3) k_mac64(const double2* __restrict__ rhat, const double2* __restrict__ khat,
                                               int nb, int nchunk, int x0, int nx, int xs, int nz,
                                               int64_t nls, int64_t nlt, double2* __restrict__ yhat) {
   __shared__ double2 kks[27 * 64];
   const int hy = nb >> 1, hz = nb / nz, np = (nx >> 1) * hy * hz;  // 2 x 2 pencil blocks, z segments
-  const int j = blockIdx.x >> 3;
-  const int chunk = (j / np) * 8 + (blockIdx.x & 7);
+  const int j = blockIdx.x >> 3, ng = np / kMacWaves;              // groups of kMacWaves of them
+  const int chunk = (j / ng) * 8 + (blockIdx.x & 7);
   if (chunk >= nchunk) return;
-  const int lane = threadIdx.x, msk = nb - 1;
-  const int blk = j % np;
+  const int lane = threadIdx.x & 63, msk = nb - 1;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int blk = j % ng * kMacWaves + wave;
   const int bx0 = x0 + 2 * (blk / (hy * hz)), by0 = 2 * ((blk / hz) % hy), z0 = blk % hz * nz;
   const double2* src = rhat + (int64_t)chunk * nls * 64 + lane;
   double2* dst = yhat + (int64_t)chunk * nlt * 64 + lane;
   double2* kk = kks + lane;
-#pragma unroll
-  for (int e = 0; e < 27; ++e) kk[e * 64] = khat[((int64_t)chunk * 27 + e) * 64 + lane];
-  int64_t col[16];  // source columns (bx0 - 1 + ix, by0 - 1 + iy), c = 4 ix + iy; -1: outside
+  for (int e = wave; e < 27; e += kMacWaves) kk[e * 64] = khat[((int64_t)chunk * 27 + e) * 64 + lane];
+  __syncthreads();
+  unsigned col[16];  // source columns (bx0 - 1 + ix, by0 - 1 + iy), c = 4 ix + iy
+  bool in[16];
 #pragma unroll
   for (int c = 0; c < 16; ++c) {
     const int sx = bx0 - 1 + c / 4, sy = by0 - 1 + c % 4;
-    const bool in = !ISO || (sx >= 0 && sx < nb && sy >= 0 && sy < nb);
-    col[c] = in ? (int64_t)((((sx & msk) - xs) & msk) * nb + (sy & msk)) * nb : -1;
+    in[c] = !ISO || (sx >= 0 && sx < nb && sy >= 0 && sy < nb);
+    col[c] = (unsigned)((((sx & msk) - xs) & msk) * nb + (sy & msk)) * nb;
+    if (ISO && !in[c]) col[c] = 0;  // any slot (its column may not be in the slab)
   }
-  double2 t0[4], t1[4], t2[4];  // sums of target planes z - 1, z, z + 1
   const double2 zero = make_double2(0.0, 0.0);
-#pragma unroll
-  for (int t = 0; t < 4; ++t) t0[t] = t1[t] = t2[t] = zero;
-  auto cmac = [](double2& s, double2 k, double2 v) {
-    s.x = fma(k.x, v.x, s.x);
-    s.x = fma(-k.y, v.y, s.x);
-    s.y = fma(k.x, v.y, s.y);
-    s.y = fma(k.y, v.x, s.y);
-  };
-  for (int z = z0 - 1; z <= z0 + nz; ++z) {
-    double2 v[16];
+  auto load_plane = [&](double2 (&v)[16], int z) {
     const bool zin = !ISO || (z >= 0 && z < nb);
 #pragma unroll
-    for (int c = 0; c < 16; ++c) v[c] = zin && col[c] >= 0 ? src[(col[c] + (z & msk)) * 64] : zero;
-    // kernel values are read here every time, not kept in registers
-    asm volatile("" ::: "memory");
+    for (int c = 0; c < 16; ++c) {
+      v[c] = src[(int64_t)(col[c] + (unsigned)(z & msk)) * 64];
+      if (ISO && !(zin && in[c])) v[c] = zero;
+    }
+  };
+  struct Sums {
+    double2 t[4];
+  };
+  // source plane z, the neighbour ez - 1 of target plane z + 1 - ez
+  auto plane = [&](const double2 (&v)[16], Sums& s, int ez) {
 #pragma unroll
     for (int ex = 0; ex < 3; ++ex)
 #pragma unroll
       for (int ey = 0; ey < 3; ++ey) {
-        // source z is neighbour ez - 1 of target z + 1 - ez
-        const double2 k0 = kk[(ex * 9 + ey * 3) * 64], k1 = kk[(ex * 9 + ey * 3 + 1) * 64],
-                      k2 = kk[(ex * 9 + ey * 3 + 2) * 64];
+        // kernel values are read here every time, not kept in registers
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        const double2 k = kk[(ex * 9 + ey * 3 + ez) * 64];
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-          const double2 s = v[(t / 2 + ex) * 4 + t % 2 + ey];
-          cmac(t2[t], k0, s);
-          cmac(t1[t], k1, s);
-          cmac(t0[t], k2, s);
+          const double2 q = v[(t / 2 + ex) * 4 + t % 2 + ey];
+          s.t[t].x = fma(k.x, q.x, s.t[t].x);
+          s.t[t].x = fma(-k.y, q.y, s.t[t].x);
+          s.t[t].y = fma(k.x, q.y, s.t[t].y);
+          s.t[t].y = fma(k.y, q.x, s.t[t].y);
         }
       }
-    if (z > z0) {
+  };
+  double2 v[16];
+  Sums s0, s1, s2;
+  // source plane z; `lo`, `mid`, `up` are the sums of the target planes z - 1, z, z + 1
+  auto step = [&](int z, Sums& lo, Sums& mid, Sums& up, bool do_lo, bool do_mid, bool do_up) {
+    load_plane(v, z);
+    if (do_lo) {
+      plane(v, lo, 2);
 #pragma unroll
       for (int t = 0; t < 4; ++t)
-        dst[((int64_t)((bx0 - x0 + t / 2) * nb + by0 + t % 2) * nb + z - 1) * 64] = t0[t];
+        dst[((int64_t)((bx0 - x0 + t / 2) * nb + by0 + t % 2) * nb + z - 1) * 64] = lo.t[t];
     }
+    if (do_mid) plane(v, mid, 1);
+    if (do_up) {
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      t0[t] = t1[t];
-      t1[t] = t2[t];
-      t2[t] = zero;
+      for (int t = 0; t < 4; ++t) up.t[t] = zero;
+      plane(v, up, 0);
     }
+  };
+  const int zl = z0 + nz - 1;
+  step(z0 - 1, s1, s2, s0, false, false, true);
+  step(z0, s2, s0, s1, false, true, true);
+#pragma unroll 1
+  for (int z = z0 + 1; z < zl; z += 2) {  // nz is even
+    step(z, s0, s1, s2, true, true, true);
+    step(z + 1, s1, s2, s0, true, true, true);
+    s1 = s0;
+    s0 = s2;
   }
+  step(zl, s0, s1, s2, true, true, false);
+  step(zl + 1, s1, s2, s0, true, false, false);
 }
 
 // Kernel transforms, neighbour e = blockIdx.y of K_e[m] = tab[m - s e] (tab
@@ -427,15 +457,16 @@ hipError_t run(const Near64* f, const T* rho, T* const* out, int nout, int isola
     const int64_t nls = (int64_t)ns * nb * nb, nlt = (int64_t)nx * nb * nb;
     // whole pencils unless that leaves the SIMDs (4 a CU) idle: a segment reads
     // two more planes than it writes
-    unsigned blocks = (unsigned)((nchunk + 7) / 8 * 8) * (unsigned)(nx / 2) * (unsigned)(nb / 2);
+    unsigned waves = (unsigned)((nchunk + 7) / 8 * 8) * (unsigned)(nx / 2) * (unsigned)(nb / 2);
     int nz = nb;
-    for (; nz > 2 && blocks < 2048; nz /= 2) blocks *= 2;
+    for (; nz > 2 && waves < 2048; nz /= 2) waves *= 2;
+    const unsigned blocks = waves / kMacWaves;
     for (int t = 0; t < nout && e == hipSuccess; ++t) {
       if (isolated)
-        k_mac64<true><<<blocks, 64, 0, st>>>(f->rhat, f->khat[t], nb, nchunk, x0, nx,
+        k_mac64<true><<<blocks, 64 * kMacWaves, 0, st>>>(f->rhat, f->khat[t], nb, nchunk, x0, nx,
                                              xs & (nb - 1), nz, nls, nlt, f->yhat);
       else
-        k_mac64<false><<<blocks, 64, 0, st>>>(f->rhat, f->khat[t], nb, nchunk, x0, nx,
+        k_mac64<false><<<blocks, 64 * kMacWaves, 0, st>>>(f->rhat, f->khat[t], nb, nchunk, x0, nx,
                                              xs & (nb - 1), nz, nls, nlt, f->yhat);
       e = hipGetLastError();
       if (e == hipSuccess) e = inv_any(f, out[t], x0, nx, st);

@@ -370,7 +370,7 @@ pfmm_status refresh_near_fft(pfmm_plan_s* pl) {
 // The FP64 near zone of a plan whose options ask for it (direct, or FP64
 // precision whatever PFMM_OPT_NEAR says) at the leaf edges it serves: made or
 // released, its kernels transformed.  Without the memory for it the plan keeps
-// the block-Toeplitz sum.  Split precision takes it too: at 256^3, s = 16, 1.44
+// the block-Toeplitz sum.  Split precision takes it too: at 256^3, s = 16, 1.21
 // ms in FP64 against 7.6-8.1 ms for the bf16 products on the matrix cores.
 pfmm_status refresh_near64(pfmm_plan_s* pl) {
   const bool want = pl->prec == PFMM_PREC_FP64 || !pl->near_fft;
