@@ -383,6 +383,22 @@ hipError_t m2l_spectral_level(const M2LSpectral* f, int l, const void* Ml, int m
                               int accumulate, int isolated, int cols32, hipStream_t st,
                               KernelTimer* kt = nullptr);
 
+// The same in steps, fused with the tree's transfers (gridlets of p = 3 .. 8,
+// FP64 gridlets at the level; m2l_fused.hip): the masses of level l and their
+// node transforms from the children's masses, or from the mesh (leaves of 4, 8
+// or 16 cells; rho64: an FP64 mesh); the sums per frequency; the inverse
+// transforms, added to Pl (accumulate), and what follows from the result: the
+// children's local values, or the mesh's (added to phi).
+bool fused_zones(const M2LSpectral* f, int p);
+hipError_t fused_m2m(const M2LSpectral* f, int l, const void* Mc, int c64, double* Mp, Weights T, hipStream_t st);
+hipError_t fused_p2m(const M2LSpectral* f, int l, const void* rho, int rho64, double* M, Weights A, int N, int s,
+                     double h3, hipStream_t st);
+hipError_t m2l_spectral_sums(const M2LSpectral* f, int l, int isolated, hipStream_t st);
+hipError_t fused_l2l(const M2LSpectral* f, int l, double* Pl, int accumulate, void* Pc, int c64, Weights T,
+                     hipStream_t st);
+hipError_t fused_l2p(const M2LSpectral* f, int l, double* Pl, int accumulate, void* phi, int phi64, Weights A,
+                     int N, int s, hipStream_t st);
+
 // FP64 -> FP32 copy of n elements.
 hipError_t launch_cast_d2f(const double* src, float* dst, int64_t n, hipStream_t st);
 

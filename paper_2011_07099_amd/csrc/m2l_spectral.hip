@@ -22,175 +22,39 @@
 // node's transform writes (and its inverse reads) 128-byte runs, and the 8
 // frequencies of a chunk, whose stencil workgroups run on one XCD, share
 // every line of it.
-#include "dft64.h"
-#include "internal.h"
+#include "spectral.h"
 
 #include <algorithm>
-#include <type_traits>
-#include <vector>
 
 namespace pfmm {
-
-struct M2LSpectral {
-  int L = 0, p = 0;
-  int64_t F = 0;                 // (2p)^2 (p + 1) frequencies per node
-  double2* spec = nullptr;       // [F][nodes] of the level being summed
-  double2* out = nullptr;        // [F][nodes]
-  std::vector<double2*> khatT;   // per level: [F][kKT] kernel values, offsets of [-3, 3]^3 innermost
-  float2* khatT32 = nullptr;     // the leaf level's khatT in FP32 (the FP32 16^3 stencil)
-  int f32 = 0;                   // the 16^3 level's stencil in FP32 with FP64 column totals
-  void* mem = nullptr;           // the one allocation that holds the arrays above
-};
 
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kFC = 8;    // frequencies per chunk of a spectrum
-constexpr int kKT = 344;  // kernel values per frequency in khatT (343 offsets, padded)
-
 inline unsigned nblk(int64_t n) { return (unsigned)((n + kThreads - 1) / kThreads); }
-
-template <int P>
-constexpr int node_threads() { return (P * (P + 1) + 63) / 64 * 64; }
-
-// Node of block g: the 8 XCDs (blocks dealt round robin) take contiguous runs
-// of nodes, so that the [frequency][node] writes of neighbouring nodes meet in
-// one L2.
-__device__ __forceinline__ int64_t xcd_node(int64_t g, int64_t nn) { return (g & 7) * (nn >> 3) + (g >> 3); }
-
-// Spectrum element (frequency f, node) of a level with nn nodes.
-__device__ __forceinline__ int64_t sidx(int f, int64_t node, int64_t nn) {
-  return ((int64_t)(f / kFC) * nn + node) * kFC + f % kFC;
-}
-
-// Forward transform of one node's p^3 gridlet (on the 2p cyclic grid, zero
-// beyond p) to its half spectrum; frequency order
-// ((kx * 2 + ky % 2) * p + ky / 2) * (p + 1) + kz.
-// Spectra are stored as TS: double2, or float2 for the 16^3 leaf level
-// summed in FP32 columns (half the bytes; its stencil rounds them to FP32
-// anyway).
-__device__ __forceinline__ double2 as_d2(double2 v) { return v; }
-__device__ __forceinline__ double2 as_d2(float2 v) { return make_double2(v.x, v.y); }
-template <class TS> __device__ __forceinline__ TS from_d2(double2 v);
-template <> __device__ __forceinline__ double2 from_d2<double2>(double2 v) { return v; }
-template <> __device__ __forceinline__ float2 from_d2<float2>(double2 v) {
-  return make_float2((float)v.x, (float)v.y);
-}
 
 template <int P, class TIN, class TS = double2>
 __global__ void __launch_bounds__(node_threads<P>()) k_node_fwd(const TIN* __restrict__ Ml, int64_t nn,
                                                                 TS* __restrict__ spec) {
-  constexpr int M = 2 * P, H = P + 1, NT = node_threads<P>();
-  __shared__ double2 A1[P * P * H];
-  __shared__ double2 A2[P * P * H];
+  __shared__ double2 A1[P * P * (P + 1)];
+  __shared__ double2 A2[P * P * (P + 1)];
   const int64_t node = xcd_node(blockIdx.x, nn);
   const TIN* src = Ml + node * (P * P * P);
-  for (int r = threadIdx.x; r < P * P; r += NT) {
-    double2 e[P], o[P];
-#pragma unroll
-    for (int z = 0; z < P; ++z) {
-      e[z] = make_double2((double)src[r * P + z], 0.0);
-      o[z] = dtwiddle<M, false>(e[z], z);
-    }
-    ddft<P, false>(e);
-    ddft<P, false>(o);
-    double2* row = A1 + r * H;
-#pragma unroll
-    for (int k = 0; k < H; ++k) row[k] = (k & 1) ? o[k >> 1] : e[k >> 1];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    for (int r = threadIdx.x; r < P * H; r += NT) {
-      const int x = r / H, kz = r % H;
-      double2 u[P];
-#pragma unroll
-      for (int y = 0; y < P; ++y) {
-        u[y] = A1[(x * P + y) * H + kz];
-        if (h) u[y] = dtwiddle<M, false>(u[y], y);
-      }
-      ddft<P, false>(u);
-#pragma unroll
-      for (int m = 0; m < P; ++m) A2[(x * P + m) * H + kz] = u[m];
-    }
-    __syncthreads();
-    for (int r = threadIdx.x; r < P * H; r += NT) {
-      const int m = r / H, kz = r % H;
-      double2 e[P], o[P];
-#pragma unroll
-      for (int x = 0; x < P; ++x) {
-        e[x] = A2[(x * P + m) * H + kz];
-        o[x] = dtwiddle<M, false>(e[x], x);
-      }
-      ddft<P, false>(e);
-      ddft<P, false>(o);
-#pragma unroll
-      for (int j = 0; j < P; ++j) {
-        spec[sidx((4 * j + h) * P * H + r, node, nn)] = from_d2<TS>(e[j]);
-        spec[sidx((4 * j + 2 + h) * P * H + r, node, nn)] = from_d2<TS>(o[j]);
-      }
-    }
-    __syncthreads();
-  }
+  node_fwd_block<P, node_threads<P>()>([&](int i) { return (double)src[i]; }, node, nn, spec, A1, A2);
 }
 
-// Inverse of k_node_fwd at the p^3 gridlet points, added to (or written into)
-// the node's potentials; unnormalised (the kernel spectra carry 1 / (2p)^3).
+// Added to (or written into) the node's potentials.
 template <int P, class TOUT, class TS = double2>
 __global__ void __launch_bounds__(node_threads<P>()) k_node_inv(const TS* __restrict__ spec,
                                                                 int64_t nn, int accumulate,
                                                                 TOUT* __restrict__ Pl) {
-  constexpr int M = 2 * P, H = P + 1, NT = node_threads<P>();
-  __shared__ double2 B1[P * P * H];
-  __shared__ double2 B2[P * P * H];
+  __shared__ double2 B1[P * P * (P + 1)];
+  __shared__ double2 B2[P * P * (P + 1)];
   const int64_t node = xcd_node(blockIdx.x, nn);
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    for (int r = threadIdx.x; r < P * H; r += NT) {
-      const int m = r / H, kz = r % H;
-      double2 e[P], o[P];
-#pragma unroll
-      for (int j = 0; j < P; ++j) {
-        e[j] = as_d2(spec[sidx((4 * j + h) * P * H + r, node, nn)]);
-        o[j] = as_d2(spec[sidx((4 * j + 2 + h) * P * H + r, node, nn)]);
-      }
-      ddft<P, true>(e);
-      ddft<P, true>(o);
-#pragma unroll
-      for (int x = 0; x < P; ++x) B1[(x * P + m) * H + kz] = dadd(e[x], dtwiddle<M, true>(o[x], x));
-    }
-    __syncthreads();
-    for (int r = threadIdx.x; r < P * H; r += NT) {
-      const int x = r / H, kz = r % H;
-      double2 v[P];
-#pragma unroll
-      for (int m = 0; m < P; ++m) v[m] = B1[(x * P + m) * H + kz];
-      ddft<P, true>(v);
-#pragma unroll
-      for (int y = 0; y < P; ++y) {
-        double2& d = B2[(x * P + y) * H + kz];
-        d = h ? dadd(d, dtwiddle<M, true>(v[y], y)) : v[y];
-      }
-    }
-    __syncthreads();
-  }
   TOUT* dst = Pl + node * (P * P * P);
-  for (int r = threadIdx.x; r < P * P; r += NT) {
-    double2 u[H];
-#pragma unroll
-    for (int k = 0; k < H; ++k) u[k] = B2[r * H + k];
-#pragma unroll
-    for (int z = 0; z < P; ++z) {
-      double b = 0.0;
-#pragma unroll
-      for (int k = 1; k < P; ++k) {
-        const double2 w = twd<M>(k * z);
-        b += u[k].x * w.x - u[k].y * w.y;
-      }
-      const double v = u[0].x + ((z & 1) ? -u[P].x : u[P].x) + 2.0 * b;
-      dst[r * P + z] = accumulate ? (TOUT)((double)dst[r * P + z] + v) : (TOUT)v;
-    }
-  }
+  node_inv_block<P, node_threads<P>()>(spec, node, nn, B1, B2, [&](int i, double v) {
+    dst[i] = accumulate ? (TOUT)((double)dst[i] + v) : (TOUT)v;
+  });
 }
 
 // (re, im) += k s, one complex multiply-add as four FMAs
@@ -635,7 +499,7 @@ hipError_t khat_levels(const M2LSpectral* f, const std::vector<double*>& tab64, 
   for (int l = 2; l <= f->L; ++l) {
     lv.tab[l - 2] = tab64[l];
     lv.khat[l - 2] = f->khatT[l];
-    lv.low[l - 2] = f->spec + (l - 2) * f->F * kKT;  // before the level's spectra
+    lv.low[l - 2] = f->out + (l - 2) * f->F * kKT;  // before any spectra
   }
   const unsigned nl = f->L - 1;
   k_khat_z<P><<<dim3(M * M, nb, nl), kKB, 0, st>>>(lv);
@@ -655,7 +519,7 @@ void zone_oct_as(const M2LSpectral* f, int l, int n, int isolated, int nchunk, h
   const int hn = n / 2, tiles = (hn / HX) * (hn / HY) * (hn / HZ);
   // the chunks rounded up to a multiple of 8, times their frequencies, per tile
   const unsigned grid = (unsigned)((nchunk + 7) / 8 * 8 * kFC) * (unsigned)tiles;
-  k_zone_oct<HX, HY, HZ, G, WRAP><<<grid, HX * HY * HZ * 4 / G, 0, st>>>(f->spec, f->khatT[l], n,
+  k_zone_oct<HX, HY, HZ, G, WRAP><<<grid, HX * HY * HZ * 4 / G, 0, st>>>(f->spec[l], f->khatT[l], n,
                                                                          isolated, nchunk, f->out);
 }
 
@@ -672,6 +536,23 @@ void zone_oct(const M2LSpectral* f, int l, int n, int isolated, int nchunk, hipS
     zone_oct_as<4, 4, 8, 2, false>(f, l, n, isolated, nchunk, st);
 }
 
+// The zone sums of a level from its spectra (FP64) into f->out.
+void zone_sums(const M2LSpectral* f, int l, int isolated, hipStream_t st) {
+  const int n = 1 << l;
+  const int nchunk = (int)(f->F / kFC);
+  if (n == 16 && !isolated) {  // the whole level per frequency, eight targets per lane
+    const unsigned cgrid = (unsigned)((nchunk + 7) / 8 * 64);  // chunks rounded up to 8, times 8
+    k_zone_level_y<8, 8><<<cgrid, 512, 0, st>>>(f->spec[l], f->khatT[l], f->F, nchunk, f->out);
+  } else if (n == 4) {
+    if (isolated)
+      k_zone_l2<true><<<(unsigned)(f->F / 4), 256, 0, st>>>(f->spec[l], f->khatT[l], f->out);
+    else
+      k_zone_l2<false><<<(unsigned)(f->F / 4), 256, 0, st>>>(f->spec[l], f->khatT[l], f->out);
+  } else {
+    zone_oct(f, l, n, isolated, nchunk, st);
+  }
+}
+
 template <int P>
 hipError_t run_level(const M2LSpectral* f, int l, const void* Ml, int m64, void* Pl, int p64,
                      int accumulate, int isolated, int cols32, hipStream_t st, KernelTimer* kt) {
@@ -680,7 +561,7 @@ hipError_t run_level(const M2LSpectral* f, int l, const void* Ml, int m64, void*
   constexpr int NT = node_threads<P>();
   // the 16^3 leaf level in FP32 columns: its spectra stored as float2
   const bool f32 = n == 16 && !isolated && cols32 && f->f32 && l == f->L;
-  float2* spec32 = reinterpret_cast<float2*>(f->spec);
+  float2* spec32 = reinterpret_cast<float2*>(f->spec[l]);
   float2* out32 = reinterpret_cast<float2*>(f->out);
   hipError_t e = tbegin(kt, st);
   if (e != hipSuccess) return e;
@@ -689,26 +570,17 @@ hipError_t run_level(const M2LSpectral* f, int l, const void* Ml, int m64, void*
   else if (f32)
     k_node_fwd<P, float, float2><<<(unsigned)nn, NT, 0, st>>>((const float*)Ml, nn, spec32);
   else if (m64)
-    k_node_fwd<P, double><<<(unsigned)nn, NT, 0, st>>>((const double*)Ml, nn, f->spec);
+    k_node_fwd<P, double><<<(unsigned)nn, NT, 0, st>>>((const double*)Ml, nn, f->spec[l]);
   else
-    k_node_fwd<P, float><<<(unsigned)nn, NT, 0, st>>>((const float*)Ml, nn, f->spec);
+    k_node_fwd<P, float><<<(unsigned)nn, NT, 0, st>>>((const float*)Ml, nn, f->spec[l]);
   e = tend(kt, st, 0, hipGetLastError());
   if (e == hipSuccess) e = tbegin(kt, st);
   if (e != hipSuccess) return e;
-  const int nchunk = (int)(f->F / kFC);
-  const unsigned cgrid = (unsigned)((nchunk + 7) / 8 * 64);  // chunks rounded up to 8, times 8
-  if (f32) {  // FP32 columns
-    k_zone_level_y<8, 8, float, float2><<<cgrid, 512, 0, st>>>(spec32, f->khatT32, f->F, nchunk, out32);
-  } else if (n == 16 && !isolated) {  // the whole level per frequency, eight targets per lane
-    k_zone_level_y<8, 8><<<cgrid, 512, 0, st>>>(f->spec, f->khatT[l], f->F, nchunk, f->out);
-  } else if (n == 4) {
-    if (isolated)
-      k_zone_l2<true><<<(unsigned)(f->F / 4), 256, 0, st>>>(f->spec, f->khatT[l], f->out);
-    else
-      k_zone_l2<false><<<(unsigned)(f->F / 4), 256, 0, st>>>(f->spec, f->khatT[l], f->out);
-  } else {
-    zone_oct(f, l, n, isolated, nchunk, st);
-  }
+  if (f32)  // FP32 columns
+    k_zone_level_y<8, 8, float, float2><<<(unsigned)((f->F / kFC + 7) / 8 * 64), 512, 0, st>>>(
+        spec32, f->khatT32, f->F, (int)(f->F / kFC), out32);
+  else
+    zone_sums(f, l, isolated, st);
   e = tend(kt, st, 1, hipGetLastError());
   if (e == hipSuccess) e = tbegin(kt, st);
   if (e != hipSuccess) return e;
@@ -725,24 +597,6 @@ hipError_t run_level(const M2LSpectral* f, int l, const void* Ml, int m64, void*
 
 }  // namespace
 
-// f(P) for the gridlet size p of 1 .. 10 as a template argument
-template <class F>
-hipError_t with_p(int p, F&& f) {
-  switch (p) {
-    case 1: return f(std::integral_constant<int, 1>());
-    case 2: return f(std::integral_constant<int, 2>());
-    case 3: return f(std::integral_constant<int, 3>());
-    case 4: return f(std::integral_constant<int, 4>());
-    case 5: return f(std::integral_constant<int, 5>());
-    case 6: return f(std::integral_constant<int, 6>());
-    case 7: return f(std::integral_constant<int, 7>());
-    case 8: return f(std::integral_constant<int, 8>());
-    case 9: return f(std::integral_constant<int, 9>());
-    case 10: return f(std::integral_constant<int, 10>());
-    default: return hipErrorInvalidValue;
-  }
-}
-
 void m2l_spectral_destroy(M2LSpectral* f) {
   if (!f) return;
   (void)hipFree(f->mem);
@@ -750,9 +604,14 @@ void m2l_spectral_destroy(M2LSpectral* f) {
 }
 
 namespace {
-// Values per frequency of the two node spectra, which also hold the low parts
-// of every level's kernels while these are transformed
-size_t spectra_per_freq(int L) { return std::max((size_t)2 << (3 * L), (size_t)(L - 1) * kKT); }
+// Values per frequency of the node spectra (every level's, and the sums of the
+// largest), which also hold the low parts of every level's kernels while these
+// are transformed
+size_t spectra_per_freq(int L) {
+  size_t n = (size_t)1 << (3 * L);
+  for (int l = 2; l <= L; ++l) n += (size_t)1 << (3 * l);
+  return std::max(n, (size_t)(L - 1) * kKT);
+}
 }  // namespace
 
 size_t m2l_spectral_bytes(int L, int p) {
@@ -780,8 +639,13 @@ hipError_t m2l_spectral_create(int L, int p, M2LSpectral** out) {
     at += n;
     return a;
   };
-  f->spec = take(f->F * (int64_t)spectra_per_freq(L));
-  f->out = f->spec + (f->F << (3 * L));
+  f->out = take(f->F * (int64_t)spectra_per_freq(L));
+  f->spec.assign(L + 1, nullptr);
+  double2* sp = f->out + (f->F << (3 * L));
+  for (int l = L; l >= 2; --l) {
+    f->spec[l] = sp;
+    sp += f->F << (3 * l);
+  }
   f->khatT.assign(L + 1, nullptr);
   for (int l = 2; l <= L; ++l) f->khatT[l] = take(f->F * kKT);
   if (L == 4) f->khatT32 = reinterpret_cast<float2*>(at);
@@ -805,7 +669,7 @@ hipError_t m2l_spectral_set_f32(M2LSpectral* f, int on, hipStream_t st) {
 }
 
 hipError_t m2l_spectral_tables(M2LSpectral* f, const std::vector<double*>& tab64, hipStream_t st) {
-  hipError_t e = with_p(f->p, [&](auto P) { return khat_levels<decltype(P)::value>(f, tab64, st); });
+  hipError_t e = with_p<1, 10>(f->p, [&](auto P) { return khat_levels<decltype(P)::value>(f, tab64, st); });
   if (e == hipSuccess) e = khat_f32(f, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   return e;
@@ -815,9 +679,15 @@ hipError_t m2l_spectral_level(const M2LSpectral* f, int l, const void* Ml, int m
                               int accumulate, int isolated, int cols32, hipStream_t st,
                               KernelTimer* kt) {
   if (l < 2 || l > f->L) return hipErrorInvalidValue;
-  return with_p(f->p, [&](auto P) {
+  return with_p<1, 10>(f->p, [&](auto P) {
     return run_level<decltype(P)::value>(f, l, Ml, m64, Pl, p64, accumulate, isolated, cols32, st, kt);
   });
+}
+
+hipError_t m2l_spectral_sums(const M2LSpectral* f, int l, int isolated, hipStream_t st) {
+  if (l < 2 || l > f->L) return hipErrorInvalidValue;
+  zone_sums(f, l, isolated, st);
+  return hipGetLastError();
 }
 
 }  // namespace pfmm

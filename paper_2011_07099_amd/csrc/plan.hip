@@ -412,6 +412,17 @@ bool zones_by_transforms(const pfmm_plan_s* pl, int l) {
   return pl->mspec && l <= pl->zone_top &&
          (pl->prec != PFMM_PREC_BF16X3 || level64(pl, l));
 }
+// Whether the zones of level l run with the transfers around them fused into
+// their node transforms: FP64 gridlets (p = 3 .. 8) and FP64 sums by transforms.
+bool zones_fused(const pfmm_plan_s* pl, int l) {
+  if (pl->m2l_fft || !level64(pl, l) || !fused_zones(pl->mspec, pl->p)) return false;
+  if (!pl->m2l_spectral) return zones_by_transforms(pl, l);
+  return !(pl->zones_f32 && l == 4 && l == pl->L && !pl->isolated);  // FP32 columns
+}
+// The same for the leaf level, whose transfers are the mesh's.
+bool leaf_fused(const pfmm_plan_s* pl) {
+  return zones_fused(pl, pl->L) && (pl->s == 4 || pl->s == 8 || pl->s == 16);
+}
 pfmm_status create_zones(pfmm_plan_s* pl) {
   if (pl->p < kZoneMinP) return PFMM_OK;
   int top = pl->L;
@@ -1267,12 +1278,18 @@ pfmm_status solve_impl(pfmm_plan_s* pl, const void* rho_in, void* phi_out, void*
   if (e == hipSuccess && overlap && !fold) e = hipEventRecord(pl->ev_join, pl->side);
   if (e != hipSuccess) return hip_fail(e, "near zone");
 
-  // upward pass
+  // upward pass; where the zones take per-node transforms of FP64 gridlets, the
+  // transfers around them are part of those (timed solves run every step alone)
+  const bool fuse_leaf = !tm.on && !fold && leaf_fused(pl);
+  auto fused = [&](int l) { return !tm.on && (l < L ? zones_fused(pl, l) : fuse_leaf); };
   if (fold) {
     if (overlap) {
       e = hipStreamWaitEvent(st, pl->ev_mass, 0);
       if (e != hipSuccess) return hip_fail(e, "leaf masses");
     }
+  } else if (fuse_leaf) {
+    e = fused_p2m(pl->mspec, L, rho_in, io64, (double*)pl->M[L], A, N, s, h3, st);
+    if (e != hipSuccess) return hip_fail(e, "P2M");
   } else {
     e = timed(PFMM_STAGE_P2M, 0, st, [&] {
       return io64 ? launch_p2m_f64in(static_cast<const double*>(rho_in), pl->M[L], A, N, s, p, h3, st)
@@ -1281,6 +1298,11 @@ pfmm_status solve_impl(pfmm_plan_s* pl, const void* rho_in, void* phi_out, void*
     if (e != hipSuccess) return hip_fail(e, "P2M");
   }
   for (int l = L - 1; l >= 2; --l) {
+    if (fused(l)) {
+      e = fused_m2m(pl->mspec, l, pl->M[l + 1], is64(l + 1), (double*)pl->M[l], T, st);
+      if (e != hipSuccess) return hip_fail(e, "M2M");
+      continue;
+    }
     e = timed(PFMM_STAGE_M2M, l, st, [&] {
       return launch_m2m(pl->M[l + 1], is64(l + 1), pl->M[l], is64(l), T, 1 << l, p, st);
     });
@@ -1310,13 +1332,27 @@ pfmm_status solve_impl(pfmm_plan_s* pl, const void* rho_in, void* phi_out, void*
     }
     return timed(PFMM_STAGE_M2L, l, st, [&] { return m2l(ta, l); });
   };
-  e = m2l_timed(a, 2);
+  // a fused level's sums, and its local values with their expansion to the next
+  auto fused_zone = [&](int l) -> hipError_t {
+    hipError_t r = m2l_spectral_sums(pl->mspec, l, pl->isolated, st);
+    if (r == hipSuccess && l < L)
+      r = fused_l2l(pl->mspec, l, (double*)pl->P[l], l > 2, pl->P[l + 1], is64(l + 1), T, st);
+    return r;
+  };
+  e = fused(2) ? fused_zone(2) : m2l_timed(a, 2);
   if (e != hipSuccess) return hip_fail(e, "M2L level 2");
   for (int l = 3; l <= L; ++l) {
-    e = timed(PFMM_STAGE_L2L, l, st, [&] {
-      return launch_l2l(pl->P[l - 1], is64(l - 1), pl->P[l], is64(l), T, 1 << (l - 1), p, st);
-    });
-    if (e != hipSuccess) return hip_fail(e, "L2L");
+    if (!fused(l - 1)) {
+      e = timed(PFMM_STAGE_L2L, l, st, [&] {
+        return launch_l2l(pl->P[l - 1], is64(l - 1), pl->P[l], is64(l), T, 1 << (l - 1), p, st);
+      });
+      if (e != hipSuccess) return hip_fail(e, "L2L");
+    }
+    if (fused(l)) {
+      e = fused_zone(l);
+      if (e != hipSuccess) return hip_fail(e, "M2L");
+      continue;
+    }
     a.n = 1 << l;
     a.m = 2;
     a.noff = 189;
@@ -1345,7 +1381,10 @@ pfmm_status solve_impl(pfmm_plan_s* pl, const void* rho_in, void* phi_out, void*
     e = hipStreamWaitEvent(st, pl->ev_join, 0);
     if (e != hipSuccess) return hip_fail(e, "join");
   }
-  if (!fold) {
+  if (fuse_leaf) {
+    e = fused_l2p(pl->mspec, L, (double*)pl->P[L], L > 2, phi_out, io64, A, N, s, st);
+    if (e != hipSuccess) return hip_fail(e, "L2P");
+  } else if (!fold) {
     e = timed(PFMM_STAGE_L2P, 0, st, [&] {
       return io64 ? launch_l2p_f64out(pl->P[L], static_cast<double*>(phi_out), A, N, s, p, st, 1)
                   : launch_l2p(pl->P[L], is64(L), phi, A, N, s, p, st, 1);
@@ -1825,22 +1864,35 @@ hipError_t batch_chain_solve(pfmm_batch_s* b, size_t f, hipStream_t st) {
   const Weights T = wts(pl->dT, pl->dT64);
   float* out[1] = {b->phi[f]};
   hipError_t e = near_fft_run(pl->nfft, b->rho[f], out, 1, 0, st);
+  // as a single solve: fused transfers around the FP64 levels' node transforms
+  const Weights A = wts(pl->dA, pl->dA64);
+  const int L = pl->L;
+  const double h3 = 1.0 / ((double)pl->N * pl->N * pl->N);
+  const bool fuse_leaf = leaf_fused(pl);
+  auto fused = [&](int l) { return l < L ? zones_fused(pl, l) : fuse_leaf; };
   if (e == hipSuccess)
-    e = launch_p2m(b->rho[f], pl->M[pl->L], level64(pl, pl->L), wts(pl->dA, pl->dA64), pl->N, pl->s,
-                   pl->p, 1.0 / ((double)pl->N * pl->N * pl->N), st);
-  for (int l = pl->L - 1; l >= 2 && e == hipSuccess; --l)
-    e = launch_m2m(pl->M[l + 1], level64(pl, l + 1), pl->M[l], level64(pl, l), T, 1 << l, pl->p, st);
-  for (int l = 2; l <= pl->L && e == hipSuccess; ++l) {
-    if (l > 2)
+    e = fuse_leaf ? fused_p2m(pl->mspec, L, b->rho[f], 0, (double*)pl->M[L], A, pl->N, pl->s, h3, st)
+                  : launch_p2m(b->rho[f], pl->M[L], level64(pl, L), A, pl->N, pl->s, pl->p, h3, st);
+  for (int l = L - 1; l >= 2 && e == hipSuccess; --l)
+    e = fused(l) ? fused_m2m(pl->mspec, l, pl->M[l + 1], level64(pl, l + 1), (double*)pl->M[l], T, st)
+                 : launch_m2m(pl->M[l + 1], level64(pl, l + 1), pl->M[l], level64(pl, l), T, 1 << l, pl->p, st);
+  for (int l = 2; l <= L && e == hipSuccess; ++l) {
+    if (l > 2 && !fused(l - 1))
       e = launch_l2l(pl->P[l - 1], level64(pl, l - 1), pl->P[l], level64(pl, l), T, 1 << (l - 1),
                      pl->p, st);
-    if (e == hipSuccess)
+    if (e != hipSuccess) break;
+    if (!fused(l)) {
       e = m2l_spectral_level(pl->mspec, l, pl->M[l], level64(pl, l), pl->P[l], level64(pl, l), l > 2, 0,
                              pl->zones_f32, st);
+      continue;
+    }
+    e = m2l_spectral_sums(pl->mspec, l, 0, st);
+    if (e == hipSuccess && l < L)
+      e = fused_l2l(pl->mspec, l, (double*)pl->P[l], l > 2, pl->P[l + 1], level64(pl, l + 1), T, st);
   }
   if (e == hipSuccess)
-    e = launch_l2p(pl->P[pl->L], level64(pl, pl->L), b->phi[f], wts(pl->dA, pl->dA64), pl->N, pl->s,
-                   pl->p, st, 1);
+    e = fuse_leaf ? fused_l2p(pl->mspec, L, (double*)pl->P[L], L > 2, b->phi[f], 0, A, pl->N, pl->s, st)
+                  : launch_l2p(pl->P[L], level64(pl, L), b->phi[f], A, pl->N, pl->s, pl->p, st, 1);
   return e;
 }
 

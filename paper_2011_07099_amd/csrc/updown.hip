@@ -17,6 +17,7 @@
 // FP64: the interpolation of Eq. 7 extrapolates past the parent's outermost
 // gridlet nodes, so rounding noise of a parent's field is amplified in its
 // children); each kernel computes in the wider of its operand types.
+#include "columns.h"
 #include "internal.h"
 
 #include <type_traits>
@@ -25,10 +26,6 @@ namespace pfmm {
 namespace {
 
 constexpr int kThreads = 256;
-
-template <class W> __device__ inline const W* wsel(Weights w);
-template <> __device__ inline const float* wsel<float>(Weights w) { return w.f; }
-template <> __device__ inline const double* wsel<double>(Weights w) { return w.d; }
 
 // S, P: leaf width and gridlet size fixed at compile time (0: the arguments),
 // so that the index arithmetic folds and the contraction loops unroll.
@@ -213,290 +210,40 @@ __global__ __launch_bounds__(kThreads) void k_l2p(const TI* __restrict__ P,
   }
 }
 
-// M2M and L2L, the eight children in one pass per axis.  The child operators
-// are T_o = T_ox (x) T_oy (x) T_oz with two 1D matrices T_0, T_1, so along each
-// axis the two children of a pair share the pass: M2M contracts x over (ox, kx)
-// for the four (oy, oz), then y over (oy, ky) for the two oz, then z over (oz,
-// kz) (14 p^4 multiply-adds against 24 p^4 child by child); L2L expands x into
-// the two ox, y into four (ox, oy), z into the eight children.
-//
-// A lane takes whole columns (the values along the contracted axis in
-// registers, from memory in the first pass), a wave the outputs whose weights
-// it reads as scalars: an LDS value is read once for several outputs and no
-// weight is read from LDS.  Reading both factors of every product from LDS was
-// the bound, and child by child (p other than 4 and 8) the barriers.  Measured
-// before / after: 64 parents in FP64 M2M 33 / 5 us at p = 7, 17 / 4.5 at p = 6, 11 /
-// 5.5 at p = 8, L2L 23 / 4.0, 13 / 3.9 and 7.5 / 5.5; 4096 parents of FP32 children, p =
-// 8, M2M 207 / 27 us.
-// LDS rows are padded to an odd number of values.
 template <class TI, class TO, class W, int P>
 __global__ __launch_bounds__(kThreads) void k_m2m(const TI* __restrict__ Mc, TO* __restrict__ Mp,
                                                    Weights Tw, int np) {
-  constexpr int P2 = P * P, P3 = P2 * P, Q = P | 1;
-  __shared__ W w[4 * P2 * Q];  // [oy][oz][ax][ky][kz]
-  __shared__ W v[2 * P2 * Q];  // [oz][ax][ay][kz]
-  const W* __restrict__ T = wsel<W>(Tw);  // [o][a][k]
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int B = blockIdx.x;
-  const int Bx = B / (np * np), By = (B / np) % np, Bz = B % np;
-  const int nc = 2 * np;
-  for (int c = lane; c < P2; c += 64) {  // (ky, kz) of the wave's (oy, oz)
-    W in[2 * P];
-#pragma unroll
-    for (int ox = 0; ox < 2; ++ox) {
-      const size_t child = ((size_t)(2 * Bx + ox) * nc + (2 * By + (wave >> 1))) * nc + (2 * Bz + (wave & 1));
-#pragma unroll
-      for (int kx = 0; kx < P; ++kx) in[ox * P + kx] = (W)Mc[child * P3 + kx * P2 + c];
-    }
-#pragma unroll
-    for (int ax = 0; ax < P; ++ax) {
-      W acc = 0;
-#pragma unroll
-      for (int k = 0; k < 2 * P; ++k) acc += T[((k / P) * P + ax) * P + k % P] * in[k];
-      w[((wave * P + ax) * P + c / P) * Q + c % P] = acc;
-    }
-  }
-  __syncthreads();
-  for (int c = lane; c < P2; c += 64) {  // (ax, kz) of oz = wave % 2, every other ay
-    const int oz = wave & 1, ax = c / P, kz = c % P;
-    W in[2 * P];
-#pragma unroll
-    for (int k = 0; k < 2 * P; ++k) in[k] = w[((((k / P) * 2 + oz) * P + ax) * P + k % P) * Q + kz];
-#pragma unroll
-    for (int i = 0; i < (P + 1) / 2; ++i) {
-      const int ay = 2 * i + (wave >> 1);
-      if (ay >= P) break;
-      W acc = 0;
-#pragma unroll
-      for (int k = 0; k < 2 * P; ++k) acc += T[((k / P) * P + ay) * P + k % P] * in[k];
-      v[((oz * P + ax) * P + ay) * Q + kz] = acc;
-    }
-  }
-  __syncthreads();
-  for (int c = lane; c < P2; c += 64) {  // (ax, ay), every fourth az
-    W in[2 * P];
-#pragma unroll
-    for (int k = 0; k < 2 * P; ++k) in[k] = v[((k / P) * P2 + c) * Q + k % P];
-#pragma unroll
-    for (int i = 0; i < (P + 3) / 4; ++i) {
-      const int az = 4 * i + wave;
-      if (az >= P) break;
-      W acc = 0;
-#pragma unroll
-      for (int k = 0; k < 2 * P; ++k) acc += T[((k / P) * P + az) * P + k % P] * in[k];
-      Mp[(size_t)B * P3 + c * P + az] = (TO)acc;
-    }
-  }
+  __shared__ W lds[pair_words<P>()];
+  TO* dst = Mp + (size_t)blockIdx.x * (P * P * P);
+  m2m_block<TI, W, P>(Mc, wsel<W>(Tw), np, blockIdx.x, lds, [&](int i, W v) { dst[i] = (TO)v; });
 }
 
 template <class TI, class TO, class W, int P>
 __global__ __launch_bounds__(kThreads) void k_l2l(const TI* __restrict__ Pp, TO* __restrict__ Pc,
                                                    Weights Tw, int np, int accumulate) {
-  constexpr int P2 = P * P, P3 = P2 * P, Q = P | 1;
-  __shared__ W w[2 * P2 * Q];  // [ox][bx][ay][az]
-  __shared__ W v[4 * P2 * Q];  // [ox][oy][bx][by][az]
-  const W* __restrict__ T = wsel<W>(Tw);  // [o][a][b]: child node b from parent node a
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int B = blockIdx.x;
-  const int Bx = B / (np * np), By = (B / np) % np, Bz = B % np;
-  const int nc = 2 * np;
-  for (int c = lane; c < P2; c += 64) {  // (ay, az) of ox = wave % 2, every other bx
-    const int ox = wave & 1;
-    W in[P];
-#pragma unroll
-    for (int a = 0; a < P; ++a) in[a] = (W)Pp[(size_t)B * P3 + a * P2 + c];
-#pragma unroll
-    for (int i = 0; i < (P + 1) / 2; ++i) {
-      const int bx = 2 * i + (wave >> 1);
-      if (bx >= P) break;
-      W acc = 0;
-#pragma unroll
-      for (int a = 0; a < P; ++a) acc += T[(ox * P + a) * P + bx] * in[a];
-      w[((ox * P + bx) * P + c / P) * Q + c % P] = acc;
-    }
-  }
-  __syncthreads();
-  for (int c = lane; c < P2; c += 64) {  // (bx, az) of (ox, oy) = wave
-    const int bx = c / P, az = c % P;
-    W in[P];
-#pragma unroll
-    for (int a = 0; a < P; ++a) in[a] = w[(((wave >> 1) * P + bx) * P + a) * Q + az];
-#pragma unroll
-    for (int by = 0; by < P; ++by) {
-      W acc = 0;
-#pragma unroll
-      for (int a = 0; a < P; ++a) acc += T[((wave & 1) * P + a) * P + by] * in[a];
-      v[((wave * P + bx) * P + by) * Q + az] = acc;
-    }
-  }
-  __syncthreads();
-  for (int c = lane; c < P2; c += 64) {  // (bx, by) of (ox, oy) = wave
-    W in[P];
-#pragma unroll
-    for (int a = 0; a < P; ++a) in[a] = v[(wave * P2 + c) * Q + a];
-#pragma unroll
-    for (int oz = 0; oz < 2; ++oz) {
-      const size_t child = ((size_t)(2 * Bx + (wave >> 1)) * nc + (2 * By + (wave & 1))) * nc + (2 * Bz + oz);
-      TO* dst = Pc + child * P3 + c * P;
-#pragma unroll
-      for (int bz = 0; bz < P; ++bz) {
-        W acc = 0;
-#pragma unroll
-        for (int a = 0; a < P; ++a) acc += T[(oz * P + a) * P + bz] * in[a];
-        dst[bz] = accumulate ? (TO)((W)dst[bz] + acc) : (TO)acc;
-      }
-    }
-  }
+  __shared__ W lds[pair_words<P>()];
+  const TI* src = Pp + (size_t)blockIdx.x * (P * P * P);
+  l2l_block<TO, W, P>([&](int i) { return (W)src[i]; }, Pc, wsel<W>(Tw), np, blockIdx.x, accumulate, lds);
 }
 
-// P2M and L2P of leaves of 8 or 16 cells by columns, as M2M and L2L: a lane
-// holds a column of cells or nodes in registers, the weights are scalars.  P2M
-// contracts z, y, x (mesh rows in the first pass), L2P expands z, y, x (the last
-// pass writes the mesh, its prior values read before the first).  Any
-// alignment.  FP32 gridlets of p = 4 and 8 keep the kernels above, whose rows
-// move as float4 (256^3, p = 8: P2M 29 us there and 24 here, L2P 35 and 34, 512^3 175
-// and 159, 247 and 262; p = 4 alike).  Bound: latency of the three passes up to some
-// 10^3 leaves, then the mesh's traffic.  Measured before (one output a thread,
-// both factors of every product from LDS) / after, FP64 gridlets, 512 leaves of s
-// = 16, p = 6: P2M 18 / 8 us, L2P 20 / 6; p = 8, 19 / 6 and 23 / 5.5.
 template <class TR, class TO, class W, int S, int P>
 __global__ __launch_bounds__(kThreads) void k_p2m_cols(const TR* __restrict__ rho, TO* __restrict__ M,
                                                         Weights Aw, int N, W h3, int vec) {
-  constexpr int P2 = P * P, Q = P | 1, G = kThreads / (S * S);  // waves per row set: 1 or 4 share the az
-  constexpr bool kHalves = S * P <= kThreads / 2;
-  __shared__ W t1[S * S * Q];  // [cx][cy][az]
-  __shared__ W t2[S * P * Q];  // [cx][ay][az]
-  const W* __restrict__ A = wsel<W>(Aw);  // [a][c]
-  const int nL = N / S;
-  const int b = (int)xcd_leaf(blockIdx.x, (int64_t)nL * nL * nL);
-  const int bx = b / (nL * nL), by = (b / nL) % nL, bz = b % nL;
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  {
-    const int r = tid % (S * S), g = G == 1 ? 0 : wave;
-    const TR* src = rho + ((size_t)(bx * S + r / S) * N + (by * S + r % S)) * N + (size_t)bz * S;
-    TR row[S];
-    if (vec) {
-      constexpr int V = 16 / sizeof(TR);
-      typedef TR vec_t __attribute__((ext_vector_type(V)));
-#pragma unroll
-      for (int q = 0; q < S / V; ++q) {
-        const vec_t x = reinterpret_cast<const vec_t*>(src)[q];
-#pragma unroll
-        for (int i = 0; i < V; ++i) row[V * q + i] = x[i];
-      }
-    } else {
-#pragma unroll
-      for (int c = 0; c < S; ++c) row[c] = src[c];
-    }
-#pragma unroll
-    for (int i = 0; i < (P + G - 1) / G; ++i) {
-      const int az = G * i + g;
-      if (az >= P) break;
-      W acc = 0;
-#pragma unroll
-      for (int c = 0; c < S; ++c) acc += A[az * S + c] * (W)row[c];
-      t1[r * Q + az] = acc;
-    }
-  }
-  __syncthreads();
-  const int col = kHalves ? tid % (kThreads / 2) : tid, h = kHalves ? wave >> 1 : 0;
-  if (col < S * P) {
-    const int cx = col / P, az = col % P;
-    W in[S];
-#pragma unroll
-    for (int c = 0; c < S; ++c) in[c] = t1[(cx * S + c) * Q + az];
-    constexpr int step = kHalves ? 2 : 1;
-#pragma unroll
-    for (int i = 0; i < (P + step - 1) / step; ++i) {
-      const int ay = step * i + h;
-      if (ay >= P) break;
-      W acc = 0;
-#pragma unroll
-      for (int c = 0; c < S; ++c) acc += A[ay * S + c] * in[c];
-      t2[(cx * P + ay) * Q + az] = acc;
-    }
-  }
-  __syncthreads();
-  for (int c = lane; c < P2; c += 64) {  // (ay, az), every fourth ax
-    W in[S];
-#pragma unroll
-    for (int x = 0; x < S; ++x) in[x] = t2[(x * P + c / P) * Q + c % P];
-#pragma unroll
-    for (int i = 0; i < (P + 3) / 4; ++i) {
-      const int ax = 4 * i + wave;
-      if (ax >= P) break;
-      W acc = 0;
-#pragma unroll
-      for (int x = 0; x < S; ++x) acc += A[ax * S + x] * in[x];
-      M[(size_t)b * (P2 * P) + ax * P2 + c] = (TO)(h3 * acc);
-    }
-  }
+  __shared__ W lds[p2m_col_words<S, P>()];
+  const int nL = N / S, b = (int)xcd_leaf(blockIdx.x, (int64_t)nL * nL * nL);
+  TO* dst = M + (size_t)b * (P * P * P);
+  p2m_block<TR, W, S, P>(rho, wsel<W>(Aw), N, b, h3, vec, lds, [&](int i, W v) { dst[i] = (TO)v; });
 }
 
 template <class TI, class TP, class W, int S, int P>
 __global__ __launch_bounds__(kThreads) void k_l2p_cols(const TI* __restrict__ Pl, TP* __restrict__ phi,
                                                         Weights Wxw, Weights Wyw, Weights Wzw, W scale,
                                                         int N, int accumulate) {
-  constexpr int P2 = P * P, G = kThreads / (S * S), SX = S / G;  // cx per thread of the last pass
-  constexpr bool kHalves = S * P <= kThreads / 2;
-  constexpr int step = kHalves ? 2 : 1;
-  __shared__ W w1[P2 * (S + 1)];  // [ax][ay][cz]
-  __shared__ W w2[P * S * S];     // [ax][cy][cz]
-  const W* __restrict__ Ax = wsel<W>(Wxw);
-  const W* __restrict__ Ay = wsel<W>(Wyw);
-  const W* __restrict__ Az = wsel<W>(Wzw);
-  const int nL = N / S;
-  const int b = (int)xcd_leaf(blockIdx.x, (int64_t)nL * nL * nL);
-  const int bx = b / (nL * nL), by = (b / nL) % nL, bz = b % nL;
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int yz = tid % (S * S), x0 = (G == 1 ? 0 : wave) * SX;
-  TP* dst = phi + ((size_t)(bx * S + x0) * N + (by * S + yz / S)) * N + (size_t)bz * S + yz % S;
-  TP prior[SX];
-  if (accumulate) {
-#pragma unroll
-    for (int x = 0; x < SX; ++x) prior[x] = dst[(size_t)x * N * N];
-  }
-  for (int c = lane; c < P2; c += 64) {  // (ax, ay), every fourth cz
-    W in[P];
-#pragma unroll
-    for (int a = 0; a < P; ++a) in[a] = (W)Pl[(size_t)b * (P2 * P) + c * P + a];
-#pragma unroll
-    for (int i = 0; i < S / 4; ++i) {
-      const int cz = 4 * i + wave;
-      W acc = 0;
-#pragma unroll
-      for (int a = 0; a < P; ++a) acc += Az[a * S + cz] * in[a];
-      w1[c * (S + 1) + cz] = acc;
-    }
-  }
-  __syncthreads();
-  const int col = kHalves ? tid % (kThreads / 2) : tid, h = kHalves ? wave >> 1 : 0;
-  if (col < S * P) {
-    const int ax = col / S, cz = col % S;
-    W in[P];
-#pragma unroll
-    for (int a = 0; a < P; ++a) in[a] = w1[(ax * P + a) * (S + 1) + cz];
-#pragma unroll
-    for (int i = 0; i < S / step; ++i) {
-      const int cy = step * i + h;
-      W acc = 0;
-#pragma unroll
-      for (int a = 0; a < P; ++a) acc += Ay[a * S + cy] * in[a];
-      w2[(ax * S + cy) * S + cz] = acc;
-    }
-  }
-  __syncthreads();
-  W in[P];
-#pragma unroll
-  for (int a = 0; a < P; ++a) in[a] = w2[a * S * S + yz];
-#pragma unroll
-  for (int x = 0; x < SX; ++x) {
-    W acc = 0;
-#pragma unroll
-    for (int a = 0; a < P; ++a) acc += Ax[a * S + x0 + x] * in[a];
-    acc *= scale;
-    dst[(size_t)x * N * N] = accumulate ? (TP)((W)prior[x] + acc) : (TP)acc;
-  }
+  __shared__ W lds[l2p_col_words<S, P>()];
+  const int nL = N / S, b = (int)xcd_leaf(blockIdx.x, (int64_t)nL * nL * nL);
+  const TI* src = Pl + (size_t)b * (P * P * P);
+  l2p_block<TP, W, S, P>([&](int i) { return (W)src[i]; }, phi, wsel<W>(Wxw), wsel<W>(Wyw), wsel<W>(Wzw),
+                         scale, N, b, accumulate, lds);
 }
 
 // V consecutive cells along z per thread, their rows read and written as
@@ -596,12 +343,12 @@ hipError_t with_p(int p, F&& f) {
   }
 }
 
-// P2M, L2P by columns where the leaf has 8 or 16 cells, else the general form
+// P2M, L2P by columns where the leaf has 4, 8 or 16 cells, else the general form
 template <class TR, class TO, class W>
 hipError_t p2m_any(const TR* rho, TO* M, Weights A, int N, int s, int p, W h3, hipStream_t st) {
   const int nL = N / s;
   const dim3 g(nL * nL * nL), b(kThreads);
-  if (s != 8 && s != 16) {
+  if (s != 4 && s != 8 && s != 16) {
     hipLaunchKernelGGL((k_p2m<TO, W, 0, 0, TR>), g, b, p2m_words(s, p) * sizeof(W), st, rho, M, A, N, s, p, h3);
     return hipGetLastError();
   }
@@ -610,8 +357,10 @@ hipError_t p2m_any(const TR* rho, TO* M, Weights A, int N, int s, int p, W h3, h
     constexpr int p_ = decltype(P)::value;
     if (s == 16)
       hipLaunchKernelGGL((k_p2m_cols<TR, TO, W, 16, p_>), g, b, 0, st, rho, M, A, N, h3, vec);
-    else
+    else if (s == 8)
       hipLaunchKernelGGL((k_p2m_cols<TR, TO, W, 8, p_>), g, b, 0, st, rho, M, A, N, h3, vec);
+    else
+      hipLaunchKernelGGL((k_p2m_cols<TR, TO, W, 4, p_>), g, b, 0, st, rho, M, A, N, h3, vec);
     return hipGetLastError();
   });
 }
@@ -621,7 +370,7 @@ hipError_t l2p_any(const TI* P, TP* out, Weights Wx, Weights Wy, Weights Wz, W s
                    hipStream_t st, int accumulate) {
   const int nL = N / s;
   const dim3 g(nL * nL * nL), b(kThreads);
-  if (s != 8 && s != 16) {
+  if (s != 4 && s != 8 && s != 16) {
     const size_t words = (size_t)(3 * p * s + p * p * p + p * p * s + p * s * s);
     hipLaunchKernelGGL((k_l2p<TI, W, 0, 0, TP>), g, b, words * sizeof(W), st, P, out, Wx, Wy, Wz, scale, N, s,
                        p, accumulate);
@@ -631,8 +380,10 @@ hipError_t l2p_any(const TI* P, TP* out, Weights Wx, Weights Wy, Weights Wz, W s
     constexpr int p_ = decltype(Pc)::value;
     if (s == 16)
       hipLaunchKernelGGL((k_l2p_cols<TI, TP, W, 16, p_>), g, b, 0, st, P, out, Wx, Wy, Wz, scale, N, accumulate);
-    else
+    else if (s == 8)
       hipLaunchKernelGGL((k_l2p_cols<TI, TP, W, 8, p_>), g, b, 0, st, P, out, Wx, Wy, Wz, scale, N, accumulate);
+    else
+      hipLaunchKernelGGL((k_l2p_cols<TI, TP, W, 4, p_>), g, b, 0, st, P, out, Wx, Wy, Wz, scale, N, accumulate);
     return hipGetLastError();
   });
 }
