@@ -549,41 +549,55 @@ __global__ void __launch_bounds__(leaf_threads<S>()) k_leaf_inv(const float2* __
   }
 }
 
+// -x in a register of its own: a negation folded into the multiply-add would
+// take its three-operand form, which issues at half the rate.
+__device__ __forceinline__ float neg_reg(float x) {
+  float r;
+  asm("v_xor_b32 %0, 0x80000000, %1" : "=v"(r) : "v"(x));
+  return r;
+}
+
 // yhat_b(k) = sum_e khat_e(k) rhat_{b+e}(k).  A thread owns one frequency
-// and a 2 x 2 block of pencils of leaves (bx, by), swept along z: the 4 x 4
-// source columns around the block are each read once per z and serve all
-// four targets (4 reads per output instead of 9), three z-planes of them in
-// registers.  Each step first adds the lowest plane's terms, then reloads
-// that plane's registers with the plane two above (in flight while the other
-// two planes' terms are added), so three register sets rotate.  The
-// thread's kernel values sit in its own slots of LDS (no barrier: only the
-// writing thread reads them).  The pencil blocks of one frequency chunk go
-// to one XCD (blocks are dealt to the 8 XCDs round robin), so its L2 serves
-// the column re-reads between neighbouring blocks.
+// and a 2 x TY block of pencils of leaves (bx, by), swept along z: the 4 x (TY
+// + 2) source columns around the block are each read once per z and serve all
+// the targets.  A source plane is added to the three target planes that see
+// it, so one source plane, the next one in flight and three planes of sums are
+// in registers; every target's terms keep the order of its neighbours (ez, ex,
+// ey).  The thread's kernel values sit in its own slots of LDS (no barrier:
+// only the writing thread reads them).  The pencil blocks of one frequency
+// chunk go to one XCD (blocks are dealt to the 8 XCDs round robin), so its L2
+// serves the column re-reads between neighbouring blocks.
 //
-// The stencil is bound by its vector memory instructions (the texture
-// units' address and data paths, not the bytes), so in the chunked layout
-// every load and store moves 16 bytes per lane: lane l takes frequency
-// 2 (l mod 32) + l / 32 of its chunk, a half-wave reads or writes one
-// leaf's 64 frequencies, and a swap of values between the half-waves
-// (v_permlane32_swap) gives each lane its frequency of two columns, or
-// gathers two targets' outputs, per instruction.
+// Bound: the vector ALU (0.7 busy at 128^3, of which 0.85 are the sums; FP32
+// at the rate without packed pairs), then the texture units, which move each
+// source 4 (TY = 2) or 3 times.  Three source planes in registers, as the sums
+// of one target plane would take, left two waves a SIMD instead of four (three
+// at TY = 4).  Measured before / after, one kernel: 32^3, s = 4 13.9 / 8.1 us, 64^3
+// 17.7 / 13.8, 128^3, s = 16 48.9 / 43.4 (isolated 78.7 / 45), 256^3 346 / 316, 512^3
+// 2423 / 2160.
+//
+// In the chunked layout every load and store moves 16 bytes per lane: lane l
+// takes frequency 2 (l mod 32) + l / 32 of its chunk, a half-wave reads or
+// writes one leaf's 64 frequencies, and a swap of values between the
+// half-waves (v_permlane32_swap) gives each lane its frequency of two columns,
+// or gathers two targets' outputs, per instruction.
 //
 // SYM = +1 (-1): the kernel is even (odd) in the cell separation, so the
 // transform of neighbour -e is the conjugate (minus the conjugate) of that of
 // e, and only the 14 kernels from the centre up in index order are kept in
 // LDS (half the LDS per thread).  SYM = 0: all 27.
-template <bool CHUNKED, bool ISO, int SYM = 0>
-__global__ void __launch_bounds__(CHUNKED ? 64 : kThreads) k_near_mac(
-    const float2* __restrict__ rhat, const float2* __restrict__ khat, int nb, int64_t F,
+template <bool CHUNKED, bool ISO, int SYM = 0, int TY = 2>
+__global__ void __launch_bounds__(CHUNKED ? 64 : kThreads, CHUNKED ? (TY == 2 ? 4 : 3) : 1) k_near_mac(
+    const float2* __restrict__ rhat, const float2* __restrict__ khat, int nb, int nz, int64_t F,
     int nchunk, float2* __restrict__ yhat) {
   constexpr bool isolated = ISO;  // sources outside the box are absent
   constexpr int W = CHUNKED ? 64 : kThreads;  // frequencies per block
   constexpr int NK = SYM ? 14 : 27;           // kernels kept
+  constexpr int CY = TY + 2, NC = 4 * CY, NT = 2 * TY;
   __shared__ float2 kks[NK * W];
   const int g = blockIdx.x;
-  const int hb = nb >> 1;
-  const int np = hb * hb;  // 2 x 2 pencil blocks
+  const int hy = nb / TY, hz = nb / nz;
+  const int np = (nb >> 1) * hy * hz;  // 2 x TY pencil blocks, segments of nz planes
   const int j = g >> 3;
   const int chunk = (j / np) * 8 + (g & 7);
   if (chunk >= nchunk) return;
@@ -612,125 +626,158 @@ __global__ void __launch_bounds__(CHUNKED ? 64 : kThreads) k_near_mac(
       __builtin_amdgcn_make_buffer_rsrc(obase, (short)0, (int)chunk_bytes, kBufferDword3);
   const int msk = nb - 1;
   const int blk = j % np;
-  const int bx0 = 2 * (blk / hb), by0 = 2 * (blk % hb);
+  const int bx0 = 2 * (blk / (hy * hz)), by0 = TY * (blk / hz % hy), z0 = blk % hz * nz;
   float2* kk = kks + threadIdx.x;  // kernel e at kk[slot(e) * W]
   // e = (ex, ey, ez) in {0, 1, 2}^3 (offset e - 1), index 9 ex + 3 ey + ez;
   // its opposite is 26 - e.  With SYM the kernels e >= 13 sit at slot
   // e - 13 and e < 13 reads slot 13 - e (its opposite's) conjugated.
 #pragma unroll
   for (int e = SYM ? 13 : 0; e < 27; ++e) kk[(SYM ? e - 13 : e) * W] = khat[(int64_t)e * F + k];
-  // columns (bx0 - 1 + ix, by0 - 1 + iy), ix, iy in [0, 4), c = 4 ix + iy
+  // columns (bx0 - 1 + ix, by0 - 1 + iy), ix in [0, 4), iy in [0, CY), c = CY ix + iy
   auto load = [&](int c, int z) -> float2 {
-    const int sx = bx0 - 1 + c / 4, sy = by0 - 1 + c % 4;
+    const int sx = bx0 - 1 + c / CY, sy = by0 - 1 + c % CY;
     if (isolated && (z < 0 || z >= nb || sx < 0 || sx >= nb || sy < 0 || sy >= nb))
       return make_float2(0.0f, 0.0f);
     const int leaf = (((sx & msk) * nb + (sy & msk)) * nb) + (z & msk);
-    if constexpr (CHUNKED) {
-      return __builtin_bit_cast(
-          float2, __builtin_amdgcn_raw_buffer_load_b64(rin, phi * 8, leaf * 512, 0));
-    } else {
-      return base[(int64_t)leaf * stride + lane];
-    }
+    return base[(int64_t)leaf * stride + lane];
   };
-  // a z-plane of the 16 columns.  Chunked: the lower half-wave loads column
+  // a z-plane of the columns.  Chunked: the lower half-wave loads column
   // c with 16 bytes per lane (frequencies 2j and 2j + 1 in lane j), the
   // upper half column c + 1; swapping the lower half's odd values with the
   // upper half's even ones leaves every lane its own frequency of both
   // columns, with half the load instructions of one 8-byte load per column.
   const unsigned hi = lane >> 5, lo16 = (lane & 31) * 16;
-  auto load_plane = [&](float2 (&dst)[16], int z) {
-    if constexpr (CHUNKED) {
+  unsigned col[NC / 2];  // this lane's column of pair c, at z = 0, in bytes
+  bool in[NC / 2];
+  if constexpr (CHUNKED) {
 #pragma unroll
-      for (int c = 0; c < 16; c += 2) {
-        const int sxa = bx0 - 1 + c / 4, sya = by0 - 1 + c % 4, syb = sya + 1;
-        const int la = (((sxa & msk) * nb + (sya & msk)) * nb) + (z & msk);
-        const int lb = (((sxa & msk) * nb + (syb & msk)) * nb) + (z & msk);
-        v4u32 q = __builtin_amdgcn_raw_buffer_load_b128(rin, (unsigned)((hi ? lb : la) * 512) + lo16, 0, 0);
-        if (isolated) {
-          const bool zin = z >= 0 && z < nb && sxa >= 0 && sxa < nb;
-          const bool ok = zin && (hi ? (syb >= 0 && syb < nb) : (sya >= 0 && sya < nb));
-          if (!ok) q = v4u32{0u, 0u, 0u, 0u};
-        }
-        const auto sre = __builtin_amdgcn_permlane32_swap(q[0], q[2], false, false);
-        const auto sim = __builtin_amdgcn_permlane32_swap(q[1], q[3], false, false);
-        dst[c] = make_float2(__uint_as_float(sre[0]), __uint_as_float(sim[0]));
-        dst[c + 1] = make_float2(__uint_as_float(sre[1]), __uint_as_float(sim[1]));
+    for (int c = 0; c < NC / 2; ++c) {
+      const int sx = bx0 - 1 + 2 * c / CY, sy = by0 - 1 + 2 * c % CY + (int)hi;
+      col[c] = (unsigned)(((sx & msk) * nb + (sy & msk)) * nb * 512) + lo16;
+      in[c] = !isolated || (sx >= 0 && sx < nb && sy >= 0 && sy < nb);
+    }
+  }
+  auto load_plane = [&](float2 (&dst)[NC], int z) {
+    if constexpr (CHUNKED) {
+      const int zo = __builtin_amdgcn_readfirstlane((z & msk) * 512);
+#pragma unroll
+      for (int c = 0; c < NC; c += 2) {
+        v4u32 q = __builtin_amdgcn_raw_buffer_load_b128(rin, col[c / 2], zo, 0);
+        if (isolated && (z < 0 || z >= nb || !in[c / 2])) q = v4u32{0u, 0u, 0u, 0u};
+        dst[c] = make_float2(__uint_as_float(q[0]), __uint_as_float(q[1]));
+        dst[c + 1] = make_float2(__uint_as_float(q[2]), __uint_as_float(q[3]));
       }
     } else {
 #pragma unroll
-      for (int c = 0; c < 16; ++c) dst[c] = load(c, z);
+      for (int c = 0; c < NC; ++c) dst[c] = load(c, z);
     }
   };
-  float2 r0[16], r1[16], r2[16];
-  load_plane(r0, -1);
-  load_plane(r1, 0);
-  load_plane(r2, 1);
-  // one complex multiply-add as four FMAs
-  auto cmac = [](float& re, float& im, float2 kv, float2 sv) {
-    re = fmaf(kv.x, sv.x, re);
-    re = fmaf(-kv.y, sv.y, re);
-    im = fmaf(kv.x, sv.y, im);
-    im = fmaf(kv.y, sv.x, im);
-  };
-  // plane `ez` (0: z - 1, 1: z, 2: z + 1) of the four targets' sums
-  auto plane = [&](float (&re)[4], float (&im)[4], const float2 (&zz)[16], int ez) {
-    // the kernel values are read from LDS here, every time: an empty asm
-    // statement with a memory clobber keeps the compiler from hoisting them
-    // into registers for the whole sweep (it emits no instruction)
-    asm volatile("" ::: "memory");
+  // the loaded plane's values to the lanes of their frequencies
+  auto settle = [&](float2 (&dst)[NC]) {
+    if constexpr (CHUNKED) {
 #pragma unroll
-    for (int ex = 0; ex < 3; ++ex)
+      for (int c = 0; c < NC; c += 2) {
+        const auto sre = __builtin_amdgcn_permlane32_swap(__float_as_uint(dst[c].x),
+                                                          __float_as_uint(dst[c + 1].x), false, false);
+        const auto sim = __builtin_amdgcn_permlane32_swap(__float_as_uint(dst[c].y),
+                                                          __float_as_uint(dst[c + 1].y), false, false);
+        dst[c] = make_float2(__uint_as_float(sre[0]), __uint_as_float(sim[0]));
+        dst[c + 1] = make_float2(__uint_as_float(sre[1]), __uint_as_float(sim[1]));
+      }
+    }
+  };
+  // sums of one target plane
+  struct Sums {
+    float re[NT], im[NT];
+  };
+  auto clear = [](Sums& s) {
+#pragma unroll
+    for (int t = 0; t < NT; ++t) s.re[t] = s.im[t] = 0.0f;
+  };
+  // source plane z, the neighbour ez - 1 of target plane z + 1 - ez
+  auto plane = [&](const float2 (&v)[NC], Sums& s, int ez) {
+#pragma unroll
+    for (int ex = 0; ex < 3; ++ex) {
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int ey = 0; ey < 3; ++ey) {
         const int e = ex * 9 + ey * 3 + ez;
         const bool kept = !SYM || e >= 13;
-        float2 kv = kk[(SYM ? (kept ? e - 13 : 13 - e) : e) * W];
-        if (!kept) kv = SYM > 0 ? make_float2(kv.x, -kv.y) : make_float2(-kv.x, kv.y);
+        const float2 kv = kk[(SYM ? (kept ? e - 13 : 13 - e) : e) * W];
+        const float ny = neg_reg(kv.y);
+        const float kx = kept || SYM > 0 ? kv.x : neg_reg(kv.x);
+        const float ky = kept || SYM < 0 ? kv.y : ny, nky = kept || SYM < 0 ? ny : kv.y;
 #pragma unroll
-        for (int tx = 0; tx < 2; ++tx)
-#pragma unroll
-          for (int ty = 0; ty < 2; ++ty)
-            cmac(re[tx * 2 + ty], im[tx * 2 + ty], kv, zz[(tx + ex) * 4 + (ty + ey)]);
-      }
-  };
-  // targets at z = bz: planes zm (bz - 1), z0 (bz), zp (bz + 1); zm is
-  // reloaded with bz + 2 once its terms are in
-  auto step = [&](int bz, float2 (&zm)[16], float2 (&z0)[16], float2 (&zp)[16]) {
-    float re[4] = {0.0f, 0.0f, 0.0f, 0.0f}, im[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    plane(re, im, zm, 0);
-    if (bz + 1 < nb) load_plane(zm, bz + 2);
-    plane(re, im, z0, 1);
-    plane(re, im, zp, 2);
-#pragma unroll
-    for (int tx = 0; tx < 2; ++tx) {
-      if constexpr (CHUNKED) {
-        // the two targets (tx, 0), (tx, 1) with one 16-byte store per lane:
-        // after the swap the lower half-wave holds frequencies 2j, 2j + 1 of
-        // the first, the upper half those of the second
-        const int l0 = ((bx0 + tx) * nb + by0) * nb + bz, l1 = l0 + nb;
-        const auto sre = __builtin_amdgcn_permlane32_swap(__float_as_uint(re[tx * 2]),
-                                                          __float_as_uint(re[tx * 2 + 1]), false, false);
-        const auto sim = __builtin_amdgcn_permlane32_swap(__float_as_uint(im[tx * 2]),
-                                                          __float_as_uint(im[tx * 2 + 1]), false, false);
-        const v4u32 q = {sre[0], sim[0], sre[1], sim[1]};
-        __builtin_amdgcn_raw_buffer_store_b128(q, rout, (unsigned)((hi ? l1 : l0) * 512) + lo16, 0, 0);
-      } else {
-#pragma unroll
-        for (int ty = 0; ty < 2; ++ty) {
-          const int leaf = ((bx0 + tx) * nb + by0 + ty) * nb + bz;
-          obase[(int64_t)leaf * stride + lane] = make_float2(re[tx * 2 + ty], im[tx * 2 + ty]);
+        for (int t = 0; t < NT; ++t) {
+          const float2 sv = v[(t / TY + ex) * CY + t % TY + ey];
+          s.re[t] = fmaf(kx, sv.x, s.re[t]);
+          s.re[t] = fmaf(nky, sv.y, s.re[t]);
+          s.im[t] = fmaf(kx, sv.y, s.im[t]);
+          s.im[t] = fmaf(ky, sv.x, s.im[t]);
         }
       }
     }
   };
-  int bz = 0;
-  for (; bz + 3 <= nb; bz += 3) {
-    step(bz, r0, r1, r2);
-    step(bz + 1, r1, r2, r0);
-    step(bz + 2, r2, r0, r1);
+  const unsigned tgt = (unsigned)((bx0 * nb + by0 + (CHUNKED ? (int)hi : 0)) * nb * 512) + lo16;
+  auto store = [&](const Sums& s, int bz) {
+#pragma unroll
+    for (int t = 0; t < NT; t += CHUNKED ? 2 : 1) {
+      if constexpr (CHUNKED) {
+        // two targets neighbouring in y with one 16-byte store per lane:
+        // after the swap the lower half-wave holds frequencies 2j, 2j + 1 of
+        // the first, the upper half those of the second
+        const auto sre = __builtin_amdgcn_permlane32_swap(__float_as_uint(s.re[t]),
+                                                          __float_as_uint(s.re[t + 1]), false, false);
+        const auto sim = __builtin_amdgcn_permlane32_swap(__float_as_uint(s.im[t]),
+                                                          __float_as_uint(s.im[t + 1]), false, false);
+        const v4u32 q = {sre[0], sim[0], sre[1], sim[1]};
+        // the whole offset per lane: with part of it in a scalar register the
+        // compiler leaves out the wait between this store and a write to its
+        // data registers (it was needed: the data changed under the store)
+        __builtin_amdgcn_raw_buffer_store_b128(
+            q, rout, tgt + (unsigned)(((t / TY * nb + t % TY) * nb + bz) * 512), 0, 0);
+      } else {
+        const int leaf = ((bx0 + t / TY) * nb + by0 + t % TY) * nb + bz;
+        obase[(int64_t)leaf * stride + lane] = make_float2(s.re[t], s.im[t]);
+      }
+    }
+  };
+  float2 va[NC], vb[NC];
+  Sums s0, s1, s2;
+  // source plane z from v; the plane after it is put into `next` meanwhile;
+  // `lo`, `mid`, `up` are the sums of the target planes z - 1, z, z + 1
+  auto step = [&](int z, float2 (&v)[NC], float2 (&next)[NC], Sums& lo, Sums& mid, Sums& up,
+                  bool do_lo, bool do_mid, bool do_up) {
+    settle(v);
+    if (do_mid || do_up) load_plane(next, z + 1);  // the last plane is read with the one before it
+    // the kernel values are read from LDS here, every time: an empty asm
+    // statement with a memory clobber keeps the compiler from hoisting them
+    // into registers for the whole sweep (it emits no instruction)
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    if (do_lo) {
+      plane(v, lo, 2);
+      store(lo, z - 1);
+    }
+    if (do_mid) plane(v, mid, 1);
+    if (do_up) {
+      clear(up);
+      plane(v, up, 0);
+    }
+  };
+  load_plane(va, z0 - 1);
+  step(z0 - 1, va, vb, s1, s2, s0, false, false, true);
+  step(z0, vb, va, s2, s0, s1, false, true, true);
+  const int zl = z0 + nz - 1;
+  for (int z = z0 + 1; z < zl; z += 2) {  // nz is even
+    step(z, va, vb, s0, s1, s2, true, true, true);
+    step(z + 1, vb, va, s1, s2, s0, true, true, true);
+    s1 = s0;
+    s0 = s2;
   }
-  if (bz < nb) step(bz, r0, r1, r2);
-  if (bz + 1 < nb) step(bz + 1, r1, r2, r0);
+  step(zl, va, vb, s0, s1, s2, true, true, false);
+  step(zl + 1, vb, va, s1, s2, s0, true, false, false);
 }
 
 }  // namespace
@@ -879,17 +926,33 @@ hipError_t inv_any(NearFft* f, float* out, const LeafTree& tree, int p, hipStrea
   }
 }
 
-template <bool ISO>
-hipError_t near_mac_iso(NearFft* f, int t, hipStream_t st) {
-  const int nchunk = (int)(f->F / 64);
-  const unsigned blocks = (unsigned)((int64_t)((nchunk + 7) / 8) * 8 * (f->nb / 2) * (f->nb / 2));
-  if (f->sym[t] > 0)
-    k_near_mac<true, ISO, 1><<<blocks, 64, 0, st>>>(f->rhat, f->khat[t], f->nb, f->F, nchunk, f->yhat);
-  else if (f->sym[t] < 0)
-    k_near_mac<true, ISO, -1><<<blocks, 64, 0, st>>>(f->rhat, f->khat[t], f->nb, f->F, nchunk, f->yhat);
-  else
-    k_near_mac<true, ISO, 0><<<blocks, 64, 0, st>>>(f->rhat, f->khat[t], f->nb, f->F, nchunk, f->yhat);
+// Blocks of 2 x 4 pencils (fewer reads a target) where these give 8 waves to
+// each of the 1024 SIMDs (the kernel alone at 256^3, 8704 waves of 2 x 4: 316 us
+// against 331 of 2 x 2; at 512^3 2160 against 2630), 2 x 2 below; there the sweeps are
+// cut in segments, which read two more planes than they write, until there are 4
+// waves a SIMD: at 32^3 8.1 us in four, 15.1 in one, 20 of 2 x 4.  At 128^3 two
+// segments are faster alone (41.5 against 43.4 us) but take more from the tree
+// that runs beside them: a solve (p = 6) 141 us against 139 in one.
+template <bool ISO, int SYM>
+hipError_t near_mac_as(const NearFft* f, int t, hipStream_t st) {
+  constexpr int64_t kWaves = 4096;
+  const int nb = f->nb, nchunk = (int)(f->F / 64);
+  const int64_t quads = (int64_t)((nchunk + 7) / 8) * 8 * (nb / 2) * (nb / 2);
+  if (quads >= 4 * kWaves) {
+    k_near_mac<true, ISO, SYM, 4><<<(unsigned)(quads / 2), 64, 0, st>>>(f->rhat, f->khat[t], nb, nb, f->F,
+                                                                       nchunk, f->yhat);
+    return hipGetLastError();
+  }
+  int nz = nb;
+  while (nz > 2 && quads * (nb / nz) < kWaves) nz /= 2;
+  k_near_mac<true, ISO, SYM, 2><<<(unsigned)(quads * (nb / nz)), 64, 0, st>>>(f->rhat, f->khat[t], nb, nz,
+                                                                             f->F, nchunk, f->yhat);
   return hipGetLastError();
+}
+template <bool ISO>
+hipError_t near_mac_iso(const NearFft* f, int t, hipStream_t st) {
+  return f->sym[t] > 0 ? near_mac_as<ISO, 1>(f, t, st)
+         : f->sym[t] < 0 ? near_mac_as<ISO, -1>(f, t, st) : near_mac_as<ISO, 0>(f, t, st);
 }
 
 hipError_t near_mac(NearFft* f, int t, int isolated, hipStream_t st) {
@@ -962,10 +1025,10 @@ hipError_t near_fft_run(NearFft* f, const float* rho, float* const* out, int nou
     e = tbegin(kt, st);
     if (e != hipSuccess) break;
     if (isolated)
-      k_near_mac<false, true><<<(unsigned)blocks, kThreads, 0, st>>>(f->rhat, f->khat[t], f->nb, f->F,
+      k_near_mac<false, true><<<(unsigned)blocks, kThreads, 0, st>>>(f->rhat, f->khat[t], f->nb, f->nb, f->F,
                                                                      nchunk, f->yhat);
     else
-      k_near_mac<false, false><<<(unsigned)blocks, kThreads, 0, st>>>(f->rhat, f->khat[t], f->nb, f->F,
+      k_near_mac<false, false><<<(unsigned)blocks, kThreads, 0, st>>>(f->rhat, f->khat[t], f->nb, f->nb, f->F,
                                                                       nchunk, f->yhat);
     e = tend(kt, st, 1 + 2 * t, hipGetLastError());
     if (e == hipSuccess) e = tbegin(kt, st);
