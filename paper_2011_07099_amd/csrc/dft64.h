@@ -100,8 +100,8 @@ __device__ __forceinline__ double2 dsub(double2 a, double2 b) { return make_doub
 template <int P, bool INV>
 __device__ __forceinline__ double2 dtwiddle(double2 a, int j) {
   const double2 w = twd<P>(j);
-  return INV ? make_double2(a.x * w.x - a.y * w.y, a.y * w.x + a.x * w.y)
-             : make_double2(a.x * w.x + a.y * w.y, a.y * w.x - a.x * w.y);
+  const double y = INV ? w.y : -w.y;  // explicit: every kernel rounds the same
+  return make_double2(fma(a.x, w.x, -(a.y * y)), fma(a.y, w.x, a.x * y));
 }
 
 // i a

@@ -155,9 +155,9 @@ __device__ __forceinline__ void node_inv_block(const TS* __restrict__ spec, int6
 #pragma unroll
       for (int k = 1; k < P; ++k) {
         const double2 w = twd<M>(k * z);
-        b += u[k].x * w.x - u[k].y * w.y;
+        b = fma(-u[k].y, w.y, fma(u[k].x, w.x, b));
       }
-      const double v = u[0].x + ((z & 1) ? -u[P].x : u[P].x) + 2.0 * b;
+      const double v = fma(2.0, b, u[0].x + ((z & 1) ? -u[P].x : u[P].x));
       store(r * P + z, v);
     }
   }
