@@ -218,7 +218,8 @@ typedef enum {
    * leaf edges 4, 8 or 16 sum it in FP64 in every precision, each leaf pair as
    * a cyclic convolution on the doubled grid (exact up to FP64 rounding;
    * buffers of about 140 bytes per cell, at most 3 GiB unless two planes of
-   * leaves need more).  Other leaf edges, batches, and plans without the memory
+   * leaves need more, made with the plan and kept while it lives, also when
+   * other routes are selected: a captured solve may use them).  Other leaf edges, batches, and plans without the memory
    * for those buffers use a block-Toeplitz GEMM (matrix cores or the portable
    * kernel, as PFMM_OPT_PRECISION selects).  Any alignment. */
   PFMM_NEAR_DIRECT = 0,

@@ -348,9 +348,12 @@ struct Near64;
 // 3 GiB unless two leaf planes need more); allocates.
 hipError_t near64_create(int N, int s, Near64** out);
 void near64_destroy(Near64* f);
-// Transform the near-zone kernels of `ntabs` (1 .. 4) FP64 tables (as
-// near_fft_tables); allocates the kernels on first use, enqueued on `st`.
+// Transform the near-zone kernels of `ntabs` (1 or 4) FP64 tables (as
+// near_fft_tables), enqueued on `st`; allocates the accelerations' kernels on
+// first use (without the memory for them the first table's alone).
 hipError_t near64_tables(Near64* f, const double* const* tabs, int ntabs, double scale, hipStream_t st);
+// Kernels transformed so far (0 without buffers).
+int near64_kernels(const Near64* f);
 // out[t] = the near zone of rho with kernel t, t < nout (written, not added);
 // isolated: sources outside the box are absent.  Any alignment.
 hipError_t near64_run(const Near64* f, const float* rho, float* const* out, int nout, int isolated,

@@ -523,10 +523,17 @@ hipError_t near64_tables(Near64* f, const double* const* tabs, int ntabs, double
   const size_t one = (size_t)27 * f->F;
   hipError_t e = hipSuccess;
   if (ntabs > 1 && !f->khat[1]) {
-    e = hipMalloc(&f->khat[1], 3 * one * sizeof(double2));
-    if (e != hipSuccess) return e;
-    f->khat[2] = f->khat[1] + one;
-    f->khat[3] = f->khat[2] + one;
+    double2* k = nullptr;
+    e = hipMalloc(&k, 3 * one * sizeof(double2));
+    if (e == hipErrorOutOfMemory) {
+      (void)hipGetLastError();
+      e = hipSuccess;
+      ntabs = 1;
+    } else if (e != hipSuccess) {
+      return e;
+    } else {
+      for (int t = 1; t < 4; ++t) f->khat[t] = k + (t - 1) * one;
+    }
   }
   for (int t = 0; t < ntabs && e == hipSuccess; ++t) {
     // the passes' [27][F] values go through the spectra (at least 64 leaves)
@@ -538,6 +545,8 @@ hipError_t near64_tables(Near64* f, const double* const* tabs, int ntabs, double
   f->ntabs = e == hipSuccess ? std::max(f->ntabs, ntabs) : 0;
   return e;
 }
+
+int near64_kernels(const Near64* f) { return f ? f->ntabs : 0; }
 
 hipError_t near64_run(const Near64* f, const float* rho, float* const* out, int nout, int isolated,
                       hipStream_t st) {

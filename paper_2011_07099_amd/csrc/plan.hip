@@ -66,8 +66,8 @@ struct pfmm_plan_s {
   int m2l_fft = 0;                // interaction zones by FFT convolution (PFMM_OPT_M2L)
   M2LFft* fft = nullptr;          // its plans, grids and transformed kernels
   int m2l_spectral = 0;           // interaction zones as spectral stencils (PFMM_OPT_M2L)
-  M2LSpectral* mspec = nullptr;   // spectra and transformed kernels of its levels, and of the
-                                  // default zones' (single solves)
+  M2LSpectral* mspec = nullptr;   // its spectra and transformed kernels (zspec where that has every level)
+  M2LSpectral* zspec = nullptr;   // those of the default zones of single solves, levels 2 .. zone_top
   int zone_top = 0;               // the default zones' finest level by transforms
   int near_fft = 0;               // leaf near zone by FFT convolution (PFMM_OPT_NEAR)
   int fold = 0;                   // P2M and L2P inside its leaf transforms (PFMM_OPT_FOLD)
@@ -303,8 +303,9 @@ void release(pfmm_plan_s* pl) {
   pl->nfft = nullptr;
   if (pl->n64) near64_destroy(pl->n64);
   pl->n64 = nullptr;
-  if (pl->mspec) m2l_spectral_destroy(pl->mspec);
-  pl->mspec = nullptr;
+  if (pl->mspec != pl->zspec) m2l_spectral_destroy(pl->mspec);
+  m2l_spectral_destroy(pl->zspec);
+  pl->mspec = pl->zspec = nullptr;
   if (pl->gfft) gstar_fft_destroy(pl->gfft);
   pl->gfft = nullptr;
   for (hipEvent_t e : pl->ev)
@@ -367,32 +368,32 @@ pfmm_status refresh_near_fft(pfmm_plan_s* pl) {
   return PFMM_OK;
 }
 
-// The FP64 near zone of a plan whose options ask for it (direct, or FP64
-// precision whatever PFMM_OPT_NEAR says) at the leaf edges it serves: made or
-// released, its kernels transformed.  Without the memory for it the plan keeps
-// the block-Toeplitz sum.  Split precision takes it too: at 256^3, s = 16, 1.21
-// ms in FP64 against 7.6-8.1 ms for the bf16 products on the matrix cores.
-pfmm_status refresh_near64(pfmm_plan_s* pl) {
-  const bool want = pl->prec == PFMM_PREC_FP64 || !pl->near_fft;
-  if (!want || (pl->s != 4 && pl->s != 8 && pl->s != 16)) {
-    if (!pl->n64) return PFMM_OK;
-    hipError_t e = hipStreamSynchronize(pl->stream);
-    if (e == hipSuccess && pl->side) e = hipStreamSynchronize(pl->side);
-    near64_destroy(pl->n64);
-    pl->n64 = nullptr;
-    return e == hipSuccess ? PFMM_OK : hip_fail(e, "FP64 near zone");
-  }
-  const double* tabs[4] = {pl->ntab64, pl->ndtab64[0], pl->ndtab64[1], pl->ndtab64[2]};
-  const double h3 = 1.0 / ((double)pl->N * pl->N * pl->N);
-  hipError_t e = pl->n64 ? hipSuccess : near64_create(pl->N, pl->s, &pl->n64);
-  if (e == hipSuccess) e = near64_tables(pl->n64, tabs, pl->accel_mode ? 4 : 1, h3, pl->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(pl->stream);
+// The FP64 near zone (direct, or FP64 precision whatever PFMM_OPT_NEAR says) at
+// the leaf edges it serves, made with the plan; without the memory for it the
+// plan keeps the block-Toeplitz sum.  Split precision takes it too: at 256^3, s =
+// 16, 1.21 ms in FP64 against 7.6-8.1 ms for the bf16 products on the matrix
+// cores.  It lives as long as the plan, whatever the options become: a solve
+// captured into a graph holds its buffers, and its kernels follow G like the
+// tables do.
+pfmm_status create_near64(pfmm_plan_s* pl) {
+  if (pl->s != 4 && pl->s != 8 && pl->s != 16) return PFMM_OK;
+  const hipError_t e = near64_create(pl->N, pl->s, &pl->n64);
   if (e == hipErrorOutOfMemory) {
     (void)hipGetLastError();
-    if (pl->n64) near64_destroy(pl->n64);
-    pl->n64 = nullptr;
     return PFMM_OK;
   }
+  return e == hipSuccess ? PFMM_OK : hip_fail(e, "FP64 near zone");
+}
+
+// Its transformed kernels: G's, and the accelerations' when these come from the
+// expansion (without the memory for those, solves that need them keep the
+// block-Toeplitz sum).
+pfmm_status refresh_near64(pfmm_plan_s* pl) {
+  if (!pl->n64) return PFMM_OK;
+  const double* tabs[4] = {pl->ntab64, pl->ndtab64[0], pl->ndtab64[1], pl->ndtab64[2]};
+  const double h3 = 1.0 / ((double)pl->N * pl->N * pl->N);
+  hipError_t e = near64_tables(pl->n64, tabs, pl->accel_mode ? 4 : 1, h3, pl->stream);
+  if (e == hipSuccess) e = hipStreamSynchronize(pl->stream);
   return e == hipSuccess ? PFMM_OK : hip_fail(e, "FP64 near zone");
 }
 
@@ -409,13 +410,15 @@ pfmm_status refresh_near64(pfmm_plan_s* pl) {
 // Else, without the memory, and in batches: block-Toeplitz products.
 constexpr int kZoneMinP = 3;
 bool zones_by_transforms(const pfmm_plan_s* pl, int l) {
-  return pl->mspec && l <= pl->zone_top &&
+  return pl->zspec && l <= pl->zone_top &&
          (pl->prec != PFMM_PREC_BF16X3 || level64(pl, l));
 }
+// The spectra that the plan's zones use.
+M2LSpectral* zone_spectra(const pfmm_plan_s* pl) { return pl->m2l_spectral ? pl->mspec : pl->zspec; }
 // Whether the zones of level l run with the transfers around them fused into
 // their node transforms: FP64 gridlets (p = 3 .. 8) and FP64 sums by transforms.
 bool zones_fused(const pfmm_plan_s* pl, int l) {
-  if (pl->m2l_fft || !level64(pl, l) || !fused_zones(pl->mspec, pl->p)) return false;
+  if (pl->m2l_fft || !level64(pl, l) || !fused_zones(zone_spectra(pl), pl->p)) return false;
   if (!pl->m2l_spectral) return zones_by_transforms(pl, l);
   return !(pl->zones_f32 && l == 4 && l == pl->L && !pl->isolated);  // FP32 columns
 }
@@ -428,13 +431,21 @@ pfmm_status create_zones(pfmm_plan_s* pl) {
   int top = pl->L;
   while (top >= 2 && m2l_spectral_bytes(top, pl->p) > ((size_t)3 << 30)) --top;
   if (top < 2) return PFMM_OK;
-  const hipError_t e = m2l_spectral_create(top, pl->p, &pl->mspec);
+  const hipError_t e = m2l_spectral_create(top, pl->p, &pl->zspec);
   if (e == hipSuccess) pl->zone_top = top;
   if (e == hipErrorOutOfMemory) {
     (void)hipGetLastError();
     return PFMM_OK;
   }
   return e == hipSuccess ? PFMM_OK : hip_fail(e, "zone buffers");
+}
+
+// The zones' transformed kernels follow the level tables.
+hipError_t refresh_zones(pfmm_plan_s* pl) {
+  hipError_t e = pl->zspec ? m2l_spectral_tables(pl->zspec, pl->tab64, pl->stream) : hipSuccess;
+  if (e == hipSuccess && pl->mspec && pl->mspec != pl->zspec)
+    e = m2l_spectral_tables(pl->mspec, pl->tab64, pl->stream);
+  return e;
 }
 
 // Every transformed near-zone kernel follows the tables.
@@ -499,10 +510,8 @@ pfmm_status tabulate_all(pfmm_plan_s* pl) {
     e = m2l_fft_tables(pl->fft, pl->tab64, pl->stream);
     if (e != hipSuccess) return hip_fail(e, "FFT kernels");
   }
-  if (pl->mspec) {  // and those of the spectral stencils
-    e = m2l_spectral_tables(pl->mspec, pl->tab64, pl->stream);
-    if (e != hipSuccess) return hip_fail(e, "spectral zone kernels");
-  }
+  e = refresh_zones(pl);  // and those of the zones' spectra
+  if (e != hipSuccess) return hip_fail(e, "spectral zone kernels");
   pfmm_status s0 = pl->accel_mode ? tabulate_accel_tables(pl) : refresh_near(pl);
   if (s0 != PFMM_OK || !pl->gdelta) return s0;
   // G_* follows the new G: new uncorrected copies, the correction applied again
@@ -774,6 +783,7 @@ pfmm_status build(pfmm_plan_s* pl) {
   if (e == hipSuccess) e = hipEventCreateWithFlags(&pl->ev_local, hipEventDisableTiming);
   if ((st = chk("fork events"))) return st;
   if ((st = create_zones(pl))) return st;
+  if ((st = create_near64(pl))) return st;
   return tabulate_all(pl);
 }
 
@@ -958,17 +968,16 @@ pfmm_status pfmm_plan_set(pfmm_plan_t h, int option, const void* value, size_t b
       if (v == PFMM_M2L_SPECTRAL) {
         if (pl->p != 4 && pl->p != 6 && pl->p != 8)
           return fail(PFMM_ERR_UNSUPPORTED, "the spectral interaction zones need p = 4, 6 or 8");
-        if (!pl->mspec || m2l_spectral_levels(pl->mspec) < pl->L) {
-          M2LSpectral* f = nullptr;
-          hipError_t e = m2l_spectral_create(pl->L, pl->p, &f);
+        if (!pl->mspec) {
+          // the default zones' spectra where they have every level; else spectra
+          // beside them, which captured solves go on using
+          M2LSpectral* f = pl->zspec;
+          hipError_t e = hipSuccess;
+          if (!f || m2l_spectral_levels(f) < pl->L) e = m2l_spectral_create(pl->L, pl->p, &f);
           if (e == hipErrorOutOfMemory) return fail(PFMM_ERR_OUT_OF_MEMORY, "spectral zone buffers");
           if (e != hipSuccess) return hip_fail(e, "spectral zone buffers");
-          if (pl->mspec) {
-            (void)hipStreamSynchronize(pl->stream);
-            m2l_spectral_destroy(pl->mspec);
-          }
           pl->mspec = f;
-          e = m2l_spectral_tables(pl->mspec, pl->tab64, pl->stream);
+          if (f != pl->zspec) e = m2l_spectral_tables(f, pl->tab64, pl->stream);
           if (e == hipSuccess) e = m2l_spectral_set_f32(pl->mspec, pl->zones_f32, pl->stream);
           if (e != hipSuccess) return hip_fail(e, "spectral zone kernels");
         }
@@ -1130,7 +1139,7 @@ pfmm_status solve_impl(pfmm_plan_s* pl, const void* rho_in, void* phi_out, void*
       return m2l_spectral_level(pl->mspec, l, ta.X, ta.fp64, ta.Y, ta.fp64, ta.accumulate,
                                 ta.isolated, pl->zones_f32, st, tm.on ? &tm : nullptr);
     if (zones_by_transforms(pl, l))
-      return m2l_spectral_level(pl->mspec, l, ta.X, ta.fp64, ta.Y, ta.fp64, ta.accumulate,
+      return m2l_spectral_level(pl->zspec, l, ta.X, ta.fp64, ta.Y, ta.fp64, ta.accumulate,
                                 ta.isolated, 0, st);
     if (ta.fp64 && ta.q == 8 && ta.C >= 31) {  // FP64 coarse level on the matrix cores
       ToepF64Args fa{};
@@ -1222,7 +1231,7 @@ pfmm_status solve_impl(pfmm_plan_s* pl, const void* rho_in, void* phi_out, void*
     e = fold ? near_fft_begin(pl->nfft, rho, outs, nout, pl->isolated, lt,
                               overlap ? pl->ev_mass : nullptr, sn, tm.on ? &tm : nullptr)
              : near_fft_run(pl->nfft, rho, outs, nout, pl->isolated, sn, tm.on ? &tm : nullptr);
-  } else if (pl->n64) {
+  } else if (near64_kernels(pl->n64) >= (accel && pl->accel_mode ? 4 : 1)) {
     void* outs[4] = {phi_out, nullptr, nullptr, nullptr};
     int nout = 1;
     if (accel && pl->accel_mode)
@@ -1288,7 +1297,7 @@ pfmm_status solve_impl(pfmm_plan_s* pl, const void* rho_in, void* phi_out, void*
       if (e != hipSuccess) return hip_fail(e, "leaf masses");
     }
   } else if (fuse_leaf) {
-    e = fused_p2m(pl->mspec, L, rho_in, io64, (double*)pl->M[L], A, N, s, h3, st);
+    e = fused_p2m(zone_spectra(pl), L, rho_in, io64, (double*)pl->M[L], A, N, s, h3, st);
     if (e != hipSuccess) return hip_fail(e, "P2M");
   } else {
     e = timed(PFMM_STAGE_P2M, 0, st, [&] {
@@ -1299,7 +1308,7 @@ pfmm_status solve_impl(pfmm_plan_s* pl, const void* rho_in, void* phi_out, void*
   }
   for (int l = L - 1; l >= 2; --l) {
     if (fused(l)) {
-      e = fused_m2m(pl->mspec, l, pl->M[l + 1], is64(l + 1), (double*)pl->M[l], T, st);
+      e = fused_m2m(zone_spectra(pl), l, pl->M[l + 1], is64(l + 1), (double*)pl->M[l], T, st);
       if (e != hipSuccess) return hip_fail(e, "M2M");
       continue;
     }
@@ -1334,9 +1343,9 @@ pfmm_status solve_impl(pfmm_plan_s* pl, const void* rho_in, void* phi_out, void*
   };
   // a fused level's sums, and its local values with their expansion to the next
   auto fused_zone = [&](int l) -> hipError_t {
-    hipError_t r = m2l_spectral_sums(pl->mspec, l, pl->isolated, st);
+    hipError_t r = m2l_spectral_sums(zone_spectra(pl), l, pl->isolated, st);
     if (r == hipSuccess && l < L)
-      r = fused_l2l(pl->mspec, l, (double*)pl->P[l], l > 2, pl->P[l + 1], is64(l + 1), T, st);
+      r = fused_l2l(zone_spectra(pl), l, (double*)pl->P[l], l > 2, pl->P[l + 1], is64(l + 1), T, st);
     return r;
   };
   e = fused(2) ? fused_zone(2) : m2l_timed(a, 2);
@@ -1382,7 +1391,7 @@ pfmm_status solve_impl(pfmm_plan_s* pl, const void* rho_in, void* phi_out, void*
     if (e != hipSuccess) return hip_fail(e, "join");
   }
   if (fuse_leaf) {
-    e = fused_l2p(pl->mspec, L, (double*)pl->P[L], L > 2, phi_out, io64, A, N, s, st);
+    e = fused_l2p(zone_spectra(pl), L, (double*)pl->P[L], L > 2, phi_out, io64, A, N, s, st);
     if (e != hipSuccess) return hip_fail(e, "L2P");
   } else if (!fold) {
     e = timed(PFMM_STAGE_L2P, 0, st, [&] {
@@ -1871,10 +1880,10 @@ hipError_t batch_chain_solve(pfmm_batch_s* b, size_t f, hipStream_t st) {
   const bool fuse_leaf = leaf_fused(pl);
   auto fused = [&](int l) { return l < L ? zones_fused(pl, l) : fuse_leaf; };
   if (e == hipSuccess)
-    e = fuse_leaf ? fused_p2m(pl->mspec, L, b->rho[f], 0, (double*)pl->M[L], A, pl->N, pl->s, h3, st)
+    e = fuse_leaf ? fused_p2m(zone_spectra(pl), L, b->rho[f], 0, (double*)pl->M[L], A, pl->N, pl->s, h3, st)
                   : launch_p2m(b->rho[f], pl->M[L], level64(pl, L), A, pl->N, pl->s, pl->p, h3, st);
   for (int l = L - 1; l >= 2 && e == hipSuccess; --l)
-    e = fused(l) ? fused_m2m(pl->mspec, l, pl->M[l + 1], level64(pl, l + 1), (double*)pl->M[l], T, st)
+    e = fused(l) ? fused_m2m(zone_spectra(pl), l, pl->M[l + 1], level64(pl, l + 1), (double*)pl->M[l], T, st)
                  : launch_m2m(pl->M[l + 1], level64(pl, l + 1), pl->M[l], level64(pl, l), T, 1 << l, pl->p, st);
   for (int l = 2; l <= L && e == hipSuccess; ++l) {
     if (l > 2 && !fused(l - 1))
@@ -1886,12 +1895,12 @@ hipError_t batch_chain_solve(pfmm_batch_s* b, size_t f, hipStream_t st) {
                              pl->zones_f32, st);
       continue;
     }
-    e = m2l_spectral_sums(pl->mspec, l, 0, st);
+    e = m2l_spectral_sums(zone_spectra(pl), l, 0, st);
     if (e == hipSuccess && l < L)
-      e = fused_l2l(pl->mspec, l, (double*)pl->P[l], l > 2, pl->P[l + 1], level64(pl, l + 1), T, st);
+      e = fused_l2l(zone_spectra(pl), l, (double*)pl->P[l], l > 2, pl->P[l + 1], level64(pl, l + 1), T, st);
   }
   if (e == hipSuccess)
-    e = fuse_leaf ? fused_l2p(pl->mspec, L, (double*)pl->P[L], L > 2, b->phi[f], 0, A, pl->N, pl->s, st)
+    e = fuse_leaf ? fused_l2p(zone_spectra(pl), L, (double*)pl->P[L], L > 2, b->phi[f], 0, A, pl->N, pl->s, st)
                   : launch_l2p(pl->P[L], level64(pl, L), b->phi[f], A, pl->N, pl->s, pl->p, st, 1);
   return e;
 }
@@ -2425,7 +2434,7 @@ pfmm_status learned_apply(pfmm_plan_s* pl, int bf16) {
       e = make_windows(pl->tab64[l], C, kM2LTerms, pl->win[l], st);
   }
   // the spectral zones' transformed kernels follow the corrected tables
-  if (e == hipSuccess && pl->mspec) e = m2l_spectral_tables(pl->mspec, pl->tab64, st);
+  if (e == hipSuccess) e = refresh_zones(pl);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   if (e != hipSuccess) return hip_fail(e, "apply learned correction");
   return PFMM_OK;
@@ -2689,7 +2698,7 @@ pfmm_status gstar_apply(pfmm_plan_s* pl) {
   if (e == hipSuccess)
     e = apply_correction(pl->gd0, pl->gdelta, pl->gduidx, ndir, pl->dtab64, nullptr, st);
   if (e == hipSuccess) e = pm_kernel(pl->dtab64, pl->dC, pl->N, pl->dwork, pl->dghat, st);
-  if (e == hipSuccess && pl->mspec) e = m2l_spectral_tables(pl->mspec, pl->tab64, st);
+  if (e == hipSuccess) e = refresh_zones(pl);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   if (e != hipSuccess) return hip_fail(e, "apply G_*");
   return refresh_near(pl);
