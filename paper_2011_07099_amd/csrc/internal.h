@@ -348,10 +348,11 @@ struct Near64;
 // 3 GiB unless two leaf planes need more); allocates.
 hipError_t near64_create(int N, int s, Near64** out);
 void near64_destroy(Near64* f);
-// Transform the near-zone kernels of `ntabs` (1 or 4) FP64 tables (as
-// near_fft_tables), enqueued on `st`; allocates the accelerations' kernels on
-// first use (without the memory for them the first table's alone).
-hipError_t near64_tables(Near64* f, const double* const* tabs, int ntabs, double scale, hipStream_t st);
+// Transform the near-zone kernels of the FP64 tables first .. ntabs - 1 (ntabs 1
+// or 4; as near_fft_tables), enqueued on `st`; allocates the accelerations'
+// kernels on first use (without the memory for them: the first table's alone).
+hipError_t near64_tables(Near64* f, const double* const* tabs, int first, int ntabs, double scale,
+                         hipStream_t st);
 // Kernels transformed so far (0 without buffers).
 int near64_kernels(const Near64* f);
 // out[t] = the near zone of rho with kernel t, t < nout (written, not added);

@@ -37,6 +37,8 @@ struct Near64 {
   double2* yhat = nullptr;   // spectra of the slab's target planes (after rhat in one allocation)
   double2* khat[4] = {nullptr, nullptr, nullptr, nullptr};  // [F / 64][27][64] per kernel: the
                              // potential's after yhat, the accelerations' in an allocation of their own
+  double2* tmp = nullptr;    // [27][F] between the passes of the kernels' transforms, which so touch
+                             // neither spectra nor other kernels: solves that use those may be in flight
 };
 
 namespace {
@@ -505,19 +507,21 @@ hipError_t near64_create(int N, int s, Near64** out) {
   }
   const size_t ns = f->planes == nb ? nb : f->planes + 2;
   const hipError_t e =
-      hipMalloc(&f->rhat, ((ns + f->planes) * plane + (size_t)27 * f->F) * sizeof(double2));
+      hipMalloc(&f->rhat, ((ns + f->planes) * plane + (size_t)54 * f->F) * sizeof(double2));
   if (e != hipSuccess) {
     near64_destroy(f);
     return e;
   }
   f->yhat = f->rhat + ns * plane;
   f->khat[0] = f->yhat + f->planes * plane;
+  f->tmp = f->khat[0] + (size_t)27 * f->F;
   *out = f;
   return hipSuccess;
 }
 
-hipError_t near64_tables(Near64* f, const double* const* tabs, int ntabs, double scale, hipStream_t st) {
-  if (ntabs < 1 || ntabs > 4) return hipErrorInvalidValue;
+hipError_t near64_tables(Near64* f, const double* const* tabs, int first, int ntabs, double scale,
+                         hipStream_t st) {
+  if (first < 0 || ntabs < 1 || ntabs > 4) return hipErrorInvalidValue;
   const double sc = scale / (8.0 * f->s * f->s * f->s);  // the inverse transform is unnormalised
   const dim3 grid(nblk(f->F), 27);
   const size_t one = (size_t)27 * f->F;
@@ -535,11 +539,10 @@ hipError_t near64_tables(Near64* f, const double* const* tabs, int ntabs, double
       for (int t = 1; t < 4; ++t) f->khat[t] = k + (t - 1) * one;
     }
   }
-  for (int t = 0; t < ntabs && e == hipSuccess; ++t) {
-    // the passes' [27][F] values go through the spectra (at least 64 leaves)
-    k_kz64<<<grid, kThreads, 0, st>>>(tabs[t], f->s, f->rhat);
-    k_kaxis64<<<grid, kThreads, 0, st>>>(f->rhat, f->s, 1, 1.0, f->yhat);
-    k_kaxis64<<<grid, kThreads, 0, st>>>(f->yhat, f->s, 0, sc, f->khat[t]);
+  for (int t = first; t < ntabs && e == hipSuccess; ++t) {
+    k_kz64<<<grid, kThreads, 0, st>>>(tabs[t], f->s, f->khat[t]);
+    k_kaxis64<<<grid, kThreads, 0, st>>>(f->khat[t], f->s, 1, 1.0, f->tmp);
+    k_kaxis64<<<grid, kThreads, 0, st>>>(f->tmp, f->s, 0, sc, f->khat[t]);
     e = hipGetLastError();
   }
   f->ntabs = e == hipSuccess ? std::max(f->ntabs, ntabs) : 0;

@@ -385,14 +385,14 @@ pfmm_status create_near64(pfmm_plan_s* pl) {
   return e == hipSuccess ? PFMM_OK : hip_fail(e, "FP64 near zone");
 }
 
-// Its transformed kernels: G's, and the accelerations' when these come from the
-// expansion (without the memory for those, solves that need them keep the
-// block-Toeplitz sum).
-pfmm_status refresh_near64(pfmm_plan_s* pl) {
+// Its transformed kernels from table `first` on (0: G's, then the accelerations'
+// when these come from the expansion; without the memory for those, solves that
+// need them keep the block-Toeplitz sum).
+pfmm_status refresh_near64(pfmm_plan_s* pl, int first) {
   if (!pl->n64) return PFMM_OK;
   const double* tabs[4] = {pl->ntab64, pl->ndtab64[0], pl->ndtab64[1], pl->ndtab64[2]};
   const double h3 = 1.0 / ((double)pl->N * pl->N * pl->N);
-  hipError_t e = near64_tables(pl->n64, tabs, pl->accel_mode ? 4 : 1, h3, pl->stream);
+  hipError_t e = near64_tables(pl->n64, tabs, first, pl->accel_mode ? 4 : 1, h3, pl->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(pl->stream);
   return e == hipSuccess ? PFMM_OK : hip_fail(e, "FP64 near zone");
 }
@@ -448,14 +448,15 @@ hipError_t refresh_zones(pfmm_plan_s* pl) {
   return e;
 }
 
-// Every transformed near-zone kernel follows the tables.
-pfmm_status refresh_near(pfmm_plan_s* pl) {
+// Every transformed near-zone kernel (`first` as above) follows the tables.
+pfmm_status refresh_near(pfmm_plan_s* pl, int first) {
   const pfmm_status r = refresh_near_fft(pl);
-  return r == PFMM_OK ? refresh_near64(pl) : r;
+  return r == PFMM_OK ? refresh_near64(pl, first) : r;
 }
 
-// Near-zone acceleration kernels of the plan's G (allocated on first use)
-pfmm_status tabulate_accel_tables(pfmm_plan_s* pl) {
+// Near-zone acceleration kernels of the plan's G (allocated on first use);
+// `first` = 0 where G's own table is new too.
+pfmm_status tabulate_accel_tables(pfmm_plan_s* pl, int first) {
   const int Cn = 2 * pl->s - 1;
   const int64_t n = cube(2 * Cn + 1);
   hipError_t e = hipSuccess;
@@ -474,7 +475,7 @@ pfmm_status tabulate_accel_tables(pfmm_plan_s* pl) {
   }
   if (e == hipSuccess) e = hipStreamSynchronize(pl->stream);
   if (e != hipSuccess) return hip_fail(e, "acceleration tables");
-  return refresh_near(pl);
+  return refresh_near(pl, first);
 }
 
 hipError_t gstar_base(pfmm_plan_s* pl);
@@ -512,7 +513,7 @@ pfmm_status tabulate_all(pfmm_plan_s* pl) {
   }
   e = refresh_zones(pl);  // and those of the zones' spectra
   if (e != hipSuccess) return hip_fail(e, "spectral zone kernels");
-  pfmm_status s0 = pl->accel_mode ? tabulate_accel_tables(pl) : refresh_near(pl);
+  pfmm_status s0 = pl->accel_mode ? tabulate_accel_tables(pl, 0) : refresh_near(pl, 0);
   if (s0 != PFMM_OK || !pl->gdelta) return s0;
   // G_* follows the new G: new uncorrected copies, the correction applied again
   e = gstar_base(pl);
@@ -862,9 +863,8 @@ pfmm_status pfmm_plan_set(pfmm_plan_t h, int option, const void* value, size_t b
           return fail(PFMM_ERR_UNSUPPORTED, "PFMM_PREC_FP64: the leaf's FP64 mesh transfers do not fit "
                                             "in 64 KiB of LDS at this leaf width and p");
       }
-      if (pl->prec == v) return PFMM_OK;
       pl->prec = v;
-      return refresh_near64(pl);
+      return PFMM_OK;
     }
     case PFMM_OPT_ZONES_FP32: {
       if (bytes != sizeof(int32_t)) return fail(PFMM_ERR_INVALID_ARG, "zones_fp32 is an int32");
@@ -955,7 +955,7 @@ pfmm_status pfmm_plan_set(pfmm_plan_t h, int option, const void* value, size_t b
         return fail(PFMM_ERR_INVALID_ARG, "unknown acceleration mode");
       pl->accel_mode = v;
       if (!v) return PFMM_OK;
-      const pfmm_status r = tabulate_accel_tables(pl);
+      const pfmm_status r = tabulate_accel_tables(pl, 1);
       if (r != PFMM_OK) pl->accel_mode = 0;
       return r;
     }
@@ -1021,9 +1021,8 @@ pfmm_status pfmm_plan_set(pfmm_plan_t h, int option, const void* value, size_t b
           return r;
         }
       }
-      if (pl->near_fft == v) return PFMM_OK;
       pl->near_fft = v;
-      return refresh_near64(pl);
+      return PFMM_OK;
     }
     case PFMM_OPT_FP64_LEVELS: {
       if (bytes != sizeof(int32_t)) return fail(PFMM_ERR_INVALID_ARG, "fp64 levels is an int32");
@@ -2701,7 +2700,7 @@ pfmm_status gstar_apply(pfmm_plan_s* pl) {
   if (e == hipSuccess) e = refresh_zones(pl);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   if (e != hipSuccess) return hip_fail(e, "apply G_*");
-  return refresh_near(pl);
+  return refresh_near(pl, 0);
 }
 
 // Forward solve with G_*, its PM potential, and the residual statistics.
