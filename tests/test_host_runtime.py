@@ -1,0 +1,103 @@
+"""The host side of the plan without a GPU: the library runs on a HIP runtime
+that executes nothing and records every call (fake_hip.cpp), in a process of its
+own.  Checked is what a result cannot show: which buffers are freed while the plan
+lives, what an option launches or waits for, and what orders kernels that share a
+buffer."""
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+PRELUDE = """
+import ctypes, sys
+sys.path.insert(0, %r)
+hip = ctypes.CDLL(sys.argv[1], ctypes.RTLD_GLOBAL)  # before the library: its HIP calls go here
+hip.fake_log.restype = ctypes.c_char_p
+hip.fake_used.restype = ctypes.c_size_t
+from paper_2011_07099_amd import pfmm
+lib = pfmm.load()
+GREEN, NEAR, PREC, M2L, ACCEL = pfmm.GREEN, pfmm.NEAR, pfmm.PREC, pfmm.M2L, pfmm.ACCEL
+
+def log():
+    return hip.fake_log().decode().splitlines()
+
+def of(lines, *kinds):
+    return [l for l in lines if l.split()[0] in kinds]
+
+def create(N, L, p, green="S"):
+    h = ctypes.c_void_p()
+    assert lib.pfmm_plan_create(N, L, p, GREEN[green], ctypes.byref(h)) == 0
+    return h
+
+def put(h, option, value):
+    v = (ctypes.c_double if isinstance(value, float) else ctypes.c_int32)(value)
+    return lib.pfmm_plan_set(h, option, ctypes.byref(v), ctypes.sizeof(v))
+
+def stream(h, s):
+    v = ctypes.c_void_p(s)
+    assert lib.pfmm_plan_set(h, pfmm.OPT_STREAM, ctypes.byref(v), 8) == 0
+
+A, B, C = (ctypes.c_void_p(x << 20) for x in (1 << 22, 1 << 23, 3 << 22))  # device addresses of arrays
+""" % ROOT
+
+
+@pytest.fixture(scope="module")
+def fake(tmp_path_factory):
+    cxx = shutil.which("g++") or shutil.which("amdclang++") or "/opt/rocm/bin/amdclang++"
+    out = str(tmp_path_factory.mktemp("fake") / "libfakehip.so")
+    subprocess.run([cxx, "-O1", "-shared", "-fPIC", "-o", out, os.path.join(HERE, "fake_hip.cpp")], check=True)
+    return out
+
+
+def run(fake, body):
+    from paper_2011_07099_amd import pfmm
+    if not os.path.exists(pfmm.LIB_PATH):
+        pytest.skip("libpfmm.so not built")
+    r = subprocess.run([sys.executable, "-c", PRELUDE + body, fake], capture_output=True, text=True,
+                       timeout=120)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+@pytest.mark.parametrize("N,L,p", [(64, 3, 8), (64, 2, 4), (128, 7, 6)])
+def test_options_free_nothing(fake, N, L, p):
+    """A captured solve holds the plan's buffers: only the plan's end frees them
+    (temporaries of a tabulation, made and freed in one call, aside)."""
+    run(fake, """
+h = create(%d, %d, %d)
+log()
+before = hip.fake_used()
+made = set()
+for option, value in ((pfmm.OPT_NEAR, 1), (pfmm.OPT_PRECISION, 2), (pfmm.OPT_PRECISION, 0), (pfmm.OPT_NEAR, 0),
+                      (pfmm.OPT_M2L, M2L["spectral"]), (pfmm.OPT_ACCEL, 1), (pfmm.OPT_NEAR, 1),
+                      (pfmm.OPT_M2L, M2L["gemm"]), (pfmm.OPT_PRECISION, 1), (pfmm.OPT_GS_A1, -0.1)):
+    if option == pfmm.OPT_NEAR and value and %d >> %d < 4:
+        continue                                    # rocFFT's plans need a device
+    assert put(h, option, value) == 0, (option, value, lib.pfmm_last_error())
+    lines = log()
+    here = {l.split()[1] for l in of(lines, "malloc")}
+    freed = {l.split()[1] for l in of(lines, "free")}
+    assert freed <= here, (option, value, freed - here)
+assert hip.fake_used() >= before
+assert lib.pfmm_plan_destroy(h) == 0
+assert hip.fake_used() == 0, hip.fake_used()
+""" % (N, L, p, N, L))
+
+
+def test_precision_and_near_zone_options_run_nothing(fake):
+    run(fake, """
+h = create(64, 3, 8)
+assert put(h, pfmm.OPT_NEAR, 1) == 0 and put(h, pfmm.OPT_NEAR, 0) == 0   # its buffers, on first use
+log()
+for option, value in ((pfmm.OPT_PRECISION, 1), (pfmm.OPT_NEAR, 1), (pfmm.OPT_PRECISION, 2),
+                      (pfmm.OPT_PRECISION, 0), (pfmm.OPT_NEAR, 0)):
+    assert put(h, option, value) == 0
+    assert log() == [], (option, value)
+assert put(h, pfmm.OPT_ACCEL, 1) == 0
+kernels = [l.split()[1] for l in of(log(), "launch")]
+assert sum("k_kz64" in k for k in kernels) == 3, kernels   # the accelerations', not G's own again
+""")
