@@ -976,10 +976,13 @@ pfmm_status pfmm_plan_set(pfmm_plan_t h, int option, const void* value, size_t b
           if (!f || m2l_spectral_levels(f) < pl->L) e = m2l_spectral_create(pl->L, pl->p, &f);
           if (e == hipErrorOutOfMemory) return fail(PFMM_ERR_OUT_OF_MEMORY, "spectral zone buffers");
           if (e != hipSuccess) return hip_fail(e, "spectral zone buffers");
-          pl->mspec = f;
           if (f != pl->zspec) e = m2l_spectral_tables(f, pl->tab64, pl->stream);
-          if (e == hipSuccess) e = m2l_spectral_set_f32(pl->mspec, pl->zones_f32, pl->stream);
-          if (e != hipSuccess) return hip_fail(e, "spectral zone kernels");
+          if (e == hipSuccess) e = m2l_spectral_set_f32(f, pl->zones_f32, pl->stream);
+          if (e != hipSuccess) {  // the plan never holds spectra without their kernels
+            if (f != pl->zspec) m2l_spectral_destroy(f);
+            return hip_fail(e, "spectral zone kernels");
+          }
+          pl->mspec = f;
         }
         pl->m2l_fft = 0;
         pl->m2l_spectral = 1;

@@ -101,3 +101,19 @@ assert put(h, pfmm.OPT_ACCEL, 1) == 0
 kernels = [l.split()[1] for l in of(log(), "launch")]
 assert sum("k_kz64" in k for k in kernels) == 3, kernels   # the accelerations', not G's own again
 """)
+
+
+def test_a_failed_spectral_option_leaves_no_spectra_without_kernels(fake):
+    """64^3 with one-cell leaves, p = 6: the option needs spectra of its own."""
+    run(fake, """
+h = create(64, 6, 6)
+used = hip.fake_used()
+hip.fake_fail_launches(1)
+assert put(h, pfmm.OPT_M2L, M2L["spectral"]) != 0
+hip.fake_fail_launches(0)
+assert hip.fake_used() == used
+log()
+assert lib.pfmm_solve(h, A, B, None) == 0            # the default zones, as before
+assert put(h, pfmm.OPT_M2L, M2L["spectral"]) == 0
+assert any("k_khat_z" in l for l in of(log(), "launch"))
+""")
