@@ -509,8 +509,8 @@ pfmm_status pfmm_solve_batch(int n, const pfmm_plan_t* plans, const float* const
  * the FMM approximates), by FP64 transforms of the mesh: exact up to FP64
  * rounding, rounded once to FP32.  Allocates its table and about 16 bytes per
  * cell of spectra on the first call; enqueued on the plan's stream.  Calls on
- * one plan share the spectrum: a call after a change of PFMM_OPT_STREAM waits
- * for the last one; a captured call must not overlap with another.
+ * one plan share the spectrum: a call, and a change of G, waits for the last one
+ * on whatever stream it runs; a captured call must not overlap with another.
  */
 pfmm_status pfmm_plan_direct(pfmm_plan_t plan, const float* density, float* potential);
 

@@ -143,9 +143,9 @@ struct pfmm_plan_s {
   double* dtab64 = nullptr;       // G at the mesh separations, |j_i| <= dC = N / 2
   int dC = 0;
   double2* dghat = nullptr;       // its transform
-  double2* dwork = nullptr;       // the density's spectrum: calls on other streams wait
-  hipStream_t dstream = nullptr;  // for ev_direct of the last one
-  hipEvent_t ev_direct = nullptr;
+  double2* dwork = nullptr;       // the density's spectrum: whoever writes it or dghat
+  hipEvent_t ev_direct = nullptr; // waits for ev_direct of the last convolution
+  std::mutex dmutex;              // a convolution's launches are not interleaved with another's
   std::vector<void*> owned;
   // stage timing (PFMM_OPT_PROFILE): a ring of event sets, one per solve;
   // each timed launch (or group of launches) has a start and an end event
@@ -454,6 +454,14 @@ pfmm_status refresh_near(pfmm_plan_s* pl, int first) {
   return r == PFMM_OK ? refresh_near64(pl, first) : r;
 }
 
+// The transform of the direct solve's table, after the last convolution on
+// whatever stream it runs: it reads dghat and keeps its spectrum in dwork.
+hipError_t refresh_direct(pfmm_plan_s* pl) {
+  std::lock_guard<std::mutex> lk(pl->dmutex);
+  const hipError_t e = hipStreamWaitEvent(pl->stream, pl->ev_direct, 0);
+  return e == hipSuccess ? pm_kernel(pl->dtab64, pl->dC, pl->N, pl->dwork, pl->dghat, pl->stream) : e;
+}
+
 // Near-zone acceleration kernels of the plan's G (allocated on first use);
 // `first` = 0 where G's own table is new too.
 pfmm_status tabulate_accel_tables(pfmm_plan_s* pl, int first) {
@@ -503,7 +511,7 @@ pfmm_status tabulate_all(pfmm_plan_s* pl) {
   if (e != hipSuccess) return hip_fail(e, "tabulate near table");
   if (pl->dtab64) {  // the direct solve's table, once it exists, follows G too
     e = tabulate_green(green_spec(pl), pl->N, pl->dC, pl->N, 1.0 / pl->N, pl->dtab64, pl->stream);
-    if (e == hipSuccess) e = pm_kernel(pl->dtab64, pl->dC, pl->N, pl->dwork, pl->dghat, pl->stream);
+    if (e == hipSuccess) e = refresh_direct(pl);
     if (e == hipSuccess) e = hipStreamSynchronize(pl->stream);
     if (e != hipSuccess) return hip_fail(e, "direct solve tables");
   }
@@ -2537,15 +2545,15 @@ pfmm_status direct_prepare(pfmm_plan_s* pl) {
 }
 
 // The exact periodic convolution with the plan's direct table (prepared).
-// Calls on one plan share its spectrum: a call on another stream than the last
-// one waits for it (a captured call does not: its order is the caller's).
+// Calls on one plan share its spectrum: each waits for the last one, whatever
+// its stream was (a handle says little: a new stream can have a destroyed one's;
+// a captured call does not wait: its order is the caller's).
 hipError_t direct_launch(pfmm_plan_s* pl, const float* rho, float* phi) {
+  std::lock_guard<std::mutex> lk(pl->dmutex);
   const bool cap = capturing(pl->stream);
-  hipError_t e = hipSuccess;
-  if (!cap && pl->dstream != pl->stream) e = hipStreamWaitEvent(pl->stream, pl->ev_direct, 0);
+  hipError_t e = cap ? hipSuccess : hipStreamWaitEvent(pl->stream, pl->ev_direct, 0);
   if (e == hipSuccess) e = pm_convolve(rho, pl->dghat, pl->dwork, pl->N, phi, pl->stream);
   if (e == hipSuccess && !cap) e = hipEventRecord(pl->ev_direct, pl->stream);
-  if (!cap) pl->dstream = pl->stream;
   return e;
 }
 
@@ -2699,7 +2707,7 @@ pfmm_status gstar_apply(pfmm_plan_s* pl) {
     e = make_windows(pl->ntab64, 2 * pl->s - 1, kNearTerms, pl->nwin, st);
   if (e == hipSuccess)
     e = apply_correction(pl->gd0, pl->gdelta, pl->gduidx, ndir, pl->dtab64, nullptr, st);
-  if (e == hipSuccess) e = pm_kernel(pl->dtab64, pl->dC, pl->N, pl->dwork, pl->dghat, st);
+  if (e == hipSuccess) e = refresh_direct(pl);
   if (e == hipSuccess) e = refresh_zones(pl);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   if (e != hipSuccess) return hip_fail(e, "apply G_*");

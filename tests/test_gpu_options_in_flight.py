@@ -62,3 +62,44 @@ def test_options_do_not_disturb_a_running_solve(then):
         getattr(pl, then[0])(then[1])
         torch.cuda.synchronize()
     assert all(torch.equal(o, ref) for o in outs)
+
+
+@pytest.mark.parametrize("change", ["a1", "gstar"])
+def test_a_new_g_waits_for_a_running_convolution(change):
+    """direct() queued behind other work on one stream, then a new G set on
+    another: the queued convolution has the old G, the next one the new."""
+    import torch
+    from paper_2011_07099_amd.pfmm import Plan
+    s, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+    N = 64
+    rho, big = density(N, 923), density(128, 924)
+    acc = torch.empty_like(big), torch.empty((3, 128, 128, 128), device="cuda")
+    ref, new, out, after = (torch.empty_like(rho) for _ in range(4))
+
+    def set_g(pl):
+        if change == "a1":
+            pl.set_a1(-0.2)
+        else:
+            n = pl.gstar_params()
+            pl.set_gstar(1e-2 * np.random.default_rng(5).standard_normal(n).astype(np.float32))
+    with Plan(N, 4, 2, "S", a1=-0.125) as pl:
+        pl.direct(rho, ref)
+        set_g(pl)
+        pl.direct(rho, new)
+        torch.cuda.synchronize()
+    assert not torch.equal(ref, new)
+    with Plan(128, 3, 8, "S1", stream=s, accel="expansion") as work, \
+            Plan(N, 4, 2, "S", a1=-0.125, stream=s2) as pl:
+        pl.direct(rho, out)                # its tables
+        if change == "gstar":
+            pl.set_gstar(None)             # its buffers
+        torch.cuda.synchronize()
+        busy(work, big, acc, s)
+        pl.set_stream(s)
+        pl.direct(rho, out)
+        assert not s.query()
+        pl.set_stream(s2)
+        set_g(pl)
+        pl.direct(rho, after)
+        torch.cuda.synchronize()
+    assert torch.equal(out, ref) and torch.equal(after, new)

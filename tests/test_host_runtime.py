@@ -117,3 +117,25 @@ assert lib.pfmm_solve(h, A, B, None) == 0            # the default zones, as bef
 assert put(h, pfmm.OPT_M2L, M2L["spectral"]) == 0
 assert any("k_khat_z" in l for l in of(log(), "launch"))
 """)
+
+
+def test_what_writes_the_convolution_s_spectrum_waits_for_the_last_one(fake):
+    """Every writer of the shared spectrum and of G's transform waits for the
+    last convolution, also on a stream whose handle it has seen before."""
+    run(fake, """
+h = create(32, 3, 4)
+stream(h, 0x100)
+assert lib.pfmm_plan_direct(h, A, B) == 0
+event = of(log(), "record")[-1].split()[1]
+for act in (lambda: lib.pfmm_plan_direct(h, A, C),                       # the same handle
+            lambda: (stream(h, 0x200), lib.pfmm_plan_direct(h, A, B))[1],
+            lambda: (stream(h, 0x100), put(h, pfmm.OPT_GS_A1, -0.1))[1]):
+    assert act() == 0
+    lines = log()
+    first = next(i for i, l in enumerate(lines) if "k_pm_" in l or "k_mesh" in l)
+    st = lines[first].split()[-1]
+    assert "wait %s %s" % (st, event) in lines[:first], lines
+hip.fake_capture(ctypes.c_void_p(0x100))              # a captured call has the caller's order
+assert lib.pfmm_plan_direct(h, A, B) == 0
+assert of(log(), "wait", "record") == []
+""")
