@@ -375,9 +375,10 @@ int m2l_spectral_levels(const M2LSpectral* f);  // L
 // Transform the kernels of every offset in [-3, 3]^3 from the FP64 level
 // tables; synchronises `st`.
 hipError_t m2l_spectral_tables(M2LSpectral* f, const std::vector<double*>& tab64, hipStream_t st);
-// Whether the 16^3 leaf level's FP32 kernel values are kept (see cols32);
-// synchronises `st` where that changes.
-hipError_t m2l_spectral_set_f32(M2LSpectral* f, int on, hipStream_t st);
+// Keep the 16^3 leaf level's FP32 kernel values (see cols32; L = 4) from now on:
+// they follow every change of the tables, so that options and captured solves
+// use them at any time.  Synchronises `st` the first time.
+hipError_t m2l_spectral_keep_f32(M2LSpectral* f, hipStream_t st);
 // Pl (+)= the level-l zone sums of Ml (Sec. 2's zones, or the isolated
 // twin's); m64 / p64: the buffers hold doubles.  cols32, with the FP32 kernel
 // values kept: the periodic 16^3 leaf level's stencil (L = 4) sums each zone

@@ -655,22 +655,22 @@ hipError_t m2l_spectral_create(int L, int p, M2LSpectral** out) {
 
 namespace {
 hipError_t khat_f32(const M2LSpectral* f, hipStream_t st) {
-  if (!f->f32 || !f->khatT32) return hipSuccess;
   k_khat_f32<<<nblk(f->F * kKT), kThreads, 0, st>>>(f->khatT[f->L], f->F * kKT, f->khatT32);
   return hipGetLastError();
 }
 }  // namespace
 
-hipError_t m2l_spectral_set_f32(M2LSpectral* f, int on, hipStream_t st) {
-  if (f->f32 == on) return hipSuccess;
-  f->f32 = on;
-  const hipError_t e = khat_f32(f, st);
-  return e == hipSuccess ? hipStreamSynchronize(st) : e;
+hipError_t m2l_spectral_keep_f32(M2LSpectral* f, hipStream_t st) {
+  if (f->f32 || !f->khatT32) return hipSuccess;
+  hipError_t e = khat_f32(f, st);
+  if (e == hipSuccess) e = hipStreamSynchronize(st);
+  f->f32 = e == hipSuccess;
+  return e;
 }
 
 hipError_t m2l_spectral_tables(M2LSpectral* f, const std::vector<double*>& tab64, hipStream_t st) {
   hipError_t e = with_p<1, 10>(f->p, [&](auto P) { return khat_levels<decltype(P)::value>(f, tab64, st); });
-  if (e == hipSuccess) e = khat_f32(f, st);
+  if (e == hipSuccess && f->f32) e = khat_f32(f, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   return e;
 }

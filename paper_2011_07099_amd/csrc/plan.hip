@@ -880,10 +880,6 @@ pfmm_status pfmm_plan_set(pfmm_plan_t h, int option, const void* value, size_t b
       std::memcpy(&v, value, sizeof v);
       if (v != 0 && v != 1) return fail(PFMM_ERR_INVALID_ARG, "zones_fp32 is 0 or 1");
       pl->zones_f32 = v;
-      if (pl->mspec) {
-        const hipError_t e = m2l_spectral_set_f32(pl->mspec, v, pl->stream);
-        if (e != hipSuccess) return hip_fail(e, "FP32 zone kernels");
-      }
       return PFMM_OK;
     }
     case PFMM_OPT_FOLD: {
@@ -985,7 +981,7 @@ pfmm_status pfmm_plan_set(pfmm_plan_t h, int option, const void* value, size_t b
           if (e == hipErrorOutOfMemory) return fail(PFMM_ERR_OUT_OF_MEMORY, "spectral zone buffers");
           if (e != hipSuccess) return hip_fail(e, "spectral zone buffers");
           if (f != pl->zspec) e = m2l_spectral_tables(f, pl->tab64, pl->stream);
-          if (e == hipSuccess) e = m2l_spectral_set_f32(f, pl->zones_f32, pl->stream);
+          if (e == hipSuccess) e = m2l_spectral_keep_f32(f, pl->stream);
           if (e != hipSuccess) {  // the plan never holds spectra without their kernels
             if (f != pl->zspec) m2l_spectral_destroy(f);
             return hip_fail(e, "spectral zone kernels");

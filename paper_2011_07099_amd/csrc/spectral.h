@@ -17,7 +17,7 @@ struct M2LSpectral {
   double2* out = nullptr;        // [F][nodes] of the level being summed
   std::vector<double2*> khatT;   // per level: [F][kKT] kernel values, offsets of [-3, 3]^3 innermost
   float2* khatT32 = nullptr;     // the leaf level's khatT in FP32 (the FP32 16^3 stencil)
-  int f32 = 0;                   // the 16^3 level's stencil in FP32 with FP64 column totals
+  int f32 = 0;                   // khatT32 follows khatT (kept from the spectral option on)
   void* mem = nullptr;           // the one allocation that holds the arrays above
 };
 

@@ -113,3 +113,26 @@ def test_a_captured_solve_follows_g_after_the_options(then):
         getattr(pl, then[0])(then[1])
         pl.set_a1(-0.2)
         replays(g, [phi], [ref], 1 << 24)
+
+
+def test_a_captured_solve_in_fp32_columns_follows_g_after_the_option():
+    """FP32 columns of the 16^3 leaf level: captured with the option on, then the
+    option off and a new G; the replay has every kernel of the new G."""
+    import torch
+    from paper_2011_07099_amd.pfmm import Plan
+    N, L, p = 64, 4, 4
+    s = torch.cuda.Stream()
+    rho = density(N, 905)
+    phi, ref = torch.empty_like(rho), torch.empty_like(rho)
+    kw = dict(m2l="spectral", zones_fp32=True, stream=s)
+    with Plan(N, L, p, "S", a1=-0.2, **kw) as pl:
+        with torch.cuda.stream(s):
+            pl.solve(rho, ref)
+        torch.cuda.synchronize()
+    with Plan(N, L, p, "S", a1=-0.1, **kw) as pl:
+        with torch.cuda.stream(s):
+            pl.solve(rho, phi)
+        g = captured(pl, rho, phi, None, s)
+        pl.set_zones_fp32(False)
+        pl.set_a1(-0.2)
+        replays(g, [phi], [ref], 1 << 24)

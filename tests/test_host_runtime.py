@@ -139,3 +139,16 @@ hip.fake_capture(ctypes.c_void_p(0x100))              # a captured call has the 
 assert lib.pfmm_plan_direct(h, A, B) == 0
 assert of(log(), "wait", "record") == []
 """)
+
+
+def test_fp32_columns_option_runs_nothing(fake):
+    run(fake, """
+h = create(64, 4, 4)
+assert put(h, pfmm.OPT_M2L, M2L["spectral"]) == 0
+log()
+for v in (1, 0, 1):
+    assert put(h, pfmm.OPT_ZONES_FP32, v) == 0
+    assert log() == []
+assert put(h, pfmm.OPT_ZONES_FP32, 0) == 0 and put(h, pfmm.OPT_GS_A1, -0.1) == 0
+assert any("k_khat_f32" in l for l in log())          # the FP32 kernels follow G, the option on or off
+""")
