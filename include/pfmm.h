@@ -219,9 +219,10 @@ typedef enum {
    * a cyclic convolution on the doubled grid (exact up to FP64 rounding;
    * buffers of about 140 bytes per cell, at most 3 GiB unless two planes of
    * leaves need more, made with the plan and kept while it lives, also when
-   * other routes are selected: a captured solve may use them).  Other leaf edges, batches, and plans without the memory
-   * for those buffers use a block-Toeplitz GEMM (matrix cores or the portable
-   * kernel, as PFMM_OPT_PRECISION selects).  Any alignment. */
+   * other routes are selected: a captured solve may use them).  Other leaf edges,
+   * batches, and plans made when those buffers would leave less than a quarter
+   * of the device's memory free use a block-Toeplitz GEMM (matrix cores or the
+   * portable kernel, as PFMM_OPT_PRECISION selects).  Any alignment. */
   PFMM_NEAR_DIRECT = 0,
   /* FFT convolution on the doubled grid, the route the paper takes (Sec. 2
    * and 3): each leaf's cells zero-padded to (2s)^3 and transformed once
@@ -245,9 +246,10 @@ typedef enum {
    * >= 3 sum it in FP64, per frequency as PFMM_M2L_SPECTRAL does (exact up to
    * FP64 rounding; every level in PFMM_PREC_FP32 and PFMM_PREC_FP64, the levels
    * kept in FP64 in PFMM_PREC_BF16X3), on the levels whose spectra fit in 3 GiB
-   * (allocated with the plan: 0.3 GB at 16^3 nodes, p = 8).  Other levels,
-   * batches, and plans without that memory use block-Toeplitz GEMMs (matrix
-   * cores or the portable kernel, as PFMM_OPT_PRECISION selects). */
+   * (allocated with the plan, where a quarter of the device's memory stays free
+   * beside them: 0.3 GB at 16^3 nodes, p = 8).  Other levels, batches, and plans
+   * without that memory use block-Toeplitz GEMMs (matrix cores or the portable
+   * kernel, as PFMM_OPT_PRECISION selects). */
   PFMM_M2L_GEMM = 0,
   /* The Hierarchical Particle-Mesh form the paper runs (Sec. 2): per target
    * node the effective masses of its whole zone on one uniform grid, one FFT

@@ -345,7 +345,8 @@ hipError_t near_fft_end(NearFft* f, float* out0, const LeafTree& tree, hipStream
 // ---------------------------------------------------------------------------
 struct Near64;
 // Buffers for N^3 cells in leaves of s^3 (about 140 bytes per cell, at most
-// 3 GiB unless two leaf planes need more); allocates.
+// 3 GiB unless two leaf planes need more), near64_bytes in one allocation.
+size_t near64_bytes(int N, int s);
 hipError_t near64_create(int N, int s, Near64** out);
 void near64_destroy(Near64* f);
 // Transform the near-zone kernels of the FP64 tables first .. ntabs - 1 (ntabs 1

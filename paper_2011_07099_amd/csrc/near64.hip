@@ -33,6 +33,7 @@ struct Near64 {
   int F = 0;                 // (2s)^2 (s + 1) frequencies per leaf
   int ntabs = 0;             // kernels transformed so far
   int planes = 0;            // target leaf planes per slab (nb: the whole box, no slabs)
+  int sources = 0;           // source leaf planes per slab
   double2* rhat = nullptr;   // spectra of the slab's source planes
   double2* yhat = nullptr;   // spectra of the slab's target planes (after rhat in one allocation)
   double2* khat[4] = {nullptr, nullptr, nullptr, nullptr};  // [F / 64][27][64] per kernel: the
@@ -486,10 +487,9 @@ void near64_destroy(Near64* f) {
   delete f;
 }
 
-hipError_t near64_create(int N, int s, Near64** out) {
-  *out = nullptr;
-  if (s != 4 && s != 8 && s != 16) return hipErrorInvalidValue;
-  Near64* f = new Near64;
+namespace {
+// The sizes of the buffers, and the bytes they take.
+size_t shape(int N, int s, Near64* f) {
   f->N = N;
   f->s = s;
   f->nb = N / s;
@@ -505,14 +505,27 @@ hipError_t near64_create(int N, int s, Near64** out) {
     f->planes = fit >= 6 ? (int)((fit - 2) / 2 & ~(size_t)1) : 2;
     if (f->planes + 2 >= nb) f->planes = nb;
   }
-  const size_t ns = f->planes == nb ? nb : f->planes + 2;
-  const hipError_t e =
-      hipMalloc(&f->rhat, ((ns + f->planes) * plane + (size_t)54 * f->F) * sizeof(double2));
+  f->sources = f->planes == nb ? nb : f->planes + 2;
+  return ((size_t)(f->sources + f->planes) * plane + (size_t)54 * f->F) * sizeof(double2);
+}
+}  // namespace
+
+size_t near64_bytes(int N, int s) {
+  Near64 f;
+  return shape(N, s, &f);
+}
+
+hipError_t near64_create(int N, int s, Near64** out) {
+  *out = nullptr;
+  if (s != 4 && s != 8 && s != 16) return hipErrorInvalidValue;
+  Near64* f = new Near64;
+  const hipError_t e = hipMalloc(&f->rhat, shape(N, s, f));
   if (e != hipSuccess) {
     near64_destroy(f);
     return e;
   }
-  f->yhat = f->rhat + ns * plane;
+  const size_t plane = (size_t)f->nb * f->nb * f->F;
+  f->yhat = f->rhat + f->sources * plane;
   f->khat[0] = f->yhat + f->planes * plane;
   f->tmp = f->khat[0] + (size_t)27 * f->F;
   *out = f;

@@ -368,6 +368,19 @@ pfmm_status refresh_near_fft(pfmm_plan_s* pl) {
   return PFMM_OK;
 }
 
+// Whether `bytes` of buffers that a plan can do without may be taken: a quarter of
+// the card stays free beside them, for what needs no less than memory (more
+// plans, training, the caller's arrays).  With less than that the plan keeps the
+// products, which need no buffers.
+bool spare_memory(size_t bytes) {
+  size_t left = 0, all = 0;
+  if (hipMemGetInfo(&left, &all) != hipSuccess) {
+    (void)hipGetLastError();
+    return true;  // unknown: the allocation itself will tell
+  }
+  return left >= bytes + all / 4;
+}
+
 // The FP64 near zone (direct, or FP64 precision whatever PFMM_OPT_NEAR says) at
 // the leaf edges it serves, made with the plan; without the memory for it the
 // plan keeps the block-Toeplitz sum.  Split precision takes it too: at 256^3, s =
@@ -377,6 +390,7 @@ pfmm_status refresh_near_fft(pfmm_plan_s* pl) {
 // tables do.
 pfmm_status create_near64(pfmm_plan_s* pl) {
   if (pl->s != 4 && pl->s != 8 && pl->s != 16) return PFMM_OK;
+  if (!spare_memory(near64_bytes(pl->N, pl->s))) return PFMM_OK;
   const hipError_t e = near64_create(pl->N, pl->s, &pl->n64);
   if (e == hipErrorOutOfMemory) {
     (void)hipGetLastError();
@@ -430,7 +444,7 @@ pfmm_status create_zones(pfmm_plan_s* pl) {
   if (pl->p < kZoneMinP) return PFMM_OK;
   int top = pl->L;
   while (top >= 2 && m2l_spectral_bytes(top, pl->p) > ((size_t)3 << 30)) --top;
-  if (top < 2) return PFMM_OK;
+  if (top < 2 || !spare_memory(m2l_spectral_bytes(top, pl->p))) return PFMM_OK;
   const hipError_t e = m2l_spectral_create(top, pl->p, &pl->zspec);
   if (e == hipSuccess) pl->zone_top = top;
   if (e == hipErrorOutOfMemory) {

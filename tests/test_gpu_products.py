@@ -1,0 +1,65 @@
+"""Single solves by block-Toeplitz products, which plans use that are made while
+little memory is free (their transforms' buffers would leave less than a quarter
+of the card): zones on the FP64 matrix cores (p = 8) and in the portable kernel,
+near zones in FP64, FP32 and split BF16, against the reference FMM.
+
+In FP64 what is left is the FP32 result: three roundings of 2^-24 of values up to
+the largest |phi|, 2.5e-7.  FP32 near zone (every tree level in FP64): the terms
+of one offset, 8^3 at most, are summed in FP32, 512 x 2^-24 = 3.1e-5 of their absolute
+sum, which all of one sign is the sum itself; 5e-5 with the rounded operands.
+Split BF16, two terms an operand: 2^-16 a product, 1e-4 with both operands' and
+the sums' rounding; 2e-4 for accelerations, whose terms have both signs."""
+import numpy as np
+import pytest
+
+from oracle import fmm as ofmm
+from paper_2011_07099_amd import fields
+
+from gpu_util import f32, rel_max
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture
+def full_card():
+    """Somewhat more than three quarters of the card's memory held."""
+    import torch
+    torch.cuda.empty_cache()
+    free, total = torch.cuda.mem_get_info()
+    hold = torch.empty(free - total // 4 + (2 << 30), dtype=torch.uint8, device="cuda")
+    assert torch.cuda.mem_get_info()[0] < total // 4
+    yield
+    del hold
+    torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("N,L,p,precision,iso,accel,tol", [
+    (64, 3, 8, "fp64", False, None, 2.5e-7),      # zones on the FP64 matrix cores
+    (32, 3, 8, "fp64", True, None, 2.5e-7),       # the same, isolated; s = 4
+    (32, 3, 5, "fp64", False, 2.5e-7, 2.5e-7),    # portable, an odd gridlet
+    (32, 2, 4, "fp64", True, 2.5e-7, 2.5e-7),     # s = 8 isolated
+    (64, 2, 4, "fp32", False, 5e-5, 5e-5),        # s = 16
+    (32, 3, 3, "fp32", True, None, 5e-5),
+    (64, 3, 8, "bf16x3", False, None, 1e-4),      # split near zone, s = 8
+    (64, 2, 8, "bf16x3", True, 2e-4, 1e-4),       # s = 16
+])
+def test_products_match_the_reference(full_card, N, L, p, precision, iso, accel, tol):
+    import torch
+    from paper_2011_07099_amd.pfmm import Plan
+    green = "X" if iso else "S1"
+    rho = f32(fields.lognormal(N, 1.5, 1.0, seed=941 + N + p))
+    r = torch.from_numpy(rho.astype(np.float32)).cuda()
+    phi = torch.empty_like(r)
+    acc = torch.empty((3, N, N, N), dtype=torch.float32, device="cuda") if accel else None
+    with Plan(N, L, p, green, isolated=iso, precision=precision, fp64_levels=30,
+              accel="expansion" if accel else "fd4") as pl:
+        pl.solve(r, phi, acc)
+        torch.cuda.synchronize()
+    if accel:
+        ref_a, ref = ofmm.fmm_accel(rho, L, p, green, periodic=not iso)
+        ea = rel_max(acc.cpu().numpy().astype(np.float64), ref_a)
+    else:
+        ref, ea = ofmm.fmm(rho, L, p, green, periodic=not iso), 0.0
+    e = rel_max(phi.cpu().numpy().astype(np.float64), ref)
+    print("products", (N, L, p, precision, iso), "potential %.3e accelerations %.3e" % (e, ea))
+    assert e < tol and (not accel or ea < accel)

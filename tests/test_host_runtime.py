@@ -152,3 +152,29 @@ for v in (1, 0, 1):
 assert put(h, pfmm.OPT_ZONES_FP32, 0) == 0 and put(h, pfmm.OPT_GS_A1, -0.1) == 0
 assert any("k_khat_f32" in l for l in log())          # the FP32 kernels follow G, the option on or off
 """)
+
+
+def test_optional_buffers_leave_a_quarter_of_the_card(fake):
+    """Plans on a small card: the first take the transforms' buffers, and later
+    ones, made where these would leave less than a quarter free, use the products
+    instead of failing; what such plans allocate by themselves still fits."""
+    run(fake, """
+total = 2 << 30
+hip.fake_total(ctypes.c_size_t(total))
+routes, plans = [], []
+while hip.fake_used() < 0.9 * total and len(plans) < 40:
+    h = create(64, 3, 8)
+    plans.append(h)
+    log()
+    assert lib.pfmm_solve(h, A, B, None) == 0
+    kernels = " ".join(of(log(), "launch"))
+    routes.append(("k_fwd64" in kernels, "k_toep" in kernels))
+    if "k_fwd64" in kernels:
+        assert hip.fake_used() <= 0.75 * total
+assert routes[0] == (True, False) and routes[-1] == (False, True), routes
+assert put(plans[-1], pfmm.OPT_ACCEL, 1) == 0 and put(plans[-1], pfmm.OPT_PRECISION, 2) == 0
+assert lib.pfmm_solve(plans[-1], A, B, C) == 0
+for h in plans:
+    assert lib.pfmm_plan_destroy(h) == 0
+assert hip.fake_used() == 0
+""")
