@@ -16,9 +16,9 @@ Prints one JSON line:
     timed run of the same number of steps with every stage alone on the
     device ("serial"); the roofline of the dominant single kernel uses its
     serial duration, with its live one beside it;
-  - m2l_mfma: the default (GEMM) interaction zones in split precision, on the
-    matrix cores, timed in the same run on the same density, per level
-    against the peak of the matrix-core instruction it uses;
+  - m2l_mfma: the default (GEMM) interaction zones in split precision, timed
+    in the same run on the same density, per level against the peak of the unit
+    its sums run on; the utilisation counts the levels on the matrix cores;
   - the CPU FP64 oracle timed on a bounded sample of the same workload (which
     also checks the GPU potential: sampled cells against the reference FMM,
     the full mesh against PM with the same G).
@@ -391,13 +391,13 @@ def table_bench(args):
 
 def m2l_bench(args):
     """The interaction zones (Eq. 6) three ways on the headline mesh (256^3,
-    L = 4, G_S1, the same density): the block-Toeplitz GEMM of this library
-    (FP32 portable kernel, and split BF16 on the matrix cores at p = 8), the
-    HPM form the paper runs (Sec. 2: per target node one FFT convolution of
-    its zone's effective masses with G, rocFFT), and the spectral stencils
-    (per-node transforms, FP64), at p = 4, 6, 8.  Levels
-    2-3 are FP64 in every variant (FP64 matrix cores at p = 8, FP64
-    transforms for the FFT).  Per-level medians of the profiled stage times
+    L = 4, G_S1, the same density): the default zones of this library (FP32
+    precision: per-node transforms in FP64 as the spectral option; split
+    precision at p = 8: a block-Toeplitz GEMM of split BF16 on the matrix cores at
+    the leaf level), the HPM form the paper runs (Sec. 2: per target node one
+    FFT convolution of its zone's effective masses with G, rocFFT), and the
+    spectral stencils (per-node transforms, FP64), at p = 4, 6, 8.  Levels
+    2-3 are FP64 in every variant.  Per-level medians of the profiled stage times
     over `steps` solves; `value` is the FFT-to-GEMM time ratio of all levels
     at p = 8 with the default (split) precision."""
     import torch
@@ -526,6 +526,13 @@ def kernel_table(plan, L, near_fft, spectral):
     return out
 
 
+def zone_sum_unit(lv):
+    """(unit, flops issued per algorithmic flop) of a periodic level's FP64 sums
+    per frequency: the 4^3 and 16^3 levels on the vector ALUs, the others as octet
+    products on the matrix cores, which issue 216 offsets for the 189 of a zone."""
+    return ("f64 valu", 1) if lv in (2, 4) else ("f64 mfma", 216 / 189)
+
+
 def kernel_work(name, N, L, p, route=None):
     """Algorithmic work of one launch of a kernel: (flops, unit, bytes,
     products).  Default route (spectral zones, FFT near zone): flops count 8
@@ -537,8 +544,9 @@ def kernel_work(name, N, L, p, route=None):
     offset and target node, 2 s^6 per neighbour leaf and target leaf, on the unit
     the precision puts them on (the other levels of GEMM zones and, at s = 4, 8,
     16, the direct near zone sum per frequency in FP64); `products`
-    is the number of bf16 products the split issues per algorithmic product
-    (the matrix cores' peak applies to issued flops)."""
+    is the number of products issued per algorithmic product: six bf16 ones of
+    the split zones, 216 / 189 of the octets (the matrix cores' peak applies to
+    issued flops)."""
     s = N >> L
     route = route or {"m2l": "spectral", "near": "fft", "precision": "bf16x3"}
     if name.startswith("m2l L") and len(name.split()) == 2 and route["m2l"] == "gemm":
@@ -546,11 +554,12 @@ def kernel_work(name, N, L, p, route=None):
         fl = (37 if lv == 2 else 189) * 2.0 * p ** 6 * 8 ** lv
         if route["precision"] == "bf16x3" and p == 8 and lv not in FP64_LEVELS:
             return fl, "bf16 mfma", None, 6
-        # p >= 3: FP64 transforms and a sum per frequency on the FP64 matrix
-        # cores; gridlets in and out, spectra out and in twice
+        # p >= 3: FP64 transforms and a sum per frequency, whose flops are
+        # counted; gridlets in and out, spectra out and in twice
         F, nodes = (2 * p) ** 2 * (p + 1), 8 ** lv
         gl = 2 * (8.0 if lv in FP64_LEVELS else 4.0) * p ** 3 * nodes
-        return (37 if lv == 2 else 189) * 8.0 * F * nodes, "f64 mfma", gl + 4 * 16.0 * F * nodes, 1
+        unit, issued = zone_sum_unit(lv)
+        return (37 if lv == 2 else 189) * 8.0 * F * nodes, unit, gl + 4 * 16.0 * F * nodes, issued
     if name == "near" and route["near"] == "direct":
         fl = 27 * 2.0 * s ** 6 * 8 ** L
         if s in (4, 8, 16):  # FP64 transforms: density in, spectra out and in twice, potential out
@@ -558,7 +567,7 @@ def kernel_work(name, N, L, p, route=None):
             return 27 * 8.0 * F * leaves, "f64 valu", 8.0 * N ** 3 + 4 * 16.0 * F * leaves, 1
         return fl, "f32 valu", None, 1
     r = _default_work(name, N, L, p, s, route.get("fold", False), route.get("zones_fp32_level"))
-    return r + (1,)
+    return r + (zone_sum_unit(int(name.split()[1][1:]))[1] if r[1] == "f64 mfma" else 1,)
 
 
 def _default_work(name, N, L, p, s, fold=False, zones_fp32_level=None):
@@ -570,7 +579,7 @@ def _default_work(name, N, L, p, s, fold=False, zones_fp32_level=None):
         gl = (8.0 if lv in FP64_LEVELS else 4.0) * p ** 3 * nodes  # gridlet buffer
         if name.endswith("stencil"):
             offs = 37 if lv == 2 else 189
-            unit = "f32 valu" if lv == zones_fp32_level else "f64 valu"
+            unit = "f32 valu" if lv == zones_fp32_level else zone_sum_unit(lv)[0]
             return offs * 8.0 * F * nodes, unit, 2 * spec + 343 * 16.0 * F
         if name.endswith("inverse transforms"):
             return None, "hbm", spec + 2 * gl
@@ -595,12 +604,13 @@ def _default_work(name, N, L, p, s, fold=False, zones_fp32_level=None):
 def gemm_m2l_mfma(rho, args):
     """The default interaction zones in split precision on the same density: a
     block-Toeplitz GEMM of split BF16 (three bf16 terms per operand, six
-    products) at the leaf level, FP64 sums per frequency at the FP64 levels
-    2-3.  Per level: HIP-event time of its launches (stages one after another),
-    algorithmic flops (2 p^6 per offset and target node of the GEMM, 8 per
-    offset, target node and frequency of the others), issued flops (times the
-    products) and the fraction of the peak of the instruction that level's
-    sums run on."""
+    products) at the leaf level, FP64 sums per frequency at the FP64 levels:
+    on the vector ALUs at level 2, as octet products on the FP64 matrix cores at
+    level 3.  Per level: HIP-event time of its launches (stages one after another;
+    with the node transforms at levels 2 and 3), algorithmic flops (2 p^6 per
+    offset and target node of the GEMM, 8 per offset, target node and frequency of
+    the others), issued flops (times the products) and the fraction of the peak
+    of the unit that level's sums run on."""
     import torch
     from paper_2011_07099_amd.pfmm import Plan
     phi = torch.empty_like(rho)
@@ -628,12 +638,13 @@ def gemm_m2l_mfma(rho, args):
         levels[str(lv)] = {"ms": ms, "unit": unit, "products": products, "flops": fl,
                            "algorithmic_tflops": tf, "issued_tflops": tf * products, "peak": peak,
                            "algorithmic_frac": tf / peak, "issued_frac": tf * products / peak}
-        issued += fl * products
-        budget += ms * 1e-3 * peak * 1e12
+        if "mfma" in unit:
+            issued += fl * products
+            budget += ms * 1e-3 * peak * 1e12
     return {"route": "default zones in split precision (block-Toeplitz split bf16 at level 4, FP64 "
                      "sums per frequency at levels 2-3), timed on the same density in this run",
-            "util": issued / budget, "util_note": "issued flops of all levels over the "
-            "time-weighted peak of the instruction each level uses",
+            "util": issued / budget, "util_note": "issued flops of the levels whose sums run on the "
+            "matrix cores over the time-weighted peak of the instruction each uses",
             "levels": levels, "m2l_ms": sum(lv_ms.values()),
             "solve_ms_with_direct_near_zone": route_ms,
             "phi": phi}
