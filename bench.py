@@ -54,7 +54,7 @@ FP64_LEVELS = (2, 3)  # coarse levels kept in FP64 (the plan's default at L = 4)
 # x 1, KiB per dispatch scaled to bytes by a plain 1 GiB copy) in the serial
 # solve of the bench route at 256^3, L = 4, p = 8, keyed by the kernel's name
 # in the bench line and the SHA-1 prefix of the sources it was taken on (its
-# file and plan.hip); another route or a changed source reports null until the
+# files and plan.hip); another route or a changed source reports null until the
 # counters are taken again.
 TRAFFIC = {
     ("near leaf transforms", "82ec6b7cc7ad"): 637840080,
@@ -70,8 +70,10 @@ TRAFFIC = {
 }
 TRAFFIC_ROUTE = {"precision": "bf16x3", "near": "fft", "m2l": "spectral", "accel": "none",
                  "zones": "fp32", "N": 256, "L": 4, "p": 8}
-KERNEL_SRC = {"m2l": ("m2l_spectral.hip", "plan.hip"), "near": ("near_fft.hip", "plan.hip"),
-              "p2m": ("updown.hip", "plan.hip"), "l2p": ("updown.hip", "plan.hip")}
+KERNEL_SRC = {"m2l": ("m2l_spectral.hip", "spectral.h", "dft64.h", "plan.hip"),
+              "near": ("near_fft.hip", "plan.hip"),
+              "p2m": ("updown.hip", "columns.h", "plan.hip"),
+              "l2p": ("updown.hip", "columns.h", "plan.hip")}
 
 
 def source_key():

@@ -97,17 +97,22 @@ typedef enum {
 /* Arithmetic of the two contraction-heavy steps (interaction-zone
  * convolution and near zone).  Tabulation of G always runs in FP64. */
 typedef enum {
-  /* FP32 products and FP32 accumulation.  The spectral interaction zones
-   * (PFMM_OPT_M2L) are FP64 in every precision.  With GEMM zones the leaf
-   * level's FP32 sums, which cancel 10^2-10^3 fold, are amplified toward the
-   * leaf corners by L2P's extrapolation beyond the outer gridlet nodes: at
-   * 256^3, p = 8 that leaves 8e-5 of max|phi| against the FP64 reference
-   * FMM (2e-5 relative L2 against PM), against 3e-6 for the spectral zones;
-   * PFMM_OPT_FP64_LEVELS = L - 1 removes it. */
+  /* FP32 fields, and FP32 gridlets on the levels that PFMM_OPT_FP64_LEVELS
+   * leaves.  Single solves sum the zones and the direct near zone in FP64 where
+   * PFMM_M2L_GEMM and PFMM_NEAR_DIRECT say so (p >= 3; leaf edges 4, 8, 16), and
+   * the spectral zones in every precision; elsewhere (p <= 2, leaf edges 1 and
+   * 2, batches of plans on the default routes) they are FP32 products with FP32
+   * accumulation.  The leaf's FP32 gridlets cancel 10^2-10^3 fold and L2P
+   * extrapolates beyond their outer nodes: at 256^3, p = 8 that leaves 1.0e-5 of
+   * max|phi| at leaf corners against FP64 throughout (1.0e-6 relative L2
+   * against PM), 8e-5 (2e-5) with FP32 products, as in batches.
+   * PFMM_OPT_FP64_LEVELS = L - 1 removes it (6e-8, 3e-7). */
   PFMM_PREC_FP32 = 0,
-  /* Split precision: each FP32 operand x is held as hi = bf16(x) and
-   * lo = bf16(x - hi); products hi*hi + hi*lo + lo*hi on the BF16 matrix
-   * cores with FP32 accumulation. */
+  /* Split precision: FP32 operands held as bf16 terms (hi = bf16(x), lo =
+   * bf16(x - hi), and a third in the interaction zones), products of those (hi*hi +
+   * hi*lo + lo*hi, six with three terms) on the BF16 matrix cores with FP32
+   * accumulation: the interaction zones of FP32 levels at p = 8 and, in batches,
+   * near zones of leaf edges 8 and 16.  Everything else as PFMM_PREC_FP32. */
   PFMM_PREC_BF16X3 = 1,
   /* FP64 throughout: every level's gridlets and interaction zones, the mesh
    * transfers and the near zone (PFMM_NEAR_DIRECT in FP64, whatever
@@ -137,12 +142,14 @@ typedef enum {
    * pfmm_plan_level_times and pfmm_plan_kernel_times read them.  1: the
    * near zone runs on the plan's stream before the tree, so every interval
    * is a stage alone on the device.  2: the near zone stays beside the tree
-   * as in an unprofiled solve (live durations of overlapped kernels).
+   * as in an unprofiled solve (live durations of overlapped kernels).  The
+   * transfers around FP64 levels, which other solves fuse with the node
+   * transforms, run as kernels of their own in both (same results).
    * Default 0. */
   PFMM_OPT_PROFILE = 4,
   /* value: int32 in [0, 30]: keep the gridlet masses and potentials of the
-   * coarsest levels 2 .. 1+value (those the tree has) in FP64, with their M2M, interaction-zone
-   * sums (on the FP64 matrix cores at p = 8) and L2L in FP64.  The downward
+   * coarsest levels 2 .. 1+value (those the tree has) in FP64, with their M2M,
+   * interaction-zone sums and L2L in FP64.  The downward
    * interpolation (Eq. 7, and its leaf analogue when s > p) extrapolates past
    * a parent's outermost gridlet nodes, so rounding noise in a coarse field
    * is amplified on its way to the mesh, most at leaf corners.  Default
@@ -444,12 +451,13 @@ pfmm_status pfmm_plan_destroy(pfmm_plan_t plan);
  * interaction-zone level and near zone of every field, split into workgroup
  * tiles of targets of one class):
  *   - the near zone of a plan in PFMM_PREC_BF16X3 with 8^3-cell sub-blocks
- *     (leaf width 8 or 16) runs on the BF16 matrix cores, 2-term split, as in
- *     pfmm_solve;
+ *     (leaf width 8 or 16) runs on the BF16 matrix cores, 2-term split;
  *   - FP64 levels at p = 8 run on the FP64 matrix cores;
  *   - everything else runs in the portable kernel: FP64 levels in FP64, the
  *     rest in FP32 with FP64 per-offset running totals.
  * Each list is drained by one persistent kernel through an atomic counter.
+ * (pfmm_solve sums most of these in FP64 by transforms, PFMM_NEAR_DIRECT and
+ * PFMM_M2L_GEMM: a batch's results differ from it by the rounding above.)
  * A plan with PFMM_NEAR_FFT (leaf edges 4, 8, 16 only) has no near-zone
  * items, and one with PFMM_M2L_SPECTRAL no interaction-zone items: their
  * transforms and stencils run as their own kernels in the same graph,

@@ -157,12 +157,15 @@ __device__ __forceinline__ void l2l_block(LOAD&& load, TO* __restrict__ Pc, cons
 // holds a column of cells or nodes in registers, the weights are scalars.  P2M
 // contracts z, y, x (mesh rows in the first pass), L2P expands z, y, x (the last
 // pass writes the mesh, its prior values read before the first).  Any
-// alignment.  FP32 gridlets of p = 4 and 8 keep the kernels above, whose rows
-// move as float4 (256^3, p = 8: P2M 29 us there and 24 here, L2P 35 and 34, 512^3 175
-// and 159, 247 and 262; p = 4 alike).  Bound: latency of the three passes up to some
-// 10^3 leaves, then the mesh's traffic.  Measured before (one output a thread,
-// both factors of every product from LDS) / after, FP64 gridlets, 512 leaves of s
-// = 16, p = 6: P2M 18 / 8 us, L2P 20 / 6; p = 8, 19 / 6 and 23 / 5.5.
+// alignment.  FP32 gridlets of p = 4 and 8 at s = 8 and 16 keep the row kernels of
+// updown.hip (k_p2m, k_l2p): L2P is no faster here (256^3, p = 8: 35 us there, 34 here;
+// 512^3 247 and 262), and P2M, which is faster (29 and 24, 175 and 159), would sum
+// in another order: results would move by their FP32 rounding, which L2P's
+// extrapolation amplifies at leaf corners, and be no closer to FP64.  Bound:
+// latency of the three passes up to some 10^3 leaves, then the mesh's traffic.
+// Measured before (one output a thread, both factors of every product from LDS) /
+// after, FP64 gridlets, 512 leaves of s = 16, p = 6: P2M 18 / 8 us, L2P 20 / 6; p = 8,
+// 19 / 6 and 23 / 5.5.
 
 template <int S, int P>
 constexpr int p2m_col_words() { return (S * S + S * P) * (P | 1); }

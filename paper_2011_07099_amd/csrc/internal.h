@@ -6,6 +6,7 @@
 
 #include <cstdint>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 namespace pfmm {
@@ -17,6 +18,17 @@ namespace pfmm {
 // the second half of a line then comes from that XCD's L2 instead of HBM.
 __device__ __forceinline__ int64_t xcd_leaf(int64_t i, int64_t n) {
   return (n & 7) ? i : (i & 7) * (n >> 3) + (i >> 3);
+}
+
+// f(P) for the gridlet size p of LO .. HI as a template argument
+template <int LO, int HI, class F>
+hipError_t with_p(int p, F&& f) {
+  if constexpr (LO > HI) {
+    return hipErrorInvalidValue;
+  } else {
+    if (p == LO) return f(std::integral_constant<int, LO>());
+    return with_p<LO + 1, HI>(p, f);
+  }
 }
 
 // Optional timing of a routine's kernels: begin() before and end(part) after
@@ -394,7 +406,9 @@ hipError_t m2l_spectral_level(const M2LSpectral* f, int l, const void* Ml, int m
 // node transforms from the children's masses, or from the mesh (leaves of 4, 8
 // or 16 cells; rho64: an FP64 mesh); the sums per frequency; the inverse
 // transforms, added to Pl (accumulate), and what follows from the result: the
-// children's local values, or the mesh's (added to phi).
+// children's local values, or the mesh's (added to phi).  Gridlets of 9 and 10 take
+// the separate kernels so far (a solve of 32^3, L = 3, p = 9 160 us, 140 fused; 64^3,
+// p = 10 201 and 175).
 bool fused_zones(const M2LSpectral* f, int p);
 hipError_t fused_m2m(const M2LSpectral* f, int l, const void* Mc, int c64, double* Mp, Weights T, hipStream_t st);
 hipError_t fused_p2m(const M2LSpectral* f, int l, const void* rho, int rho64, double* M, Weights A, int N, int s,

@@ -5,7 +5,6 @@
 #include "dft64.h"
 #include "internal.h"
 
-#include <type_traits>
 #include <vector>
 
 namespace pfmm {
@@ -160,17 +159,6 @@ __device__ __forceinline__ void node_inv_block(const TS* __restrict__ spec, int6
       const double v = fma(2.0, b, u[0].x + ((z & 1) ? -u[P].x : u[P].x));
       store(r * P + z, v);
     }
-  }
-}
-
-// f(P) for the gridlet size p of LO .. HI as a template argument
-template <int LO, int HI, class F>
-hipError_t with_p(int p, F&& f) {
-  if constexpr (LO > HI) {
-    return hipErrorInvalidValue;
-  } else {
-    if (p == LO) return f(std::integral_constant<int, LO>());
-    return with_p<LO + 1, HI>(p, f);
   }
 }
 

@@ -20,8 +20,6 @@
 #include "columns.h"
 #include "internal.h"
 
-#include <type_traits>
-
 namespace pfmm {
 namespace {
 
@@ -325,24 +323,6 @@ inline size_t p2m_words_rows(int s, int p) {
 }
 
 namespace {
-// f(P) for the gridlet size p of 1 .. 10 as a template argument
-template <class F>
-hipError_t with_p(int p, F&& f) {
-  switch (p) {
-    case 1: return f(std::integral_constant<int, 1>());
-    case 2: return f(std::integral_constant<int, 2>());
-    case 3: return f(std::integral_constant<int, 3>());
-    case 4: return f(std::integral_constant<int, 4>());
-    case 5: return f(std::integral_constant<int, 5>());
-    case 6: return f(std::integral_constant<int, 6>());
-    case 7: return f(std::integral_constant<int, 7>());
-    case 8: return f(std::integral_constant<int, 8>());
-    case 9: return f(std::integral_constant<int, 9>());
-    case 10: return f(std::integral_constant<int, 10>());
-    default: return hipErrorInvalidValue;
-  }
-}
-
 // P2M, L2P by columns where the leaf has 4, 8 or 16 cells, else the general form
 template <class TR, class TO, class W>
 hipError_t p2m_any(const TR* rho, TO* M, Weights A, int N, int s, int p, W h3, hipStream_t st) {
@@ -353,7 +333,7 @@ hipError_t p2m_any(const TR* rho, TO* M, Weights A, int N, int s, int p, W h3, h
     return hipGetLastError();
   }
   const int vec = ((uintptr_t)rho & 15) == 0;
-  return with_p(p, [&](auto P) {
+  return with_p<1, 10>(p, [&](auto P) {
     constexpr int p_ = decltype(P)::value;
     if (s == 16)
       hipLaunchKernelGGL((k_p2m_cols<TR, TO, W, 16, p_>), g, b, 0, st, rho, M, A, N, h3, vec);
@@ -376,7 +356,7 @@ hipError_t l2p_any(const TI* P, TP* out, Weights Wx, Weights Wy, Weights Wz, W s
                        p, accumulate);
     return hipGetLastError();
   }
-  return with_p(p, [&](auto Pc) {
+  return with_p<1, 10>(p, [&](auto Pc) {
     constexpr int p_ = decltype(Pc)::value;
     if (s == 16)
       hipLaunchKernelGGL((k_l2p_cols<TI, TP, W, 16, p_>), g, b, 0, st, P, out, Wx, Wy, Wz, scale, N, accumulate);
@@ -414,7 +394,7 @@ hipError_t launch_m2m(const void* Mc, int c64, void* Mp, int p64, Weights T, int
                       hipStream_t st) {
   if (c64 && !p64) return hipErrorInvalidValue;  // a finer level is never wider than its parent
   const dim3 g(np * np * np), b(kThreads);
-  return with_p(p, [&](auto P) {
+  return with_p<1, 10>(p, [&](auto P) {
     constexpr int p_ = decltype(P)::value;
     if (!p64)
       hipLaunchKernelGGL((k_m2m<float, float, float, p_>), g, b, 0, st, (const float*)Mc, (float*)Mp, T, np);
@@ -431,7 +411,7 @@ hipError_t launch_l2l(const void* Pp, int p64, void* Pc, int c64, Weights T, int
                       hipStream_t st, int accumulate) {
   if (c64 && !p64) return hipErrorInvalidValue;
   const dim3 g(np * np * np), b(kThreads);
-  return with_p(p, [&](auto P) {
+  return with_p<1, 10>(p, [&](auto P) {
     constexpr int p_ = decltype(P)::value;
     if (!p64)
       hipLaunchKernelGGL((k_l2l<float, float, float, p_>), g, b, 0, st, (const float*)Pp, (float*)Pc, T, np,

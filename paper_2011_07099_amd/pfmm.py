@@ -177,15 +177,17 @@ class Plan:
         _check(load().pfmm_plan_set(self._h, OPT_FOLD, ctypes.byref(v), 4))
 
     def set_near(self, mode):
-        """Leaf near zone by "direct" summation (block Toeplitz) or "fft"
-        (convolution on the doubled grid, one transform per leaf)."""
+        """Leaf near zone "direct" (the exact sum: FP64 transforms per leaf at
+        leaf edges 4, 8, 16, else block Toeplitz) or "fft" (FP32 convolution on
+        the doubled grid, one transform per leaf)."""
         v = ctypes.c_int32(NEAR[mode])
         _check(load().pfmm_plan_set(self._h, OPT_NEAR, ctypes.byref(v), 4))
 
     def set_m2l(self, mode):
-        """Interaction zones by "gemm" (block Toeplitz), "fft" (the HPM FFT
-        convolution, a comparator) or "spectral" (per-node transforms and a
-        per-frequency stencil, FP64; p = 4, 6 or 8)."""
+        """Interaction zones by "gemm" (the default: the sum over every offset,
+        in single solves with p >= 3 by per-node FP64 transforms, else block
+        Toeplitz), "fft" (the HPM FFT convolution, a comparator) or "spectral"
+        (per-node FP64 transforms on every level; p = 4, 6 or 8)."""
         v = ctypes.c_int32(M2L[mode])
         _check(load().pfmm_plan_set(self._h, OPT_M2L, ctypes.byref(v), 4))
 

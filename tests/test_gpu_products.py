@@ -20,7 +20,7 @@ from gpu_util import f32, rel_max
 pytestmark = pytest.mark.gpu
 
 
-@pytest.fixture
+@pytest.fixture(scope="module")
 def full_card():
     """Somewhat more than three quarters of the card's memory held."""
     import torch
