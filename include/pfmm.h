@@ -457,7 +457,9 @@ pfmm_status pfmm_plan_destroy(pfmm_plan_t plan);
  *     rest in FP32 with FP64 per-offset running totals.
  * Each list is drained by one persistent kernel through an atomic counter.
  * (pfmm_solve sums most of these in FP64 by transforms, PFMM_NEAR_DIRECT and
- * PFMM_M2L_GEMM: a batch's results differ from it by the rounding above.)
+ * PFMM_M2L_GEMM: a batch's results differ from it by the rounding above, and a
+ * loop of single solves over plans on the default routes is faster; batches
+ * are meant for PFMM_NEAR_FFT and PFMM_M2L_SPECTRAL plans.)
  * A plan with PFMM_NEAR_FFT (leaf edges 4, 8, 16 only) has no near-zone
  * items, and one with PFMM_M2L_SPECTRAL no interaction-zone items: their
  * transforms and stencils run as their own kernels in the same graph,
