@@ -225,8 +225,9 @@ typedef enum {
    * leaf edges 4, 8 or 16 sum it in FP64 in every precision, each leaf pair as
    * a cyclic convolution on the doubled grid (exact up to FP64 rounding;
    * buffers of about 140 bytes per cell, at most 3 GiB unless two planes of
-   * leaves need more, made with the plan and kept while it lives, also when
-   * other routes are selected: a captured solve may use them).  Other leaf edges,
+   * leaves need more, made with the plan; given back where another route is
+   * selected before the first solve, kept from then on while the plan lives, as
+   * a captured solve may use them).  Other leaf edges,
    * batches, and plans made when those buffers would leave less than a quarter
    * of the device's memory free use a block-Toeplitz GEMM (matrix cores or the
    * portable kernel, as PFMM_OPT_PRECISION selects).  Any alignment. */

@@ -74,6 +74,8 @@ struct pfmm_plan_s {
   int zones_f32 = 0;              // FP32 columns in the 16^3 spectral stencil (PFMM_OPT_ZONES_FP32)
   NearFft* nfft = nullptr;        // its plans, buffers and transformed kernels
   Near64* n64 = nullptr;          // the direct near zone by FP64 transforms (s = 4, 8, 16)
+  int n64_returned = 0;           // given back before the first solve (PFMM_OPT_NEAR)
+  int solved = 0;                 // a solve has been enqueued: graphs may hold the buffers
   uint16_t* zero = nullptr;       // 512 zero bf16 values: the source outside an isolated box
   // accelerations from the expansion (PFMM_OPT_ACCEL; tables on first use)
   int accel_mode = 0;
@@ -385,9 +387,9 @@ bool spare_memory(size_t bytes) {
 // the leaf edges it serves, made with the plan; without the memory for it the
 // plan keeps the block-Toeplitz sum.  Split precision takes it too: at 256^3, s =
 // 16, 1.21 ms in FP64 against 7.6-8.1 ms for the bf16 products on the matrix
-// cores.  It lives as long as the plan, whatever the options become: a solve
-// captured into a graph holds its buffers, and its kernels follow G like the
-// tables do.
+// cores.  From the first solve on it lives as long as the plan, whatever the
+// options become: a solve captured into a graph holds its buffers, and its
+// kernels follow G like the tables do.
 pfmm_status create_near64(pfmm_plan_s* pl) {
   if (pl->s != 4 && pl->s != 8 && pl->s != 16) return PFMM_OK;
   if (!spare_memory(near64_bytes(pl->N, pl->s))) return PFMM_OK;
@@ -409,6 +411,26 @@ pfmm_status refresh_near64(pfmm_plan_s* pl, int first) {
   hipError_t e = near64_tables(pl->n64, tabs, first, pl->accel_mode ? 4 : 1, h3, pl->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(pl->stream);
   return e == hipSuccess ? PFMM_OK : hip_fail(e, "FP64 near zone");
+}
+
+// After a change of the near-zone option or the precision.  Until the plan's
+// first solve nothing can hold the buffers, so a plan that is set to the FFT near
+// zone right after its creation gives them back (2.4 GB at 256^3), and takes
+// them again if it is set back.
+pfmm_status select_near64(pfmm_plan_s* pl) {
+  const bool wanted = pl->prec == PFMM_PREC_FP64 || !pl->near_fft;
+  if (!wanted && pl->n64 && !pl->solved) {
+    near64_destroy(pl->n64);
+    pl->n64 = nullptr;
+    pl->n64_returned = 1;
+  } else if (wanted && pl->n64_returned) {
+    pl->n64_returned = 0;
+    pfmm_status r = create_near64(pl);
+    if (r == PFMM_OK) r = refresh_near64(pl, 0);
+    const hipError_t e = r == PFMM_OK ? hipStreamSynchronize(pl->stream) : hipSuccess;
+    return e == hipSuccess ? r : hip_fail(e, "FP64 near zone");
+  }
+  return PFMM_OK;
 }
 
 // The default zones (PFMM_M2L_GEMM) of a single solve go by per-node FP64
@@ -886,7 +908,7 @@ pfmm_status pfmm_plan_set(pfmm_plan_t h, int option, const void* value, size_t b
                                             "in 64 KiB of LDS at this leaf width and p");
       }
       pl->prec = v;
-      return PFMM_OK;
+      return select_near64(pl);
     }
     case PFMM_OPT_ZONES_FP32: {
       if (bytes != sizeof(int32_t)) return fail(PFMM_ERR_INVALID_ARG, "zones_fp32 is an int32");
@@ -1047,7 +1069,7 @@ pfmm_status pfmm_plan_set(pfmm_plan_t h, int option, const void* value, size_t b
         }
       }
       pl->near_fft = v;
-      return PFMM_OK;
+      return select_near64(pl);
     }
     case PFMM_OPT_FP64_LEVELS: {
       if (bytes != sizeof(int32_t)) return fail(PFMM_ERR_INVALID_ARG, "fp64 levels is an int32");
@@ -1118,6 +1140,7 @@ pfmm_status solve_impl(pfmm_plan_s* pl, const void* rho_in, void* phi_out, void*
       (accel_out && accel_out == phi_out))
     return fail(PFMM_ERR_INVALID_ARG, "buffers must not alias");
   const bool f64 = pl->prec == PFMM_PREC_FP64;
+  pl->solved = 1;
   if (io64 && !f64) return fail(PFMM_ERR_INVALID_ARG, "FP64 buffers need a PFMM_PREC_FP64 plan");
   // FP64 precision sums the near zone directly in FP64, whatever PFMM_OPT_NEAR says
   const bool near_fft = pl->near_fft && !f64;

@@ -30,8 +30,11 @@ def test_precision_and_near_zone_options_wait_for_nothing():
     rho = density(N, 921)
     out = torch.empty_like(rho), torch.empty((3, N, N, N), device="cuda")
     with Plan(N, 3, 8, "S1", stream=s, accel="expansion") as work, Plan(64, 3, 8, "S1", stream=s) as pl:
+        small = density(64, 925)
+        pl.solve(small, torch.empty_like(small))
         pl.set_near("fft")                 # its buffers, on first use
         pl.set_near("direct")
+        torch.cuda.synchronize()
         busy(work, rho, out, s)
         assert not s.query()               # the stream is busy
         for name, value in (("set_precision", "bf16x3"), ("set_near", "fft"), ("set_precision", "fp64"),

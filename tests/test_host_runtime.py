@@ -69,9 +69,9 @@ def test_options_free_nothing(fake, N, L, p):
     (temporaries of a tabulation, made and freed in one call, aside)."""
     run(fake, """
 h = create(%d, %d, %d)
+assert lib.pfmm_solve(h, A, B, None) == 0
 log()
 before = hip.fake_used()
-made = set()
 for option, value in ((pfmm.OPT_NEAR, 1), (pfmm.OPT_PRECISION, 2), (pfmm.OPT_PRECISION, 0), (pfmm.OPT_NEAR, 0),
                       (pfmm.OPT_M2L, M2L["spectral"]), (pfmm.OPT_ACCEL, 1), (pfmm.OPT_NEAR, 1),
                       (pfmm.OPT_M2L, M2L["gemm"]), (pfmm.OPT_PRECISION, 1), (pfmm.OPT_GS_A1, -0.1)):
@@ -91,6 +91,7 @@ assert hip.fake_used() == 0, hip.fake_used()
 def test_precision_and_near_zone_options_run_nothing(fake):
     run(fake, """
 h = create(64, 3, 8)
+assert lib.pfmm_solve(h, A, B, None) == 0
 assert put(h, pfmm.OPT_NEAR, 1) == 0 and put(h, pfmm.OPT_NEAR, 0) == 0   # its buffers, on first use
 log()
 for option, value in ((pfmm.OPT_PRECISION, 1), (pfmm.OPT_NEAR, 1), (pfmm.OPT_PRECISION, 2),
@@ -188,4 +189,28 @@ h = create(1024, 8, 1)
 assert put(h, pfmm.OPT_NEAR, 1) == 2, lib.pfmm_last_error()
 h = create(512, 7, 1)
 assert put(h, pfmm.OPT_NEAR, 1) == 0
+""")
+
+
+def test_a_plan_set_to_another_near_zone_before_its_first_solve_gives_buffers_back(fake):
+    """Plan(..., near="fft") does not hold the direct near zone's 140 bytes a cell;
+    set back, it has them and their kernels again, and after a solve it keeps them."""
+    run(fake, """
+N = 128
+h = create(N, 3, 8)
+log()
+for _ in range(2):
+    before = hip.fake_used()
+    assert put(h, pfmm.OPT_NEAR, 1) == 0
+    assert before - hip.fake_used() > 30 * N ** 3      # 140 bytes a cell less the FFT near zone's on first use
+    log()
+    assert put(h, pfmm.OPT_NEAR, 0) == 0
+    lines = log()
+    assert sum("k_kz64" in l for l in lines) == 1 and lines[-1].startswith("sync"), lines
+assert put(h, pfmm.OPT_NEAR, 1) == 0 and put(h, pfmm.OPT_PRECISION, 2) == 0    # FP64: direct, whatever the option
+assert lib.pfmm_solve(h, A, B, None) == 0
+assert "k_fwd64" in " ".join(log())
+used = hip.fake_used()
+assert put(h, pfmm.OPT_PRECISION, 0) == 0 and put(h, pfmm.OPT_NEAR, 0) == 0 and put(h, pfmm.OPT_NEAR, 1) == 0
+assert hip.fake_used() == used and log() == []
 """)
