@@ -242,9 +242,7 @@ typedef enum {
    * does not apply to it.  With PFMM_ACCEL_EXPANSION the three acceleration
    * kernels reuse the forward transforms.  For leaf edges s = 4, 8, 16 the
    * transforms are the library's own (one workgroup per leaf, in LDS, reading
-   * and writing the mesh directly; 1024^3 cells in leaves of 4, whose spectra
-   * are beyond their 32-bit offsets, are refused with PFMM_ERR_UNSUPPORTED);
-   * other s use rocFFT on zero-padded blocks.
+   * and writing the mesh directly); other s use rocFFT on zero-padded blocks.
    * pfmm_solve then needs density, potential and accel 16-byte aligned
    * (PFMM_ERR_INVALID_ARG otherwise). */
   PFMM_NEAR_FFT = 1

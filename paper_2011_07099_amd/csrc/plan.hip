@@ -1051,10 +1051,6 @@ pfmm_status pfmm_plan_set(pfmm_plan_t h, int option, const void* value, size_t b
       std::memcpy(&v, value, sizeof v);
       if (v != PFMM_NEAR_DIRECT && v != PFMM_NEAR_FFT)
         return fail(PFMM_ERR_INVALID_ARG, "unknown near-zone mode");
-      // the stencil of the library's own transforms addresses a chunk of 64
-      // frequencies (512 bytes per leaf) with 32-bit offsets
-      if (v == PFMM_NEAR_FFT && pl->s >= 4 && cube(pl->N / pl->s) * 512 >= (int64_t)1 << 32)
-        return fail(PFMM_ERR_UNSUPPORTED, "the FFT near zone serves up to 128 leaves of 4 cells per axis");
       if (v == PFMM_NEAR_FFT && !pl->nfft) {
         NearFft* f = nullptr;
         const hipError_t e = near_fft_create(pl->N, pl->s, &f);

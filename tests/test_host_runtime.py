@@ -181,17 +181,6 @@ assert hip.fake_used() == 0
 """)
 
 
-def test_the_fft_near_zone_refuses_more_leaves_than_its_offsets_reach(fake):
-    """256^3 leaves of 4 cells: a chunk of the spectra has 8 GiB, which the
-    stencil's 32-bit buffer size held as 0 (every source read as zero)."""
-    run(fake, """
-h = create(1024, 8, 1)
-assert put(h, pfmm.OPT_NEAR, 1) == 2, lib.pfmm_last_error()
-h = create(512, 7, 1)
-assert put(h, pfmm.OPT_NEAR, 1) == 0
-""")
-
-
 def test_a_plan_set_to_another_near_zone_before_its_first_solve_gives_buffers_back(fake):
     """Plan(..., near="fft") does not hold the direct near zone's 140 bytes a cell;
     set back, it has them and their kernels again, and after a solve it keeps them."""
