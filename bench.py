@@ -57,16 +57,16 @@ FP64_LEVELS = (2, 3)  # coarse levels kept in FP64 (the plan's default at L = 4)
 # files and plan.hip); another route or a changed source reports null until the
 # counters are taken again.
 TRAFFIC = {
-    ("near leaf transforms", "5fcb55a4fe89"): 637781090,
-    ("near stencil", "5fcb55a4fe89"): 1326349832,
-    ("near inverse transforms", "5fcb55a4fe89"): 655806190,
-    ("p2m", "8eb4d39e8559"): 75793120,
-    ("l2p", "8eb4d39e8559"): 143398954,
-    ("m2l L4 node transforms", "1764f23ad44b"): 84221622,
-    ("m2l L4 stencil", "1764f23ad44b"): 163778337,
-    ("m2l L4 inverse transforms", "1764f23ad44b"): 92437859,
-    ("m2l L3 stencil", "1764f23ad44b"): 50542941,
-    ("m2l L2 stencil", "1764f23ad44b"): 19812439,
+    ("near leaf transforms", "63b18dd950ab"): 637854558,
+    ("near stencil", "63b18dd950ab"): 1325060045,
+    ("near inverse transforms", "63b18dd950ab"): 655614670,
+    ("p2m", "b817a1f8d1b0"): 75568108,
+    ("l2p", "b817a1f8d1b0"): 143371562,
+    ("m2l L4 node transforms", "10c73c98fadf"): 84157174,
+    ("m2l L4 stencil", "10c73c98fadf"): 163767073,
+    ("m2l L4 inverse transforms", "10c73c98fadf"): 92430819,
+    ("m2l L3 stencil", "10c73c98fadf"): 50542941,
+    ("m2l L2 stencil", "10c73c98fadf"): 19812439,
 }
 TRAFFIC_ROUTE = {"precision": "bf16x3", "near": "fft", "m2l": "spectral", "accel": "none",
                  "zones": "fp32", "N": 256, "L": 4, "p": 8}
